@@ -48,27 +48,6 @@
 namespace trevr {
 
 // ------------------------------------------------------ active buckets
-// One row of the grid per scene (blockIdx.y); buckets of all scenes are
-// appended to one list, with their scene.
-__global__ void k_active_buckets(const DevTree* __restrict__ TT, const uint8_t* active,
-                                 uint32_t* blist, uint32_t* bscene, uint32_t* bnact,
-                                 uint32_t* nb) {
-  const DevTree& T = TT[blockIdx.y];
-  const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (p >= T.num_nodes) return;
-  const uint4 nk = T.nk[p];
-  if (!(nk.w & META_LEAF)) return;
-  const uint8_t* act = active ? active + T.eoff : nullptr;
-  const uint2 lk = T.nlink[p];
-  uint32_t cnt = 0;
-  for (uint32_t s = lk.x; s < lk.x + lk.y; ++s) cnt += (act == nullptr || act[T.perm[s]]) ? 1u : 0u;
-  if (cnt == 0) return;
-  const uint32_t b = atomicAdd(nb, 1u);
-  blist[b] = (uint32_t)p;
-  bscene[b] = blockIdx.y;
-  bnact[b] = cnt;
-}
-
 // Order-independent 64-bit fingerprint of the active set: the sum over
 // active input indices i of a 64-bit mix of i (splitmix64 finaliser).  A
 // backward call compares it with the forward's to decide whether the
@@ -102,6 +81,73 @@ __global__ void __launch_bounds__(256) k_active_hash(const DevTree* __restrict__
   }
 }
 
+// The buckets with active members, and the fingerprint of the active set in
+// the same pass (the members' flags are read once).  One row of the grid per
+// scene (blockIdx.y); buckets of all scenes are appended to one list, with
+// their scene.  A workgroup takes kActNodes nodes per thread and appends its
+// buckets with one atomic, adds its hashes with another: both addresses are
+// shared by the whole launch and their atomics queue (one append per
+// wavefront of 64 nodes took 125 us at 2^21 elements, and the fingerprint 25
+// us in a launch of its own).
+constexpr int kActNodes = 4;
+__global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restrict__ TT,
+                                                        const uint8_t* active, uint32_t* blist,
+                                                        uint32_t* bscene, uint32_t* bnact,
+                                                        uint32_t* nb, unsigned long long* hash) {
+  __shared__ unsigned long long part[4];
+  __shared__ uint32_t wcnt[kActNodes][4], base_s;
+  const DevTree& T = TT[blockIdx.y];
+  const uint8_t* act = active ? active + T.eoff : nullptr;
+  const int t = threadIdx.x, wv = t >> 6;
+  const int64_t p0 = blockIdx.x * (int64_t)(256 * kActNodes) + t;
+  uint32_t cnt[kActNodes];
+  int pos[kActNodes];
+  unsigned long long v = 0ull;
+#pragma unroll
+  for (int r = 0; r < kActNodes; ++r) {
+    const int64_t p = p0 + 256 * r;
+    cnt[r] = 0u;
+    if (p < T.num_nodes && (T.nk[p].w & META_LEAF)) {
+      const uint2 lk = T.nlink[p];
+      for (uint32_t s = lk.x; s < lk.x + lk.y; ++s) {
+        const uint32_t i = T.perm[s];
+        if (act == nullptr || act[i]) {
+          ++cnt[r];
+          v += mix64((unsigned long long)(T.eoff + i) + 1ull);
+        }
+      }
+    }
+    const uint64_t m = ballot64(cnt[r] != 0u);
+    pos[r] = mbcnt(m);
+    if ((t & 63) == 0) wcnt[r][wv] = (uint32_t)__popcll(m);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += (unsigned long long)__shfl_xor((long long)v, o);
+  if ((t & 63) == 0) part[wv] = v;
+  __syncthreads();
+  if (t == 0) {
+    uint32_t tot = 0;
+    for (int r = 0; r < kActNodes; ++r)
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t c = wcnt[r][w];
+        wcnt[r][w] = tot;
+        tot += c;
+      }
+    base_s = tot ? atomicAdd(nb, tot) : 0u;
+    const unsigned long long sum = part[0] + part[1] + part[2] + part[3];
+    if (sum) atomicAdd(hash, sum);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kActNodes; ++r) {
+    if (cnt[r] == 0u) continue;
+    const uint32_t b = base_s + wcnt[r][wv] + (uint32_t)pos[r];
+    blist[b] = (uint32_t)(p0 + 256 * r);
+    bscene[b] = blockIdx.y;
+    bnact[b] = cnt[r];
+  }
+}
+
 // p-p radius (Section 2.4): past every bucket member by its size, then grown
 // until no element inside is wider than the beam there (w r).  One
 // wavefront per bucket.
@@ -120,8 +166,7 @@ __global__ void __launch_bounds__(64) k_setup(const DevTree* __restrict__ TT, It
                                               uint32_t* stage, uint32_t stage_cap) {
   __shared__ uint32_t stack[SC];
   const int lane = threadIdx.x;
-  const uint32_t b = grid_item(I);
-  if (b == kNoItem) return;
+  for (uint32_t b = grid_item(I); b != kNoItem; b = grid_next(I, b)) {
   const DevTree& T = TT[bscene[b]];
   const uint32_t leaf = blist[b];
   double c[3];
@@ -168,6 +213,8 @@ __global__ void __launch_bounds__(64) k_setup(const DevTree* __restrict__ TT, It
     if (stage_cap) stage[(size_t)b * stage_cap] = o.out ? o.nrun : kNoRuns;
     if (overflow) atomicOr(ovf, OVF_SETUP);
   }
+  __syncthreads();
+  }
 }
 
 // One workgroup (one wavefront) per bucket: a plain grid, since most buckets
@@ -192,10 +239,9 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
   constexpr int kWords = SC / 2 > (int)kSortRuns ? SC / 2 : (int)kSortRuns;
   __shared__ unsigned long long lds[kWords];   // the traversal stack, or sort keys
   const uint32_t lane = threadIdx.x;
-  const uint32_t b = blockIdx.x;
-  if (b >= rng[1]) return;
+  for (uint32_t b = blockIdx.x; b < rng[1]; b += gridDim.x, __syncthreads()) {
   const DevTree& T = TT[bscene[b]];
-  if (!(T.flags & TREVR_NEAR_FIELD)) return;
+  if (!(T.flags & TREVR_NEAR_FIELD)) continue;
   const uint32_t nl = nlumc[b];
   uint32_t* out = nidx + noff[b];
   const uint32_t* sg = stage_cap ? stage + (size_t)bsrc[b] * stage_cap : nullptr;
@@ -240,7 +286,7 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
       bl += tl;
       bd += td;
     }
-    return;
+    continue;
   }
   double c[3];
   leaf_centre(T, blist[b], c);
@@ -255,7 +301,7 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
   uint32_t* bits = reinterpret_cast<uint32_t*>(lds);
   constexpr uint32_t kBitWords = 2u * (uint32_t)kWords;
   const uint32_t words = (uint32_t)((T.n + 31) / 32), n = noff[b + 1] - noff[b];
-  if (overflow || words > kBitWords) return;
+  if (overflow || words > kBitWords) continue;
   for (int part = 0; part < 2; ++part) {
     const uint32_t lo = part ? nl : 0u, hi = part ? n : nl;
     if (hi - lo < 2u) continue;
@@ -280,6 +326,7 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
       }
     }
   }
+  }
 }
 
 // ------------------------------------------------------------- the walk
@@ -294,8 +341,7 @@ __global__ void __launch_bounds__(64) k_walk(const DevTree* __restrict__ TT, Ite
   __shared__ uint32_t stack[SC];
   __shared__ uint32_t lfirst[64], lbeg[64];
   const int lane = threadIdx.x;
-  const uint32_t bucket = grid_item(I);
-  if (bucket == kNoItem) return;
+  for (uint32_t bucket = grid_item(I); bucket != kNoItem; bucket = grid_next(I, bucket)) {
   const DevTree& T = TT[bscene[bucket]];
   const uint32_t leafb = blist[bucket];
   const double r = brad[bucket];
@@ -416,6 +462,8 @@ __global__ void __launch_bounds__(64) k_walk(const DevTree* __restrict__ TT, Ite
     if (ncut > __atomic_load_n(ovf + 1, __ATOMIC_RELAXED)) atomicMax(ovf + 1, ncut);
     atomic_max_u64(&T.counters[CNT_MAX_CUT], ncut);
     atomic_max_u64(&T.counters[CNT_MAX_STACK], (unsigned long long)maxsp);
+  }
+  __syncthreads();
   }
 }
 
@@ -1349,13 +1397,29 @@ __global__ void __launch_bounds__(256) k_cost_bins(const DevTree* __restrict__ T
   }
 }
 
-// After the exclusive scan of the bins: rng[2 + 2c], rng[3 + 2c] get the
-// range of the buckets with c + 1 bands.
-__global__ void k_class_ranges(const uint32_t* bins, uint32_t* rng) {
-  const int cl = threadIdx.x;
-  if (cl >= kMaxBands) return;
-  rng[2 + 2 * cl] = bins[cl * kOrderBins];
-  rng[3 + 2 * cl] = cl + 1 < kMaxBands ? bins[(cl + 1) * kOrderBins] : rng[1];
+// Exclusive scan of the bins in place, then the range of the buckets with
+// c + 1 bands in rng[2 + 2c], rng[3 + 2c].  One workgroup of 1024 threads.
+// Heaviest-first order uses the first kCostBins bins of each band count only,
+// fewer than the threads, so one step scans them (scanning all 65536 words
+// took 61 us of every call, a quarter of the smallest one; now 4 us).
+__global__ void __launch_bounds__(1024) k_scan_bins(uint32_t* bins, uint32_t order,
+                                                    uint32_t* rng) {
+  static_assert(kMaxBands * kCostBins <= 1024, "one bin per thread");
+  const int t = threadIdx.x;
+  if (order == ORDER_COST) {
+    const bool in = t < kMaxBands * kCostBins;
+    uint32_t* a = bins + (t / kCostBins) * kOrderBins + t % kCostBins;
+    const uint32_t v = in ? *a : 0u;
+    const uint32_t e = block_excl_u32(v, nullptr);
+    if (in) *a = e;
+  } else {
+    block_scan_u32(bins, (int64_t)kMaxBands * kOrderBins, nullptr);
+  }
+  __syncthreads();
+  if (t < kMaxBands) {
+    rng[2 + 2 * t] = bins[t * kOrderBins];
+    rng[3 + 2 * t] = t + 1 < kMaxBands ? bins[(t + 1) * kOrderBins] : rng[1];
+  }
 }
 
 __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
@@ -1446,6 +1510,16 @@ static unsigned grid_of(int64_t work, int threads) {
   return (unsigned)std::max<int64_t>(1, (work + threads - 1) / threads);
 }
 
+// Grid of the kernels of one wavefront per bucket (setup, p-p list fill,
+// walk): at most kLightGrid workgroups, which take buckets a grid's width
+// apart.  A workgroup per leaf of the tree spent most of a launch starting
+// workgroups without a bucket when few elements are active (2^21 elements, 1%
+// active, 18 thousand buckets of 405 thousand leaves).
+constexpr uint64_t kLightGrid = 32768;
+static unsigned light_grid(uint64_t buckets) {
+  return (unsigned)std::max<uint64_t>(1, std::min(buckets, kLightGrid));
+}
+
 #define TREVR_LAUNCH_CHECK(what)                                               \
   do {                                                                         \
     if ((rc = hip_check(hipGetLastError(), what)) != TREVR_OK) return rc;      \
@@ -1472,6 +1546,7 @@ Scratch carve_scratch(void* base, int64_t leaves, size_t cut_entries) {
   s.tot = cv.take<unsigned long long>(TOT_N);
   s.ovf = cv.take<uint32_t>(4);
   s.ahash = cv.take<unsigned long long>(2);
+  s.head_words = (cv.off - (size_t)((char*)s.rng - (char*)base)) / 4;
   s.bins = cv.take<uint32_t>(kMaxBands * kOrderBins);
   s.ncnt = cv.take<uint32_t>(L + 1);
   s.tcnt = cv.take<uint32_t>(L + 1);
@@ -1588,12 +1663,12 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
   hipStream_t st = L.st;
   trevr_status rc;
   if ((rc = zero_words(st, S.rng, S.zero_words)) != TREVR_OK) return rc;
-  const dim3 gn(grid_of(L.max_nodes, 256), (unsigned)L.S);
+  const dim3 gn(grid_of(L.max_nodes, 256 * kActNodes), (unsigned)L.S);
   k_active_buckets<<<gn, 256, 0, st>>>(L.TT, active, S.blist_raw, S.bscene_raw, S.bnact_raw,
-                                       S.rng + 1);
+                                       S.rng + 1, S.ahash);
   TREVR_LAUNCH_CHECK("k_active_buckets");
   const Items I{0u, 0xFFFFFFFFu, S.rng, nullptr};
-  const unsigned gb = grid_of(L.leaves, 1);
+  const unsigned gb = light_grid((uint64_t)L.leaves);
   if (L.stack_large)
     k_setup<kStackLarge><<<gb, 64, 0, st>>>(L.TT, I, S.blist_raw, S.bscene_raw, S.brad_raw,
                                              S.bprev_raw, S.barg_raw, S.ncnt_raw, S.nlumc_raw,
@@ -1607,10 +1682,8 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
   k_cost_bins<<<gl, 256, 0, st>>>(L.TT, S.rng + 1, S.bscene_raw, S.bnact_raw, S.ncnt_raw,
                                   S.nlumc_raw, L.cfg.order, (uint32_t)L.S, S.bbin, S.bins);
   TREVR_LAUNCH_CHECK("k_cost_bins");
-  k_scan_u32<<<1, 1024, 0, st>>>(S.bins, (int64_t)kMaxBands * kOrderBins, nullptr);
-  TREVR_LAUNCH_CHECK("k_scan_u32");
-  k_class_ranges<<<1, 64, 0, st>>>(S.bins, S.rng);
-  TREVR_LAUNCH_CHECK("k_class_ranges");
+  k_scan_bins<<<1, 1024, 0, st>>>(S.bins, L.cfg.order, S.rng);
+  TREVR_LAUNCH_CHECK("k_scan_bins");
   k_reorder<<<gl, 256, 0, st>>>(L.TT, S.rng + 1, L.cfg.order, S.bbin, S.bins, S.blist_raw,
                                 S.bscene_raw, S.bnact_raw, S.ncnt_raw, S.nlumc_raw, S.brad_raw,
                                 S.bprev_raw, S.barg_raw, S.bsrc, S.blist, S.bscene, S.bnact,
@@ -1618,11 +1691,8 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
                                 S.tot);
   TREVR_LAUNCH_CHECK("k_reorder");
   const int64_t Lp = std::max<int64_t>(L.leaves, 1) + 1;
-  k_scan_arrays<<<4, 1024, 0, st>>>(ScanArrays{{S.ncnt, S.tcnt, S.jcnt, S.pcnt}}, Lp);
+  k_scan_arrays<<<4, 1024, 0, st>>>(ScanArrays{{S.ncnt, S.tcnt, S.jcnt, S.pcnt}}, Lp, S.rng + 1);
   TREVR_LAUNCH_CHECK("k_scan_arrays");
-  const dim3 ge(std::min(grid_of(L.max_n, 256), kHashBlocks), (unsigned)L.S);
-  k_active_hash<<<ge, 256, 0, st>>>(L.TT, active, S.ahash);
-  TREVR_LAUNCH_CHECK("k_active_hash");
   return TREVR_OK;
 }
 
@@ -1641,32 +1711,26 @@ trevr_status bucket_setup(trevr_tree* T, const uint8_t* active, Scratch& S, uint
   hipStream_t st = T->stream;
   trevr_status rc;
   uint32_t* hbuf = T->host_u32;
+  const auto at = [&](const void* p) { return (size_t)((const uint32_t*)p - S.rng); };
   for (;;) {
     const Launch L = tree_launch(T);
     if ((rc = setup_kernels(L, active, S)) != TREVR_OK) return rc;
-    hipError_t e = hipMemcpyAsync(hbuf, S.tot, TOT_N * sizeof(unsigned long long),
+    // the words from rng to the fingerprint (neighbours in the scratch) in
+    // one copy: a copy of a few words costs about 3 us, whatever its size
+    hipError_t e = hipMemcpyAsync(hbuf, S.rng, S.head_words * sizeof(uint32_t),
                                   hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(hbuf + 2 * TOT_N, S.ahash, sizeof(unsigned long long),
-                         hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(hbuf + 2 * TOT_N + 2, S.rng + 1, sizeof(uint32_t),
-                         hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(hbuf + 2 * TOT_N + 3, S.ovf, sizeof(uint32_t), hipMemcpyDeviceToHost,
-                         st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if ((rc = hip_check(e, "bucket readback")) != TREVR_OK) return rc;
-    if (!(hbuf[2 * TOT_N + 3] & OVF_SETUP)) break;
+    if (!(hbuf[at(S.ovf)] & OVF_SETUP)) break;
     // a p-p range query ran out of the small traversal stack: use the
     // large one for this tree from now on
     if (T->stack_large)
       return set_error(TREVR_E_CAPACITY, "a p-p range query exceeds the traversal stack");
     T->stack_large = true;
   }
-  std::memcpy(tot, hbuf, TOT_N * sizeof(uint64_t));
-  std::memcpy(hash, hbuf + 2 * TOT_N, sizeof(uint64_t));
-  *nb = hbuf[2 * TOT_N + 2];
+  std::memcpy(tot, hbuf + at(S.tot), TOT_N * sizeof(uint64_t));
+  std::memcpy(hash, hbuf + at(S.ahash), sizeof(uint64_t));
+  *nb = hbuf[1];
   for (int k = 0; k < TOT_RECV; ++k)
     if (tot[k] > 0xFFFFFFFFull)
       return set_error(TREVR_E_CAPACITY, "per-call p-p sizes exceed 32-bit offsets");
@@ -1692,7 +1756,7 @@ trevr_status active_hash(trevr_tree* T, const uint8_t* active, unsigned long lon
 
 trevr_status near_fill(const Launch& L, const Scratch& S) {
   trevr_status rc = TREVR_OK;
-  const unsigned g = grid_of(L.leaves, 1);
+  const unsigned g = light_grid((uint64_t)L.leaves);
   if (L.stack_large)
     k_near_fill<kStackLarge><<<g, 64, 0, L.st>>>(L.TT, S.rng, S.blist, S.bscene, S.brad, S.ncnt,
                                                   S.nlumc, S.bsrc, S.stage, S.stage_cap, S.nidx);
@@ -1704,10 +1768,10 @@ trevr_status near_fill(const Launch& L, const Scratch& S) {
 }
 
 trevr_status walk_launch(const Launch& L, const Scratch& S, const Items& I, uint64_t count,
-                         uint32_t cap) {
-  trevr_status rc;
-  if ((rc = zero_words(L.st, S.ovf, 2)) != TREVR_OK) return rc;
-  const unsigned gb = grid_of((int64_t)count, 1);
+                         uint32_t cap, bool clean) {
+  trevr_status rc = TREVR_OK;
+  if (!clean && (rc = zero_words(L.st, S.ovf, 2)) != TREVR_OK) return rc;
+  const unsigned gb = light_grid(count);
   if (L.stack_large)
     k_walk<kStackLarge><<<gb, 64, 0, L.st>>>(L.TT, I, S.blist, S.bscene, S.brad, S.cut, cap,
                                               S.bstat, S.ovf);
@@ -1720,14 +1784,15 @@ trevr_status walk_launch(const Launch& L, const Scratch& S, const Items& I, uint
 
 trevr_status walk_batch(trevr_tree* T, const Scratch& S, uint32_t b0, uint32_t cnt,
                         const std::function<trevr_status(uint32_t, uint32_t, uint32_t)>& run,
-                        bool* whole) {
+                        bool* whole, bool clean) {
   trevr_status rc;
   uint32_t* hbuf = T->host_u32;
   for (;;) {
     hipEvent_t ev = prof_begin(T);
     if ((rc = walk_launch(tree_launch(T), S, Items{b0, b0 + cnt, nullptr, nullptr}, cnt,
-                          T->cut_default)) != TREVR_OK)
+                          T->cut_default, clean)) != TREVR_OK)
       return rc;
+    clean = false;
     prof_end(T, TREVR_PROF_WALK, ev);
     hipError_t e = hipMemcpyAsync(hbuf, S.ovf, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost,
                                   T->stream);
@@ -1883,7 +1948,7 @@ trevr_status compute_J_impl(trevr_tree* T, const uint8_t* active, const float* b
         return r;
       prof_end(T, TREVR_PROF_REDUCE, e1);
       return r;
-    }, &whole);
+    }, &whole, b0 == 0);
     if (rc != TREVR_OK) return rc;
   }
   T->counters_valid = true;

@@ -68,11 +68,11 @@ __device__ inline uint32_t next_item(const Items& I, uint32_t* s_item) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
 }
 
-// The item of this workgroup in a plain grid launch of one workgroup per
-// item (blockIdx.x counts from the start of the range), kNoItem past its
-// end.  The light per-bucket kernels (setup, walk) launch this way: the
-// hardware hands out workgroups in order, and a work-queue claim would cost
-// them more than it balances.
+// The first item of this workgroup in a plain grid launch (blockIdx.x counts
+// from the start of the range), kNoItem past its end, and the one after b: a
+// grid's width on.  The light per-bucket kernels (setup, walk) launch this
+// way: the hardware hands out workgroups in order, and a work-queue claim
+// would cost them more than it balances.
 __device__ inline uint32_t grid_item(const Items& I) {
   uint32_t b = I.lo, e = I.hi;
   if (I.rng) {
@@ -81,6 +81,10 @@ __device__ inline uint32_t grid_item(const Items& I) {
   }
   const uint32_t it = b + blockIdx.x;
   return (b < e && it < e) ? it : kNoItem;
+}
+__device__ inline uint32_t grid_next(const Items& I, uint32_t b) {
+  const uint32_t e = I.rng ? min(I.hi, I.rng[1]) : I.hi;
+  return e - b > gridDim.x ? b + gridDim.x : kNoItem;
 }
 
 // Queue counter pairs of a scratch, one per item kernel.

@@ -28,6 +28,7 @@ struct Scratch {
   uint32_t* bins;               // cost bins per band count
   uint32_t *ncnt, *tcnt, *jcnt, *pcnt;   // sizes, scanned in place into offsets
   size_t zero_words;            // words from rng to the end of pcnt
+  size_t head_words;            // words from rng to the end of ahash (read back together)
   // processing order
   uint32_t *blist, *bscene, *bnact, *nlumc, *bstat;
   double *brad, *bprev;         // p-p radius; before its last growth (-1: none)
@@ -99,9 +100,10 @@ trevr_status launch_active_hash(const Launch& L, const uint8_t* active,
                                 unsigned long long* out);
 // Fill the p-p lists (S.nidx must be set).
 trevr_status near_fill(const Launch& L, const Scratch& S);
-// Tree walks of the items into the cut lists (cap entries each).
+// Tree walks of the items into the cut lists (cap entries each); clean: the
+// overflow words are zero already.
 trevr_status walk_launch(const Launch& L, const Scratch& S, const Items& I, uint64_t count,
-                         uint32_t cap);
+                         uint32_t cap, bool clean = false);
 // p-p columns per (receiver, ray, band) and, for the sources, pair optical
 // depths and (with J) the p-p part of J, of the items of band count B.
 trevr_status launch_pp_rays(const Launch& L, int B, const Scratch& S, const Items& I,
@@ -129,7 +131,7 @@ void take_kept(const trevr_tree* T, Scratch& S, Carve& cv, uint32_t nb);
 // longest (*whole = false).
 trevr_status walk_batch(trevr_tree* T, const Scratch& S, uint32_t b0, uint32_t cnt,
                         const std::function<trevr_status(uint32_t, uint32_t, uint32_t)>& run,
-                        bool* whole);
+                        bool* whole, bool clean = false);
 // Sizes of the gradient accumulators (sums over the scenes of a forest).
 struct GradDims {
   int64_t jn;       // sum of B n

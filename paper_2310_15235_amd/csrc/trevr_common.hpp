@@ -244,45 +244,85 @@ __device__ inline int mbcnt(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Exclusive scan of `total` uint32 in place by one workgroup of 1024
-// threads, in chunks of 1024 x kScanPer words (each thread's kScanPer
-// consecutive words loaded together, wavefront scans, then the 16 wavefront
-// totals); the grand total goes to *sum_out when given.
-constexpr int kScanPer = 16;
-__device__ inline void block_scan_u32(uint32_t* a, int64_t total, uint32_t* sum_out) {
+// Exclusive prefix of v over a workgroup of 1024 threads; *total (when given)
+// gets the sum.  Two barriers.
+__device__ inline uint32_t block_excl_u32(uint32_t v, uint32_t* total) {
   __shared__ uint32_t wtot[16];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
+    if (lane >= o) incl += u;
+  }
+  if (lane == 63) wtot[wv] = incl;
+  __syncthreads();
+  uint32_t wbase = 0, btot = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const uint32_t x = wtot[w];
+    if (w < wv) wbase += x;
+    btot += x;
+  }
+  __syncthreads();
+  if (total) *total = btot;
+  return wbase + (incl - v);
+}
+
+// Exclusive scan of `total` uint32 in place by one workgroup of 1024
+// threads, in chunks of 1024 x kScanPer words (a is 16-byte aligned); the
+// grand total goes to *sum_out when given.  Each thread moves its kScanPer
+// consecutive words in 16-byte pieces and the next chunk is loaded before
+// this one is scanned: one workgroup has nothing else to hide its loads
+// behind.
+constexpr int kScanPer = 16;
+__device__ inline void block_scan_u32(uint32_t* a, int64_t total, uint32_t* sum_out) {
+  const int t = threadIdx.x;
   uint32_t carry = 0;
+  uint4 nx[kScanPer / 4];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int k = 0; k < kScanPer / 4; ++k) {
+      const int64_t i = i0 + 4 * k;
+      if (i + 4 <= total) {
+        nx[k] = *reinterpret_cast<const uint4*>(a + i);
+      } else {
+        nx[k].x = i < total ? a[i] : 0u;
+        nx[k].y = i + 1 < total ? a[i + 1] : 0u;
+        nx[k].z = i + 2 < total ? a[i + 2] : 0u;
+        nx[k].w = 0u;
+      }
+    }
+  };
+  load((int64_t)t * kScanPer);
   for (int64_t base = 0; base < total; base += 1024 * kScanPer) {
     const int64_t i0 = base + (int64_t)t * kScanPer;
-    uint32_t v[kScanPer];
+    uint4 v[kScanPer / 4];
     uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-      v[k] = (i0 + k < total) ? a[i0 + k] : 0u;
-      s += v[k];
+    for (int k = 0; k < kScanPer / 4; ++k) {
+      v[k] = nx[k];
+      s += v[k].x + v[k].y + v[k].z + v[k].w;
     }
-    uint32_t incl = s;
+    load(i0 + 1024 * kScanPer);
+    uint32_t btot;
+    uint32_t run = carry + block_excl_u32(s, &btot);
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
-      if (lane >= o) incl += u;
-    }
-    if (lane == 63) wtot[wv] = incl;
-    __syncthreads();
-    uint32_t wbase = 0, btot = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      const uint32_t x = wtot[w];
-      if (w < wv) wbase += x;
-      btot += x;
-    }
-    __syncthreads();
-    uint32_t run = carry + wbase + (incl - s);
-#pragma unroll
-    for (int k = 0; k < kScanPer; ++k) {
-      if (i0 + k < total) a[i0 + k] = run;
-      run += v[k];
+    for (int k = 0; k < kScanPer / 4; ++k) {
+      const int64_t i = i0 + 4 * k;
+      uint4 o;
+      o.x = run;
+      o.y = o.x + v[k].x;
+      o.z = o.y + v[k].y;
+      o.w = o.z + v[k].z;
+      run = o.w + v[k].w;
+      if (i + 4 <= total) {
+        *reinterpret_cast<uint4*>(a + i) = o;
+      } else {
+        if (i < total) a[i] = o.x;
+        if (i + 1 < total) a[i + 1] = o.y;
+        if (i + 2 < total) a[i + 2] = o.z;
+      }
     }
     carry += btot;
   }
@@ -294,12 +334,15 @@ static __global__ void __launch_bounds__(1024) k_scan_u32(uint32_t* a, int64_t t
   block_scan_u32(a, total, sum_out);
 }
 
-// Up to four arrays of `total` words scanned at once, one workgroup each.
+// Up to four arrays scanned at once, one workgroup each: the first *used + 1
+// of their `total` words (the ones behind them are zero and not read).
 struct ScanArrays {
   uint32_t* a[4];
 };
-static __global__ void __launch_bounds__(1024) k_scan_arrays(ScanArrays s, int64_t total) {
-  block_scan_u32(s.a[blockIdx.x], total, nullptr);
+static __global__ void __launch_bounds__(1024) k_scan_arrays(ScanArrays s, int64_t total,
+                                                             const uint32_t* used) {
+  const int64_t n = (int64_t)*used + 1;
+  block_scan_u32(s.a[blockIdx.x], n < total ? n : total, nullptr);
 }
 
 }  // namespace trevr

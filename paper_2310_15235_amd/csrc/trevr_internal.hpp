@@ -145,7 +145,7 @@ struct trevr_tree {
 };
 
 namespace trevr {
-constexpr int kHostWords = 64;
+constexpr int kHostWords = 512;
 // Copy the host DevTree of a tree (and its level table) to the device copy
 // the kernels read; synchronises.
 trevr_status upload_dev(trevr_tree* t);
