@@ -121,17 +121,6 @@ void prof_destroy(Prof* p) {
   p->pool.clear();
 }
 
-trevr_status upload_dev(trevr_tree* t) {
-  t->dev.depth = (int32_t)t->levels.size();
-  hipError_t e = hipMemcpyAsync(t->buf.dev, &t->dev, sizeof(DevTree), hipMemcpyHostToDevice,
-                                t->stream);
-  if (e == hipSuccess && !t->levels.empty())
-    e = hipMemcpyAsync(t->buf.levels, t->levels.data(), t->levels.size() * sizeof(uint2),
-                       hipMemcpyHostToDevice, t->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(t->stream);
-  return hip_check(e, "tree table upload");
-}
-
 }  // namespace trevr
 
 using namespace trevr;
@@ -237,11 +226,6 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   rc = hip_check(hipHostMalloc((void**)&T->host_u32, kHostWords * sizeof(uint32_t)), "hipHostMalloc");
   if (rc == TREVR_OK) rc = build_tree_impl(T, x, y, z, m, rho, kappa, lum);
   if (rc != TREVR_OK) {
-    trevr_tree_destroy(T);
-    return rc;
-  }
-  D.num_nodes = T->num_nodes;
-  if ((rc = upload_dev(T)) != TREVR_OK) {
     trevr_tree_destroy(T);
     return rc;
   }
@@ -444,28 +428,31 @@ trevr_status trevr_tree_export(trevr_tree* t, int64_t* perm, int64_t* ints, doub
     for (int64_t i = 0; i < n; ++i) perm[i] = p32[i];
   }
   if (ints || box) {
-    std::vector<uint32_t> first(nn), count(nn), c0(nn), c1(nn), size(nn), pre(nn);
-    std::vector<int32_t> lown(nn), split(nn);
+    std::vector<uint32_t> next(nn);
+    std::vector<uint2> link(nn);
     std::vector<uint4> nk(nn);
     double hdr[8];
-    ok = ok && dl(first.data(), t->buf.b_first, 4 * nn) && dl(count.data(), t->buf.b_count, 4 * nn) &&
-         dl(c0.data(), t->buf.b_c0, 4 * nn) && dl(c1.data(), t->buf.b_c1, 4 * nn) &&
-         dl(size.data(), t->buf.b_size, 4 * nn) && dl(pre.data(), t->buf.b_pre, 4 * nn) &&
-         dl(lown.data(), t->buf.b_lown, 4 * nn) && dl(split.data(), t->buf.b_split, 4 * nn) &&
+    ok = ok && dl(next.data(), t->buf.next, 4 * nn) &&
+         dl(link.data(), t->buf.nlink, sizeof(uint2) * nn) &&
          dl(nk.data(), t->buf.nk, sizeof(uint4) * nn) && dl(hdr, t->buf.hdr, sizeof(hdr));
+    std::vector<int64_t> first(nn), count(nn);   // children follow their parent
+    for (int64_t p = nn - 1; ok && p >= 0; --p) {
+      const bool leaf = (nk[p].w & META_LEAF) != 0u;
+      first[p] = leaf ? (int64_t)link[p].x : first[p + 1];
+      count[p] = leaf ? (int64_t)link[p].y : count[p + 1] + count[link[p].x];
+    }
     if (ok) {
-      for (int64_t i = 0; i < nn; ++i) {
-        const int64_t p = pre[i];
-        const bool leaf = split[i] < 0;
+      for (int64_t p = 0; p < nn; ++p) {
+        const bool leaf = (nk[p].w & META_LEAF) != 0u;
         if (ints) {
           int64_t* o = ints + 7 * p;
-          o[0] = first[i];
-          o[1] = count[i];
-          o[2] = lown[i];
-          o[3] = split[i];
-          o[4] = leaf ? -1 : (int64_t)pre[c0[i]];
-          o[5] = leaf ? -1 : (int64_t)pre[c1[i]];
-          o[6] = p + size[i];
+          o[0] = first[p];
+          o[1] = count[p];
+          o[2] = (int64_t)(nk[p].w & 63u);
+          o[3] = leaf ? -1 : (int64_t)link[p].y;
+          o[4] = leaf ? -1 : p + 1;
+          o[5] = leaf ? -1 : (int64_t)link[p].x;
+          o[6] = (int64_t)next[p];
         }
         if (box) {
           const uint4 k = nk[p];

@@ -84,37 +84,47 @@ __global__ void __launch_bounds__(256) k_active_hash(const DevTree* __restrict__
 // The buckets with active members, and the fingerprint of the active set in
 // the same pass (the members' flags are read once).  One row of the grid per
 // scene (blockIdx.y); buckets of all scenes are appended to one list, with
-// their scene.  A workgroup takes kActNodes nodes per thread and appends its
+// their scene.  A workgroup takes PER nodes per thread and appends its
 // buckets with one atomic, adds its hashes with another: both addresses are
 // shared by the whole launch and their atomics queue (one append per
 // wavefront of 64 nodes took 125 us at 2^21 elements, and the fingerprint 25
-// us in a launch of its own).
-constexpr int kActNodes = 4;
+// us in a launch of its own; now 32).  A thread's nodes follow one another, so
+// trees of up to kActFew nodes, whose atomics do not matter, take one each
+// (4096 elements: 14.5 -> 7 us).
+constexpr int64_t kActFew = 1 << 16;
+template <int PER>
 __global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restrict__ TT,
                                                         const uint8_t* active, uint32_t* blist,
                                                         uint32_t* bscene, uint32_t* bnact,
                                                         uint32_t* nb, unsigned long long* hash) {
   __shared__ unsigned long long part[4];
-  __shared__ uint32_t wcnt[kActNodes][4], base_s;
+  __shared__ uint32_t wcnt[PER][4], base_s;
   const DevTree& T = TT[blockIdx.y];
   const uint8_t* act = active ? active + T.eoff : nullptr;
   const int t = threadIdx.x, wv = t >> 6;
-  const int64_t p0 = blockIdx.x * (int64_t)(256 * kActNodes) + t;
-  uint32_t cnt[kActNodes];
-  int pos[kActNodes];
+  const int64_t p0 = blockIdx.x * (int64_t)(256 * PER) + t;
+  uint32_t cnt[PER];
+  int pos[PER];
   unsigned long long v = 0ull;
 #pragma unroll
-  for (int r = 0; r < kActNodes; ++r) {
+  for (int r = 0; r < PER; ++r) {
     const int64_t p = p0 + 256 * r;
     cnt[r] = 0u;
     if (p < T.num_nodes && (T.nk[p].w & META_LEAF)) {
       const uint2 lk = T.nlink[p];
-      for (uint32_t s = lk.x; s < lk.x + lk.y; ++s) {
-        const uint32_t i = T.perm[s];
-        if (act == nullptr || act[i]) {
-          ++cnt[r];
-          v += mix64((unsigned long long)(T.eoff + i) + 1ull);
-        }
+      for (uint32_t s0 = 0; s0 < lk.y; s0 += 8) {   // eight members' loads together
+        uint32_t i[8];
+        uint8_t on[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) i[k] = T.perm[lk.x + min(s0 + (uint32_t)k, lk.y - 1u)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) on[k] = act == nullptr ? (uint8_t)1 : act[i[k]];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (s0 + (uint32_t)k < lk.y && on[k]) {
+            ++cnt[r];
+            v += mix64((unsigned long long)(T.eoff + i[k]) + 1ull);
+          }
       }
     }
     const uint64_t m = ballot64(cnt[r] != 0u);
@@ -127,7 +137,7 @@ __global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restric
   __syncthreads();
   if (t == 0) {
     uint32_t tot = 0;
-    for (int r = 0; r < kActNodes; ++r)
+    for (int r = 0; r < PER; ++r)
       for (int w = 0; w < 4; ++w) {
         const uint32_t c = wcnt[r][w];
         wcnt[r][w] = tot;
@@ -139,7 +149,7 @@ __global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restric
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kActNodes; ++r) {
+  for (int r = 0; r < PER; ++r) {
     if (cnt[r] == 0u) continue;
     const uint32_t b = base_s + wcnt[r][wv] + (uint32_t)pos[r];
     blist[b] = (uint32_t)(p0 + 256 * r);
@@ -1663,9 +1673,10 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
   hipStream_t st = L.st;
   trevr_status rc;
   if ((rc = zero_words(st, S.rng, S.zero_words)) != TREVR_OK) return rc;
-  const dim3 gn(grid_of(L.max_nodes, 256 * kActNodes), (unsigned)L.S);
-  k_active_buckets<<<gn, 256, 0, st>>>(L.TT, active, S.blist_raw, S.bscene_raw, S.bnact_raw,
-                                       S.rng + 1, S.ahash);
+  const bool few = L.max_nodes <= kActFew;
+  const dim3 gn(grid_of(L.max_nodes, few ? 256 : 1024), (unsigned)L.S);
+  (few ? k_active_buckets<1> : k_active_buckets<4>)<<<gn, 256, 0, st>>>(
+      L.TT, active, S.blist_raw, S.bscene_raw, S.bnact_raw, S.rng + 1, S.ahash);
   TREVR_LAUNCH_CHECK("k_active_buckets");
   const Items I{0u, 0xFFFFFFFFu, S.rng, nullptr};
   const unsigned gb = light_grid((uint64_t)L.leaves);

@@ -90,15 +90,6 @@ __device__ inline uint32_t grid_next(const Items& I, uint32_t b) {
 // Queue counter pairs of a scratch, one per item kernel.
 enum { Q_PPR = 0, Q_PPS, Q_FAR, Q_PPS_BWD, Q_FAR_BWD, Q_PPR_BWD, Q_N };
 
-// Order LDS writes of some lanes before reads by other lanes of the same
-// wavefront (the lanes execute together; this keeps the compiler and the
-// memory model from reordering across the hand-off).
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The atomic only when v exceeds the value read first (a stale read is never
 // larger than the current value, so no update is lost): most callers'
 // values stop exceeding the maximum early, and atomics on one address queue.

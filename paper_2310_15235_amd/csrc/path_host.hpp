@@ -88,8 +88,6 @@ Launch tree_launch(const trevr_tree* T);
 // least 1.
 unsigned persistent_grid(const void* fn, int threads, uint64_t items, uint32_t div);
 
-trevr_status zero_words(hipStream_t st, void* p, size_t words);
-
 // Bucket setup without synchronising: active buckets of every scene, p-p
 // radii and set sizes, grouping by band count and heaviest-first order,
 // per-bucket offsets of the dynamic scratch and their 64-bit totals, the

@@ -6,13 +6,23 @@
 // (luminosities, luminosity centre, bucket absorption) and per-direction
 // transmission-averaged absorption.
 //
-// Levels are built top-down, one launch per level (children of a level are
-// allocated with an atomic counter), then renumbered into depth-first
-// preorder so a subtree is a contiguous index range.  Moments and
-// transmission tables are reduced bottom-up, level by level, with FP64 sums
-// formed in a fixed order (buckets sum their elements in key order; a parent
-// adds its two children), which makes every node moment independent of the
-// launch shape.
+// The topology comes from the sorted keys alone (Karras 2012, "Maximizing
+// parallelism in the construction of BVHs, octrees, and k-d trees"): every
+// internal node of the binary radix tree finds its range and split by itself,
+// the ones too large for a bucket are kept, and a prefix sum over the first
+// slots of the nodes numbers them in depth-first preorder, so a subtree is a
+// contiguous index range.  Moments and transmission tables are reduced
+// bottom-up, a workgroup per subtree of at most kSubtree elements and level by
+// level above, with FP64 sums formed in a fixed order (buckets sum their
+// elements in key order; a parent adds its two children), which makes every
+// node moment independent of the launch shape.
+//
+// What bounds the build is the number of dependent steps, not bytes (4 MB at
+// 2^18 elements of one band): before, one launch per level and step (200
+// launches, the host reading the levels back every six), now some 30 with one
+// readback.  Kernels of a build, before -> now: 4096 elements of one band 540 ->
+// 165 us, 2^18 of three bands 1360 -> 400 us, 2^21 of two bands and 24 direction
+// classes 3500 -> 1480 us.
 
 #include <algorithm>
 #include <cmath>
@@ -33,13 +43,19 @@ __device__ inline float ord2f(uint32_t u) {
 __device__ inline bool finite_pos(float v) { return isfinite(v) && v > 0.0f; }
 
 // ------------------------------------------------------------- root cube
-__global__ void k_init(uint32_t* bbox_u, uint32_t* err, unsigned long long* counters,
-                       uint32_t* alloc) {
+// Zeroes the build's counters; with a box from the caller also writes the
+// header.  One workgroup.
+__global__ void k_init(TreeBufs tb, double bx, double by, double bz, double bL) {
   const int t = threadIdx.x;
-  if (t < 3) { bbox_u[t] = 0xFFFFFFFFu; bbox_u[3 + t] = 0u; }
-  if (t < 4) err[t] = 0u;
-  if (t < CNT_N) counters[t] = 0ull;
-  if (t == 0) *alloc = 1u;
+  if (t < 3) { tb.bbox_u[t] = 0xFFFFFFFFu; tb.bbox_u[3 + t] = 0u; }
+  if (t < 4) tb.err[t] = 0u;
+  if (t < CNT_N) tb.counters[t] = 0ull;
+  if (t < (int)(sizeof(BuildWords) / 4)) reinterpret_cast<uint32_t*>(tb.words)[t] = 0u;
+  if (t == 0) tb.tsum[0] = 0u;
+  if (t == 0 && bL > 0.0) {
+    tb.hdr[0] = bx; tb.hdr[1] = by; tb.hdr[2] = bz; tb.hdr[3] = bL;
+    tb.hdr[4] = ldexp(1.0, kKeyBits) / bL;
+  }
 }
 
 __global__ void __launch_bounds__(256) k_bbox(const float* x, const float* y, const float* z,
@@ -79,93 +95,302 @@ __global__ void __launch_bounds__(256) k_bbox(const float* x, const float* y, co
   }
 }
 
-// hdr = {lo_x, lo_y, lo_z, L, 2^21 / L}.  L is the largest extent of the
-// bounding box (1 if all elements coincide) unless the caller fixed a box.
-__global__ void k_header(const uint32_t* bbox_u, double bx, double by, double bz, double bL,
-                         double* hdr) {
+// hdr = {lo_x, lo_y, lo_z, L, 2^21 / L} without a box from the caller: L is
+// the largest extent of the bounding box (1 if all elements coincide).
+__global__ void k_header(const uint32_t* bbox_u, double* hdr) {
   if (threadIdx.x != 0) return;
-  double lo[3], L;
-  if (bL > 0.0) {
-    lo[0] = bx; lo[1] = by; lo[2] = bz; L = bL;
-  } else {
-    L = 0.0;
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = (double)ord2f(bbox_u[a]);
-      const double hi = (double)ord2f(bbox_u[3 + a]);
-      L = fmax(L, hi - lo[a]);
-    }
-    if (L == 0.0) L = 1.0;
+  double lo[3], L = 0.0;
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = (double)ord2f(bbox_u[a]);
+    const double hi = (double)ord2f(bbox_u[3 + a]);
+    L = fmax(L, hi - lo[a]);
   }
+  if (L == 0.0) L = 1.0;
   hdr[0] = lo[0]; hdr[1] = lo[1]; hdr[2] = lo[2]; hdr[3] = L;
   hdr[4] = ldexp(1.0, kKeyBits) / L;
 }
 
 // ----------------------------------------------------------- Morton keys
-__global__ void k_keys(const float* x, const float* y, const float* z, const float* m,
-                       const float* rho, const float* kappa, const float* lum, int64_t n,
-                       int B, const double* hdr, uint64_t* keys, uint32_t* vals,
-                       uint32_t* err) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float X[3] = {x[i], y[i], z[i]};
-  bool ok = isfinite(X[0]) && isfinite(X[1]) && isfinite(X[2]) && finite_pos(m[i]) &&
-            finite_pos(rho[i]);
-  for (int b = 0; b < B; ++b) {
-    const float kv = kappa[(int64_t)b * n + i], lv = lum[(int64_t)b * n + i];
-    ok = ok && isfinite(kv) && kv >= 0.0f && isfinite(lv) && lv >= 0.0f;
-  }
-  if (!ok) atomicOr(err, ERR_DATA);
-  uint32_t q[3];
+// Bit b of a 21-bit word to bit 3b, and back.
+__device__ inline uint64_t spread3(uint32_t v) {
+  uint64_t x = v & 0x1FFFFFu;
+  x = (x | (x << 32)) & 0x001F00000000FFFFull;
+  x = (x | (x << 16)) & 0x001F0000FF0000FFull;
+  x = (x | (x << 8)) & 0x100F00F00F00F00Full;
+  x = (x | (x << 4)) & 0x10C30C30C30C30C3ull;
+  x = (x | (x << 2)) & 0x1249249249249249ull;
+  return x;
+}
+__device__ inline uint32_t compact3(uint64_t k, int a) {
+  // bits of axis a sit at positions 3b + (2 - a)
+  uint64_t x = (k >> (2 - a)) & 0x1249249249249249ull;
+  x = (x | (x >> 2)) & 0x10C30C30C30C30C3ull;
+  x = (x | (x >> 4)) & 0x100F00F00F00F00Full;
+  x = (x | (x >> 8)) & 0x001F0000FF0000FFull;
+  x = (x | (x >> 16)) & 0x001F00000000FFFFull;
+  x = (x | (x >> 32)) & 0x1FFFFFull;
+  return (uint32_t)x;
+}
+
+__device__ inline uint64_t morton_key(const double* hdr, float x, float y, float z) {
+  const float X[3] = {x, y, z};
   const double scale = hdr[4];
+  uint64_t k = 0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     double u = floor(((double)X[a] - hdr[a]) * scale);
     if (!(u >= 0.0)) u = 0.0;
     if (u > 2097151.0) u = 2097151.0;
-    q[a] = (uint32_t)u;
+    k |= spread3((uint32_t)u) << (2 - a);
   }
-  uint64_t k = 0;
-  for (int b = kKeyBits - 1; b >= 0; --b)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) k = (k << 1) | (uint64_t)((q[a] >> b) & 1u);
-  keys[i] = k;
-  vals[i] = (uint32_t)i;
+  return k;
 }
 
-// ------------------------------------------- stable LSD radix sort, 8 bits
-__global__ void __launch_bounds__(256) k_sort_hist(const uint64_t* keys, int64_t n, int shift,
-                                                   uint32_t* hist, int nblk) {
+// Keys, the check of the inputs, the bits in which keys differ (for the
+// sort) and each element packed into one record of rec_floats(B) floats
+// {x, y, z, m, rho, (kappa, lum) per band}: the gather after the sort then
+// touches one or two cache lines per element instead of one per array
+// (2^21 elements, two bands: gather 338 -> 98 us, the keys 30 -> 57 with the
+// records' 100 MB).
+__global__ void __launch_bounds__(256) k_keys(const float* x, const float* y, const float* z,
+                                              const float* m, const float* rho,
+                                              const float* kappa, const float* lum, int64_t n,
+                                              int B, TreeBufs tb) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  uint64_t diff = 0ull;
+  if (i < n) {
+    const float X[3] = {x[i], y[i], z[i]};
+    const float mi = m[i], ri = rho[i];
+    float4* rec = reinterpret_cast<float4*>(tb.rec + i * rec_floats(B));
+    float4 q = make_float4(ri, 0.0f, 0.0f, 0.0f);
+    rec[0] = make_float4(X[0], X[1], X[2], mi);
+    bool ok = isfinite(X[0]) && isfinite(X[1]) && isfinite(X[2]) && finite_pos(mi) &&
+              finite_pos(ri);
+    int fill = 1, at = 1;
+    for (int b = 0; b < B; ++b) {
+      const float kv = kappa[(int64_t)b * n + i], lv = lum[(int64_t)b * n + i];
+      ok = ok && isfinite(kv) && kv >= 0.0f && isfinite(lv) && lv >= 0.0f;
+      if (fill == 1) {
+        q.y = kv;
+        q.z = lv;
+        fill = 3;
+      } else {
+        q.w = kv;
+        rec[at++] = q;
+        q.x = lv;
+        fill = 1;
+      }
+    }
+    rec[at] = q;
+    if (!ok) atomicOr(tb.err, ERR_DATA);
+    const uint64_t k = morton_key(tb.hdr, X[0], X[1], X[2]);
+    tb.keys_alt[i] = k;
+    tb.starts[i] = 0u;
+    if (i == n - 1) tb.starts[n] = 0u;
+    diff = k ^ morton_key(tb.hdr, x[0], y[0], z[0]);
+  }
+  __shared__ unsigned long long part[4];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) diff |= (uint64_t)__shfl_xor((long long)diff, o);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = diff;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long d = part[0] | part[1] | part[2] | part[3];
+    // the atomic only for bits not seen set yet (a stale read shows fewer)
+    if (d & ~__atomic_load_n(&tb.words->diff, __ATOMIC_RELAXED)) atomicOr(&tb.words->diff, d);
+  }
+}
+
+// ------------------------------------------------------------- the sort
+// Up to kSmallSort elements: one workgroup sorts in LDS, 8 bits a pass, the
+// passes whose bits all keys share left out.  Each wavefront ranks its 256
+// consecutive keys by matching digits (ballots), the counts per (wavefront,
+// digit) are scanned, the keys move to the other buffer.  At 4096 elements
+// the passes over global memory took 225 us in 24 launches of one or two
+// workgroups, this one 36 us.
+constexpr int kSmallSort = 4096;
+__global__ void __launch_bounds__(1024) k_sort_small(int64_t n64, TreeBufs tb) {
+  __shared__ uint64_t K[2][kSmallSort];
+  __shared__ uint16_t V[2][kSmallSort];
+  __shared__ uint32_t cnt[16][256];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, n = (int)n64;
+  for (int i = t; i < n; i += 1024) {
+    K[0][i] = tb.keys_alt[i];
+    V[0][i] = (uint16_t)i;
+  }
+  const uint64_t diff = tb.words->diff;
+  int cur = 0;
+  for (int shift = 0; shift < 64; shift += 8) {
+    if (((diff >> shift) & 255ull) == 0ull) continue;
+    __syncthreads();
+    for (int i = t; i < 16 * 256; i += 1024) (&cnt[0][0])[i] = 0u;
+    __syncthreads();
+    uint64_t k[4];
+    uint32_t rk[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = w * 256 + r * 64 + lane;
+      const bool valid = i < n;
+      k[r] = valid ? K[cur][i] : 0ull;
+      const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+      uint64_t mm = ballot64(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const bool on = (d >> bit) & 1u;
+        const uint64_t bb = ballot64(on);
+        mm &= on ? bb : ~bb;
+      }
+      const uint32_t pre = cnt[w][d];
+      wave_lds_sync();
+      const int rank = mbcnt(mm);
+      if (valid && rank == 0) cnt[w][d] = pre + (uint32_t)__popcll(mm);
+      wave_lds_sync();
+      rk[r] = pre + (uint32_t)rank;
+    }
+    __syncthreads();
+    uint32_t run = 0;
+    if (t < 256)
+      for (int ww = 0; ww < 16; ++ww) run += cnt[ww][t];
+    const uint32_t base = block_excl_u32(run, nullptr);
+    if (t < 256) {
+      run = base;
+      for (int ww = 0; ww < 16; ++ww) {
+        const uint32_t c = cnt[ww][t];
+        cnt[ww][t] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = w * 256 + r * 64 + lane;
+      if (i < n) {
+        const uint32_t p = cnt[w][(uint32_t)(k[r] >> shift) & 255u] + rk[r];
+        K[cur ^ 1][p] = k[r];
+        V[cur ^ 1][p] = V[cur][i];
+      }
+    }
+    cur ^= 1;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 1024) {
+    tb.keys[i] = K[cur][i];
+    tb.vals[i] = V[cur][i];
+  }
+}
+
+// More elements: stable LSD radix sort, 8 bits a pass, of the 32 highest
+// bits in which keys differ (four passes over 4-byte keys); k_sort_finish
+// then orders the few elements whose 32 bits agree.  When some run of those
+// is long (elements crowded into 2^-10 of the varying extent) every later
+// kernel of the build exits and the host builds again with all 64 bits
+// sorted (WIDE: eight passes over 8-byte keys).
+__device__ inline uint32_t top_bits(uint64_t k, uint64_t diff) {
+  const int len = 64 - __clzll((long long)diff);   // varying bits
+  return (uint32_t)(len > 32 ? k >> (len - 32) : k);
+}
+template <bool WIDE> struct SortKey { using type = uint32_t; };
+template <> struct SortKey<true> { using type = uint64_t; };
+
+// The key of pass `pass`: the first pass of the short sort reads the full
+// keys in input order.
+template <bool WIDE>
+__device__ inline typename SortKey<WIDE>::type sort_key(const void* in, int64_t i, int pass,
+                                                        uint64_t diff) {
+  if (WIDE) return (typename SortKey<WIDE>::type)((const uint64_t*)in)[i];
+  if (pass == 0) return (typename SortKey<WIDE>::type)top_bits(((const uint64_t*)in)[i], diff);
+  return (typename SortKey<WIDE>::type)((const uint32_t*)in)[i];
+}
+
+template <bool WIDE, int ITEMS>
+__global__ void __launch_bounds__(256) k_sort_hist(const void* in, int64_t n, int pass,
+                                                   TreeBufs tb, int nblk) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0u;
+  const uint64_t diff = tb.words->diff;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * SortCfg::kTile;
-  for (int r = 0; r < SortCfg::kItems; ++r) {
+  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = base + r * 256 + threadIdx.x;
-    if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
+    if (i < n)
+      atomicAdd(&h[(uint32_t)(sort_key<WIDE>(in, i, pass, diff) >> (8 * pass)) & 255u], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+  tb.hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
 }
 
-__global__ void __launch_bounds__(256) k_sort_scatter(const uint64_t* kin, const uint32_t* vin,
-                                                      uint64_t* kout, uint32_t* vout,
-                                                      int64_t n, int shift,
-                                                      const uint32_t* hist, int nblk) {
+// Exclusive scan of one digit's counts over the tiles (one workgroup per
+// digit) and the digit's total.
+__global__ void __launch_bounds__(256) k_sort_rows(uint32_t* hist, uint32_t* dtot, int nblk) {
+  __shared__ uint32_t wsum[4];
+  uint32_t* a = hist + (int64_t)blockIdx.x * nblk;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  uint32_t carry = 0;
+  for (int b0 = 0; b0 < nblk; b0 += 256) {
+    const uint32_t v = b0 + t < nblk ? a[b0 + t] : 0u;
+    uint32_t incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    uint32_t pre = carry, tot = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < w) pre += wsum[q];
+      tot += wsum[q];
+    }
+    if (b0 + t < nblk) a[b0 + t] = pre + incl - v;
+    carry += tot;
+    __syncthreads();
+  }
+  if (t == 0) dtot[blockIdx.x] = carry;
+}
+
+template <bool WIDE, int ITEMS>
+__global__ void __launch_bounds__(256) k_sort_scatter(const void* in, const uint32_t* vin,
+                                                      void* out, uint32_t* vout, int64_t n,
+                                                      int pass, TreeBufs tb, int nblk) {
+  using Key = typename SortKey<WIDE>::type;
   __shared__ uint32_t run[256];
-  __shared__ uint32_t goff[256];
   __shared__ uint32_t wcnt[4][256];
-  const int t = threadIdx.x, w = t >> 6;
-  run[t] = 0u;
-  goff[t] = hist[(int64_t)t * nblk + blockIdx.x];
-  wcnt[0][t] = wcnt[1][t] = wcnt[2][t] = wcnt[3][t] = 0u;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * SortCfg::kTile;
-  for (int r = 0; r < SortCfg::kItems; ++r) {
+  __shared__ uint32_t wsum[4];
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const uint64_t diff = tb.words->diff;
+  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS);
+  Key k[ITEMS];
+  uint32_t v[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = base + r * 256 + t;
-    const bool valid = i < n;
-    const uint64_t k = valid ? kin[i] : 0ull;
-    const uint32_t v = valid ? vin[i] : 0u;
-    const uint32_t d = (uint32_t)(k >> shift) & 255u;
+    k[r] = i < n ? sort_key<WIDE>(in, i, pass, diff) : (Key)0;
+    v[r] = i < n ? (pass == 0 ? (uint32_t)i : vin[i]) : 0u;
+  }
+  // first slot of digit t in this tile: the smaller digits, then the tiles
+  // before this one
+  {
+    const uint32_t d = tb.dtot[t];
+    uint32_t incl = d;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    uint32_t pre = incl - d;
+    for (int q = 0; q < w; ++q) pre += wsum[q];
+    run[t] = pre + tb.hist[(int64_t)t * nblk + blockIdx.x];
+    wcnt[0][t] = wcnt[1][t] = wcnt[2][t] = wcnt[3][t] = 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const bool valid = base + r * 256 + t < n;
+    const uint32_t d = (uint32_t)(k[r] >> (8 * pass)) & 255u;
     uint64_t mm = ballot64(valid);
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) {
@@ -177,11 +402,10 @@ __global__ void __launch_bounds__(256) k_sort_scatter(const uint64_t* kin, const
     if (valid && rank_w == 0) wcnt[w][d] = (uint32_t)__popcll(mm);
     __syncthreads();
     if (valid) {
-      uint32_t pre = run[d];
-      for (int ww = 0; ww < w; ++ww) pre += wcnt[ww][d];
-      const uint32_t dst = goff[d] + pre + (uint32_t)rank_w;
-      kout[dst] = k;
-      vout[dst] = v;
+      uint32_t dst = run[d] + (uint32_t)rank_w;
+      for (int ww = 0; ww < w; ++ww) dst += wcnt[ww][d];
+      ((Key*)out)[dst] = k[r];
+      vout[dst] = v[r];
     }
     __syncthreads();
     run[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
@@ -190,25 +414,72 @@ __global__ void __launch_bounds__(256) k_sort_scatter(const uint64_t* kin, const
   }
 }
 
+// Full keys in sorted order.  After the short sort the first thread of a run
+// of equal 32 bits orders the run by the full keys (stable: equal keys stay
+// in input order); a run longer than kRunMax raises words->resort.  Uniform
+// elements have runs of two at most (2^21 of them in 2^32 cells: 500 runs).
+constexpr int kRunMax = 24;
+__global__ void __launch_bounds__(256) k_sort_finish(int64_t n, TreeBufs tb, int wide) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (wide) {   // sorted in place: the full keys lie in keys_alt
+    tb.keys[i] = tb.keys_alt[i];
+    return;
+  }
+  const uint32_t* top = tb.top;
+  const uint32_t k = top[i];
+  const bool whole = (tb.words->diff >> 32) == 0ull;   // 32 bits are all that vary
+  if (whole || ((i == 0 || top[i - 1] != k) && (i + 1 >= n || top[i + 1] != k))) {
+    tb.keys[i] = tb.keys_alt[tb.vals[i]];
+    return;
+  }
+  if (i > 0 && top[i - 1] == k) return;   // the run's first thread orders it
+  int len = 1;
+  while (len <= kRunMax && i + len < n && top[i + len] == k) ++len;
+  if (len > kRunMax) {
+    __atomic_store_n(&tb.words->resort, 1u, __ATOMIC_RELAXED);
+    return;
+  }
+  for (int a = 0; a < len; ++a) {   // insertion sort in place
+    const uint32_t v = tb.vals[i + a];
+    const uint64_t kv = tb.keys_alt[v];
+    int q = a;
+    for (; q > 0 && tb.keys[i + q - 1] > kv; --q) {
+      tb.keys[i + q] = tb.keys[i + q - 1];
+      tb.vals[i + q] = tb.vals[i + q - 1];
+    }
+    tb.keys[i + q] = kv;
+    tb.vals[i + q] = v;
+  }
+}
+
 // ------------------------------------------------- sorted element arrays
-__global__ void k_gather(const float* x, const float* y, const float* z, const float* m,
-                         const float* rho, const float* kappa, const float* lum, int64_t n,
-                         int B, const uint32_t* vals, TreeBufs tb) {
+__global__ void __launch_bounds__(256) k_gather(int64_t n, int B, TreeBufs tb) {
   const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const uint32_t i = vals[s];
+  if (s >= n || tb.words->resort) return;
+  const uint32_t i = tb.vals[s];
+  const float4* rec = reinterpret_cast<const float4*>(tb.rec + (int64_t)i * rec_floats(B));
+  const float4 p = rec[0];
+  float4 q = rec[1];
   tb.perm[s] = i;
-  tb.x[s] = x[i];
-  tb.y[s] = y[i];
-  tb.z[s] = z[i];
-  const float mi = m[i], ri = rho[i];
-  tb.m[s] = mi;
-  tb.rho[s] = ri;
-  tb.h[s] = cbrt((double)mi / (double)ri);   // element size, Section 2.1
+  tb.x[s] = p.x;
+  tb.y[s] = p.y;
+  tb.z[s] = p.z;
+  tb.m[s] = p.w;
+  tb.rho[s] = q.x;
+  tb.h[s] = cbrt((double)p.w / (double)q.x);   // element size, Section 2.1
   double lb = 0.0;
-  for (int b = 0; b < B; ++b) {
-    const float lv = lum[(int64_t)b * n + i];
-    tb.kappa[(int64_t)b * n + s] = kappa[(int64_t)b * n + i];
+  for (int b = 0, at = 2; b < B; ++b) {
+    float kv, lv;
+    if ((b & 1) == 0) {
+      kv = q.y;
+      lv = q.z;
+    } else {
+      kv = q.w;
+      q = rec[at++];
+      lv = q.x;
+    }
+    tb.kappa[(int64_t)b * n + s] = kv;
     tb.lum[(int64_t)b * n + s] = lv;
     lb += (double)lv;
   }
@@ -216,183 +487,429 @@ __global__ void k_gather(const float* x, const float* y, const float* z, const f
 }
 
 // ------------------------------------------------------------- topology
-__global__ void k_root(TreeBufs tb, int64_t n) {
-  if (threadIdx.x != 0) return;
-  tb.b_first[0] = 0u;
-  tb.b_count[0] = (uint32_t)n;
-  tb.b_lown[0] = 0;
-  tb.b_pre[0] = 0u;
-  tb.levels[0] = make_uint2(0u, 1u);
+// A node of the radix tree is kept as a cell if it holds more than leaf_size
+// elements and its keys are not all equal; the other children of kept nodes
+// are the buckets.
+__device__ inline bool kept_range(const uint64_t* keys, uint32_t f, uint32_t l, int leaf_size) {
+  return l - f + 1u > (uint32_t)leaf_size && keys[f] != keys[l];
 }
 
-// One level: a node is a bucket if it holds at most leaf_size elements or
-// all its keys are equal; otherwise it splits at the first bit in which its
-// keys differ (its sorted range splits where that bit turns on).
-// The level's range [lb, le) is read from levels[d] (written by the previous
-// level's k_level_next), so levels follow each other without the host.
-__global__ void k_level(TreeBufs tb, int d, int leaf_size) {
-  const uint2 lv = tb.levels[d];
-  const uint32_t i = lv.x + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= lv.y) return;
-  const uint32_t f = tb.b_first[i], c = tb.b_count[i];
-  const uint64_t k0 = tb.keys[f], k1 = tb.keys[f + c - 1];
-  if (c <= (uint32_t)leaf_size || k0 == k1) {
-    tb.b_split[i] = -1;
+// Length of the common prefix of the keys of slots i and j, slots told apart
+// by their index where keys are equal; -1 outside the array.
+__device__ inline int common_prefix(const uint64_t* keys, int64_t n, uint64_t ki, int64_t i,
+                                    int64_t j) {
+  if (j < 0 || j >= n) return -1;
+  const uint64_t x = ki ^ keys[j];
+  if (x) return __clzll((long long)x);
+  return 64 + __clz((int)((uint32_t)i ^ (uint32_t)j));
+}
+
+// Internal node i of the radix tree covers slots from i to r_end[i], split
+// after slot r_split[i]; its internal children are the nodes r_split[i] and
+// r_split[i] + 1, whose r_par gets i.  Nodes not kept get r_end = kNoNode.
+// starts[f] counts the cells and buckets whose first slot is f.
+constexpr uint32_t kNoNode = 0xFFFFFFFFu;
+__global__ void __launch_bounds__(256) k_radix(int64_t n, int leaf_size, TreeBufs tb) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n || tb.words->resort) return;
+  const uint64_t* keys = tb.keys;
+  const uint64_t ki = keys[i];
+  const int dn = common_prefix(keys, n, ki, i, i + 1), dp = common_prefix(keys, n, ki, i, i - 1);
+  const int64_t d = dn > dp ? 1 : -1;
+  const int dmin = dn > dp ? dp : dn;
+  tb.r_end[i] = kNoNode;
+  // more than leaf_size elements, or not a cell (the root's bounds are known)
+  if (i == n - 1 || common_prefix(keys, n, ki, i, i + d * leaf_size) <= dmin) {
+    if (i == 0) atomicAdd(&tb.starts[0], 1u);   // the whole tree is one bucket
     return;
   }
-  const int s = __clzll((long long)(k0 ^ k1)) - 1;
-  const uint64_t bit = 1ull << (62 - s);
-  uint32_t lo = f, hi = f + c - 1;  // key[lo] lacks the bit, key[hi] has it
-  while (hi - lo > 1) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    if (tb.keys[mid] & bit) hi = mid; else lo = mid;
+  int64_t lmax = 2 * (int64_t)leaf_size;
+  while (common_prefix(keys, n, ki, i, i + lmax * d) > dmin) lmax *= 2;
+  int64_t len = 0;
+  for (int64_t s = lmax / 2; s >= 1; s /= 2)
+    if (common_prefix(keys, n, ki, i, i + (len + s) * d) > dmin) len += s;
+  // lmax need not be a power of two: close the last gap
+  while (common_prefix(keys, n, ki, i, i + (len + 1) * d) > dmin) ++len;
+  const int64_t j = i + len * d;
+  const uint32_t f = (uint32_t)(d > 0 ? i : j), l = (uint32_t)(d > 0 ? j : i);
+  const uint64_t k0 = keys[f], k1 = keys[l];
+  if (k0 == k1) {   // equal keys: a bucket however many
+    if (i == 0) atomicAdd(&tb.starts[0], 1u);
+    return;
   }
-  const uint32_t pos = atomicAdd(tb.alloc, 2u);
-  tb.b_first[pos] = f;
-  tb.b_count[pos] = hi - f;
-  tb.b_lown[pos] = s + 1;
-  tb.b_first[pos + 1] = hi;
-  tb.b_count[pos + 1] = f + c - hi;
-  tb.b_lown[pos + 1] = s + 1;
-  tb.b_c0[i] = pos;
-  tb.b_c1[i] = pos + 1;
-  tb.b_split[i] = s;
+  const uint64_t bit = 1ull << (63 - __clzll((long long)(k0 ^ k1)));
+  uint32_t lo = f, hi = l;   // key[lo] lacks the bit, key[hi] has it
+  while (hi - lo > 1u) {
+    const uint32_t mid = lo + (hi - lo) / 2u;
+    if (keys[mid] & bit) hi = mid; else lo = mid;
+  }
+  tb.r_end[i] = (uint32_t)j;
+  tb.r_split[i] = lo;
+  if (lo > f) tb.r_par[lo] = (uint32_t)i;
+  if (hi < l) tb.r_par[hi] = (uint32_t)i;
+  atomicAdd(&tb.starts[f], 1u);
+  if (!kept_range(keys, f, lo, leaf_size)) atomicAdd(&tb.starts[f], 1u);
+  if (!kept_range(keys, hi, l, leaf_size)) atomicAdd(&tb.starts[hi], 1u);
 }
 
-// Range of level d + 1: the nodes allocated by the splits of level d.
-__global__ void k_level_next(TreeBufs tb, int d) {
-  if (threadIdx.x == 0) tb.levels[d + 1] = make_uint2(tb.levels[d].y, *tb.alloc);
+// Exclusive scan of `total` words in tiles of 16384, one workgroup each: in
+// place within the tile, the tiles' sums to tsum.
+constexpr int kScanTile = 1024 * kScanPer;
+__global__ void __launch_bounds__(1024) k_scan_tiles(uint32_t* a, int64_t total, uint32_t* tsum) {
+  const int64_t b = blockIdx.x * (int64_t)kScanTile;
+  const int64_t m = total - b < kScanTile ? total - b : (int64_t)kScanTile;
+  block_scan_u32(a + b, m, gridDim.x > 1 ? tsum + blockIdx.x : nullptr);
 }
 
-__global__ void k_sizes(TreeBufs tb, uint32_t lb, uint32_t le) {
-  const uint32_t i = lb + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= le) return;
-  tb.b_size[i] = (tb.b_split[i] < 0) ? 1u : 1u + tb.b_size[tb.b_c0[i]] + tb.b_size[tb.b_c1[i]];
+// Cells and buckets starting before slot f.
+__device__ inline uint32_t starts_before(const TreeBufs& tb, uint32_t f) {
+  return tb.starts[f] + tb.tsum[f / (uint32_t)kScanTile];
 }
 
-__global__ void k_preorder(TreeBufs tb, uint32_t lb, uint32_t le) {
-  const uint32_t i = lb + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= le || tb.b_split[i] < 0) return;
-  const uint32_t p = tb.b_pre[i];
-  const uint32_t c0 = tb.b_c0[i];
-  tb.b_pre[c0] = p + 1u;
-  tb.b_pre[tb.b_c1[i]] = p + 1u + tb.b_size[c0];
-}
-
-__device__ inline uint32_t compact3(uint64_t k, int a) {
-  // bits of axis a sit at positions 3b + (2 - a)
-  uint32_t q = 0;
-  for (int b = 0; b < kKeyBits; ++b) q |= (uint32_t)((k >> (3 * b + 2 - a)) & 1ull) << b;
-  return q;
-}
-
-__global__ void k_scatter_nodes(TreeBufs tb, uint32_t total) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const uint32_t p = tb.b_pre[i];
-  const int l = tb.b_lown[i];
-  const uint64_t key = tb.keys[tb.b_first[i]];
+__device__ inline void put_node(const TreeBufs& tb, uint32_t p, uint64_t key, int lown, bool leaf,
+                                uint2 link, uint32_t next, int depth, bool big) {
   uint32_t kk[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) kk[a] = compact3(key, a) >> (kKeyBits - nbits_axis(l, a));
-  const bool leaf = tb.b_split[i] < 0;
-  tb.nk[p] = make_uint4(kk[0], kk[1], kk[2], (uint32_t)l | (leaf ? META_LEAF : 0u));
-  tb.nlink[p] = leaf ? make_uint2(tb.b_first[i], tb.b_count[i])
-                     : make_uint2(tb.b_pre[tb.b_c1[i]], (uint32_t)tb.b_split[i]);
-  tb.next[p] = p + tb.b_size[i];
+  for (int a = 0; a < 3; ++a) kk[a] = compact3(key, a) >> (kKeyBits - nbits_axis(lown, a));
+  tb.nk[p] = make_uint4(kk[0], kk[1], kk[2], (uint32_t)lown | (leaf ? META_LEAF : 0u));
+  tb.nlink[p] = link;
+  tb.next[p] = next;
+  tb.depth[p] = (uint8_t)(depth | (big ? kDeepBig : 0));
+}
+
+// The kept nodes and their buckets in preorder.  A node comes after every
+// node that starts before it and after its ancestors that start with it:
+// its index is the prefix sum at its first slot plus the number of the
+// latter, counted (with its depth) by climbing to the root.  Nodes of up to
+// kSubtree elements below a larger one are listed as subtree roots.
+//
+// A workgroup strides over the slots and adds its counts per depth and its
+// list of roots once: with a workgroup per 256 slots, their atomics on a few
+// shared lines took most of 495 us at 2^21 elements (now 150).
+__global__ void __launch_bounds__(256) k_nodes(int64_t n, int leaf_size, TreeBufs tb) {
+  constexpr uint32_t kList = 1024, kMostNew = 3 * 256;
+  __shared__ uint32_t lcnt[kMaxLevels + 3], lbig, nlist, lbase, list[kList];
+  if (tb.words->resort) return;
+  const int t = threadIdx.x;
+  for (int k = t; k < kMaxLevels + 3; k += 256) lcnt[k] = 0u;
+  if (t == 0) {
+    lbig = 0u;
+    nlist = 0u;
+  }
+  __syncthreads();
+  const uint64_t* keys = tb.keys;
+  auto flush = [&]() {   // the roots listed so far to the global list
+    __syncthreads();
+    if (t == 0 && nlist) lbase = atomicAdd(&tb.words->nroots, nlist);
+    __syncthreads();
+    for (uint32_t k = t; k < nlist; k += 256) tb.roots[lbase + k] = list[k];
+    __syncthreads();
+    if (t == 0) nlist = 0u;
+    __syncthreads();
+  };
+  for (int64_t i0 = blockIdx.x * (int64_t)256; i0 < n; i0 += (int64_t)gridDim.x * 256) {
+    const int64_t i = i0 + t;
+    const uint32_t e = i < n ? tb.r_end[i] : kNoNode;
+    if (i == 0 && e == kNoNode) {   // one bucket
+      put_node(tb, 0u, keys[0], 0, true, make_uint2(0u, (uint32_t)n), 1u, 0, false);
+      atomicAdd(&lcnt[0], 1u);
+      list[atomicAdd(&nlist, 1u)] = 0u;
+    }
+    if (e != kNoNode) {
+      const uint32_t f = min((uint32_t)i, e), l = max((uint32_t)i, e), g = tb.r_split[i];
+      int depth = 0, lown = 0;
+      uint32_t same = 0, pcount = 0;
+      for (uint32_t j = (uint32_t)i; j != 0u && depth < kMaxLevels; ++depth) {
+        const uint32_t q = tb.r_par[j], qe = tb.r_end[q];
+        if (depth == 0) {
+          const uint32_t gs = tb.r_split[q];
+          lown = __clzll((long long)(keys[gs] ^ keys[gs + 1]));   // parent's split bit + 1
+          pcount = max(q, qe) - min(q, qe) + 1u;
+        }
+        same += min(q, qe) == f ? 1u : 0u;
+        j = q;
+      }
+      const int s = __clzll((long long)(keys[g] ^ keys[g + 1])) - 1;   // split bit
+      const uint32_t count = l - f + 1u;
+      const bool big = count > (uint32_t)kSubtree;
+      const uint32_t p = starts_before(tb, f) + same, c1 = starts_before(tb, g + 1u);
+      put_node(tb, p, keys[f], lown, false, make_uint2(c1, (uint32_t)s),
+               starts_before(tb, l + 1u), depth, big);
+      atomicAdd(&lcnt[depth], 1u);
+      if (big) atomicMax(&lbig, (uint32_t)depth + 1u);
+      else if (i == 0 || pcount > (uint32_t)kSubtree) list[atomicAdd(&nlist, 1u)] = p;
+      const uint32_t cf[2] = {f, g + 1u}, cl[2] = {g, l}, cp[2] = {p + 1u, c1};
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (kept_range(keys, cf[q], cl[q], leaf_size)) continue;
+        put_node(tb, cp[q], keys[cf[q]], s + 1, true, make_uint2(cf[q], cl[q] - cf[q] + 1u),
+                 cp[q] + 1u, depth + 1, false);
+        atomicAdd(&lcnt[depth + 1], 1u);
+        if (big) list[atomicAdd(&nlist, 1u)] = cp[q];
+      }
+    }
+    __syncthreads();
+    const bool full = nlist > kList - kMostNew;   // uniform: a barrier on either side
+    __syncthreads();
+    if (full) flush();
+  }
+  flush();
+  for (int k = t; k < kMaxLevels + 3; k += 256)
+    if (lcnt[k]) atomicAdd(&tb.words->lcnt[k], lcnt[k]);
+  if (t == 0 && lbig > __atomic_load_n(&tb.words->bigdepth, __ATOMIC_RELAXED))
+    atomicMax(&tb.words->bigdepth, lbig);
+}
+
+// The nodes grouped by depth: levels[d] the index range of depth d in b_pre,
+// b_lown and b_split.  Workgroup 0 also writes the level table and the
+// counts the host reads back, and completes the device's DevTree.
+__global__ void __launch_bounds__(256) k_levels(int64_t n, TreeBufs tb) {
+  __shared__ uint32_t lbeg[kMaxLevels + 4], lcnt[kMaxLevels + 3], lbase[kMaxLevels + 3];
+  BuildWords& bw = *tb.words;
+  if (bw.resort) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) tb.info[0] = 1u;
+    return;
+  }
+  const int t = threadIdx.x;
+  if (t < kMaxLevels + 3) lcnt[t] = bw.lcnt[t];
+  __syncthreads();
+  if (t == 0) {
+    uint32_t run = 0, d = 0;
+    for (int k = 0; k < kMaxLevels + 3; ++k) {
+      const uint32_t c = lcnt[k];
+      lbeg[k] = run;
+      run += c;
+      if (c) d = (uint32_t)k + 1u;
+    }
+    lbeg[kMaxLevels + 3] = run;
+    if (blockIdx.x == 0) {
+      tb.info[0] = 0u;
+      tb.info[1] = run;
+      tb.info[2] = d;
+      tb.info[3] = bw.bigdepth;
+      tb.dev->num_nodes = (int64_t)run;
+      tb.dev->depth = (int32_t)d;
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && t < kMaxLevels + 3) tb.levels[t] = make_uint2(lbeg[t], lbeg[t + 1]);
+  const uint32_t total = lbeg[kMaxLevels + 3];
+  for (uint32_t p0 = blockIdx.x * 256u; p0 < total; p0 += gridDim.x * 256u) {
+    __syncthreads();
+    if (t < kMaxLevels + 3) lcnt[t] = 0u;
+    __syncthreads();
+    const uint32_t p = p0 + (uint32_t)t;
+    int d = 0;
+    uint32_t rank = 0;
+    if (p < total) {
+      d = (int)(tb.depth[p] & (kDeepBig - 1u));
+      rank = atomicAdd(&lcnt[d], 1u);
+    }
+    __syncthreads();
+    if (t < kMaxLevels + 3 && lcnt[t]) lbase[t] = lbeg[t] + atomicAdd(&bw.lcur[t], lcnt[t]);
+    __syncthreads();
+    if (p < total) {
+      const uint32_t i = lbase[d] + rank;
+      const uint4 nk = tb.nk[p];
+      tb.b_pre[i] = p;
+      tb.b_lown[i] = (int32_t)(nk.w & 63u);
+      tb.b_split[i] = (nk.w & META_LEAF) ? -1 : (int32_t)tb.nlink[p].y;
+    }
+  }
 }
 
 // --------------------------------------------------------------- moments
-// Bucket sums over the elements in key order, parents as child0 + child1.
-// The bucket absorption is sum(kappa m) / sum(m / rho) (Section 2.6);
-// the centre of luminosity is sum(Lbol x)/Lbol, the box centre when dark.
-__global__ void k_moments(TreeBufs tb, uint32_t lb, uint32_t le, int64_t n, int B, int nclass) {
-  const uint32_t i = lb + blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= le) return;
-  const uint32_t p = tb.b_pre[i];
-  double Lb[kMaxBands], sl[3] = {0.0, 0.0, 0.0}, lbol = 0.0, kmass = 0.0;
-  for (int b = 0; b < B; ++b) Lb[b] = 0.0;
+// Luminosity centre sl/lbol, the box centre when dark, and the node's flags.
+__device__ inline void node_done(const TreeBufs& tb, uint32_t p, const double sl[3], double lbol,
+                                 double kmass) {
   uint4 nk = tb.nk[p];
-  if (tb.b_split[i] < 0) {
-    double kmv[kMaxBands], vol = 0.0;
-    for (int b = 0; b < B; ++b) kmv[b] = 0.0;
-    const uint32_t f = tb.b_first[i], c = tb.b_count[i];
-    for (uint32_t s = f; s < f + c; ++s) {
-      const double ms = (double)tb.m[s];
-      for (int b = 0; b < B; ++b) {
-        const double kv = (double)tb.kappa[(int64_t)b * n + s];
-        Lb[b] += (double)tb.lum[(int64_t)b * n + s];
-        kmv[b] += kv * ms;
-        kmass += kv * ms;
-      }
-      const double lbs = tb.lbol[s];
-      lbol += lbs;
-      sl[0] += lbs * (double)tb.x[s];
-      sl[1] += lbs * (double)tb.y[s];
-      sl[2] += lbs * (double)tb.z[s];
-      vol += ms / (double)tb.rho[s];
-    }
-    const int64_t row = (int64_t)p * nclass * B;
-    for (int b = 0; b < B; ++b) {
-      const double ab = kmv[b] / vol;
-      for (int c2 = 0; c2 < nclass; ++c2) {
-        tb.alpha64[row + (int64_t)c2 * B + b] = ab;
-        tb.alpha32[row + (int64_t)c2 * B + b] = (float)ab;
-      }
-    }
-  } else {
-    const uint32_t p0 = p + 1u, p1 = tb.nlink[p].x;
-    for (int b = 0; b < B; ++b)
-      Lb[b] = tb.Lb[(int64_t)p0 * B + b] + tb.Lb[(int64_t)p1 * B + b];
-    const double4 s0 = tb.sl[p0], s1 = tb.sl[p1];
-    lbol = s0.w + s1.w;
-    sl[0] = s0.x + s1.x;
-    sl[1] = s0.y + s1.y;
-    sl[2] = s0.z + s1.z;
-    kmass = tb.kmass[p0] + tb.kmass[p1];
-  }
-  for (int b = 0; b < B; ++b) tb.Lb[(int64_t)p * B + b] = Lb[b];
-  tb.sl[p] = make_double4(sl[0], sl[1], sl[2], lbol);
-  tb.kmass[p] = kmass;
   double lo[3], hi[3];
   node_box(tb.hdr, nk, lo, hi);
   double c[3];
   for (int a = 0; a < 3; ++a) c[a] = (lbol > 0.0) ? sl[a] / lbol : 0.5 * (lo[a] + hi[a]);
+  tb.sl[p] = make_double4(sl[0], sl[1], sl[2], lbol);
+  tb.kmass[p] = kmass;
   tb.cen[p] = make_double4(c[0], c[1], c[2], lbol);
-  nk.w |= (lbol > 0.0 ? META_LUM : 0u) | (kmass > 0.0 ? META_ABS : 0u);
-  tb.nk[p] = nk;
+  tb.nk[p].w = nk.w | (lbol > 0.0 ? META_LUM : 0u) | (kmass > 0.0 ? META_ABS : 0u);
 }
 
-// Internal nodes of one level, one thread per (node, direction class): the
-// two children combine on the split box, then the result grows through the
-// empty prefix boxes up to the owned box (empty space is vacuum).  With
-// `linear` (TREVR_ABSORPTION_AVG) the combine is the linear volume-weighted
-// mean instead of the transmission average.
-__global__ void k_alpha(TreeBufs tb, uint32_t lb, uint32_t le, int B, int nclass, int linear) {
-  const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t cnt = (int64_t)(le - lb) * nclass;
-  if (gid >= cnt) return;
-  const uint32_t i = lb + (uint32_t)(gid / nclass);
-  const int c = (int)(gid % nclass);
-  const int s = tb.b_split[i];
-  if (s < 0) return;
-  const uint32_t p = tb.b_pre[i], p0 = p + 1u, p1 = tb.nlink[p].x;
-  const int l = tb.b_lown[i];
-  const double L = tb.hdr[3];
-  for (int b = 0; b < B; ++b) {
-    const double a1 = tb.alpha64[((int64_t)p0 * nclass + c) * B + b];
-    const double a2 = tb.alpha64[((int64_t)p1 * nclass + c) * B + b];
-    double A;
-    if (linear) {
-      A = combine_linear(a1, a2);
-      for (int mm = s - 1; mm >= l; --mm) A = combine_linear(A, 0.0);
-    } else {
-      A = combine64(&tb.geom[((int64_t)s * nclass + c) * 3], L, a1, a2);
-      for (int mm = s - 1; mm >= l; --mm)
-        A = combine64(&tb.geom[((int64_t)mm * nclass + c) * 3], L, A, 0.0);
+// One of a bucket's B + 1 sums over its elements in key order.  Role b < B:
+// the luminosity and the absorption sum(kappa m) / sum(m / rho) (Section 2.6)
+// of band b, the same in every direction; role B: the luminosity centre and
+// the absorbing mass.  Eight elements' values are loaded before they are
+// added, so a role waits on memory a few times and not once per element.
+__device__ inline void leaf_role(const TreeBufs& tb, uint32_t p, int role, int64_t n, int B,
+                                 int nclass) {
+  const uint2 lk = tb.nlink[p];
+  const uint32_t end = lk.x + lk.y;
+  constexpr int kLoad = 8;
+  if (role < B) {
+    const float* kap = tb.kappa + (int64_t)role * n;
+    const float* lum = tb.lum + (int64_t)role * n;
+    double Lb = 0.0, kmv = 0.0, vol = 0.0;
+    for (uint32_t s0 = lk.x; s0 < end; s0 += kLoad) {
+      float m[kLoad], r[kLoad], kv[kLoad], lv[kLoad];
+#pragma unroll
+      for (int k = 0; k < kLoad; ++k) {
+        const uint32_t s = min(s0 + (uint32_t)k, end - 1u);
+        m[k] = tb.m[s];
+        r[k] = tb.rho[s];
+        kv[k] = kap[s];
+        lv[k] = lum[s];
+      }
+#pragma unroll
+      for (int k = 0; k < kLoad; ++k) {
+        if (s0 + (uint32_t)k >= end) break;
+        const double ms = (double)m[k];
+        Lb += (double)lv[k];
+        kmv += (double)kv[k] * ms;
+        vol += ms / (double)r[k];
+      }
     }
-    tb.alpha64[((int64_t)p * nclass + c) * B + b] = A;
-    tb.alpha32[((int64_t)p * nclass + c) * B + b] = (float)A;
+    tb.Lb[(int64_t)p * B + role] = Lb;
+    const double ab = kmv / vol;
+    const int64_t row = (int64_t)p * nclass * B + role;
+    for (int c = 0; c < nclass; ++c) {
+      tb.alpha64[row + (int64_t)c * B] = ab;
+      tb.alpha32[row + (int64_t)c * B] = (float)ab;
+    }
+    return;
+  }
+  double sl[3] = {0.0, 0.0, 0.0}, lbol = 0.0, kmass = 0.0;
+  for (uint32_t s0 = lk.x; s0 < end; s0 += kLoad) {
+    float x[kLoad], y[kLoad], z[kLoad];
+    double lb[kLoad];
+#pragma unroll
+    for (int k = 0; k < kLoad; ++k) {
+      const uint32_t s = min(s0 + (uint32_t)k, end - 1u);
+      x[k] = tb.x[s];
+      y[k] = tb.y[s];
+      z[k] = tb.z[s];
+      lb[k] = tb.lbol[s];
+    }
+#pragma unroll
+    for (int k = 0; k < kLoad; ++k) {
+      if (s0 + (uint32_t)k >= end) break;
+      lbol += lb[k];
+      sl[0] += lb[k] * (double)x[k];
+      sl[1] += lb[k] * (double)y[k];
+      sl[2] += lb[k] * (double)z[k];
+    }
+  }
+  for (uint32_t s = lk.x; s < end; ++s) {
+    const double ms = (double)tb.m[s];
+    for (int b = 0; b < B; ++b) kmass += (double)tb.kappa[(int64_t)b * n + s] * ms;
+  }
+  node_done(tb, p, sl, lbol, kmass);
+}
+
+// One of a cell's nclass x B + 1 steps from its two children.  Role c B + b:
+// the transmission average of band b in direction class c -- the children
+// combine on the split box, then the result grows through the empty prefix
+// boxes up to the owned box (empty space is vacuum); with `linear`
+// (TREVR_ABSORPTION_AVG) the combine is the linear volume-weighted mean
+// instead.  Role nclass x B: the moments.
+__device__ inline void cell_role(const TreeBufs& tb, uint32_t p, int role, int B, int nclass,
+                                 int linear) {
+  const uint2 lk = tb.nlink[p];
+  const uint32_t p0 = p + 1u, p1 = lk.x;
+  if (role == nclass * B) {
+    for (int b = 0; b < B; ++b)
+      tb.Lb[(int64_t)p * B + b] = tb.Lb[(int64_t)p0 * B + b] + tb.Lb[(int64_t)p1 * B + b];
+    const double4 s0 = tb.sl[p0], s1 = tb.sl[p1];
+    const double sl[3] = {s0.x + s1.x, s0.y + s1.y, s0.z + s1.z};
+    node_done(tb, p, sl, s0.w + s1.w, tb.kmass[p0] + tb.kmass[p1]);
+    return;
+  }
+  const int s = (int)lk.y, l = (int)(tb.nk[p].w & 63u), c = role / B;
+  const int64_t row = (int64_t)nclass * B;
+  const double a1 = tb.alpha64[p0 * row + role], a2 = tb.alpha64[p1 * row + role];
+  double A;
+  if (linear) {
+    A = combine_linear(a1, a2);
+    for (int mm = s - 1; mm >= l; --mm) A = combine_linear(A, 0.0);
+  } else {
+    const double L = tb.hdr[3];
+    A = combine64(&tb.geom[((int64_t)s * nclass + c) * 3], L, a1, a2);
+    for (int mm = s - 1; mm >= l; --mm)
+      A = combine64(&tb.geom[((int64_t)mm * nclass + c) * 3], L, A, 0.0);
+  }
+  tb.alpha64[p * row + role] = A;
+  tb.alpha32[p * row + role] = (float)A;
+}
+
+// Subtrees of at most kSubtree elements, a workgroup each: its buckets, then
+// its cells from the deepest level up, a barrier between levels (the
+// children's values were stored by the same workgroup).  One launch for some
+// ten levels; level by level over the whole tree, moments and averages took 528
+// us in 50 launches (2^18 elements, three bands), now 103 here and 86 in k_cells.
+__global__ void __launch_bounds__(256) k_subtrees(int64_t n, int B, int nclass, int linear,
+                                                  TreeBufs tb) {
+  constexpr int kMost = 2 * kSubtree;
+  __shared__ uint16_t order[kMost];
+  // bins: the buckets, then the cells by relative depth (at most 63 levels of
+  // cells: a key has 63 bits to split at)
+  __shared__ uint32_t cnt[64], cur[64];
+  if (tb.words->resort) return;
+  const int t = threadIdx.x;
+  const uint32_t nroots = tb.words->nroots, roles = (uint32_t)(nclass * B + 1);
+  for (uint32_t q = blockIdx.x; q < nroots; q += gridDim.x) {
+    const uint32_t p0 = tb.roots[q], m = tb.next[p0] - p0;
+    const int d0 = (int)(tb.depth[p0] & (kDeepBig - 1u));
+    __syncthreads();
+    if (t < 64) cnt[t] = 0u;
+    __syncthreads();
+    for (uint32_t k = t; k < m; k += 256) {
+      const bool leaf = (tb.nk[p0 + k].w & META_LEAF) != 0u;
+      atomicAdd(&cnt[leaf ? 0 : 1 + (int)(tb.depth[p0 + k] & (kDeepBig - 1u)) - d0], 1u);
+    }
+    __syncthreads();
+    if (t < 64) {
+      const uint32_t c = cnt[t];
+      uint32_t incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
+        if (t >= o) incl += u;
+      }
+      cnt[t] = cur[t] = incl - c;
+    }
+    __syncthreads();
+    for (uint32_t k = t; k < m; k += 256) {
+      const bool leaf = (tb.nk[p0 + k].w & META_LEAF) != 0u;
+      order[atomicAdd(&cur[leaf ? 0 : 1 + (int)(tb.depth[p0 + k] & (kDeepBig - 1u)) - d0], 1u)] =
+          (uint16_t)k;
+    }
+    __syncthreads();
+    const uint32_t nleaf = cur[0];
+    for (uint32_t w = t; w < nleaf * (uint32_t)(B + 1); w += 256)
+      leaf_role(tb, p0 + order[w / (uint32_t)(B + 1)], (int)(w % (uint32_t)(B + 1)), n, B, nclass);
+    int top = 63;
+    while (top > 0 && cur[top] == cnt[top]) --top;
+    for (int d = top; d >= 1; --d) {
+      __syncthreads();
+      const uint32_t b = cnt[d], work = (cur[d] - b) * roles;
+      for (uint32_t w = t; w < work; w += 256)
+        cell_role(tb, p0 + order[b + w / roles], (int)(w % roles), B, nclass, linear);
+    }
+  }
+}
+
+// The larger cells of levels dhi down to dlo, one thread per (cell, role):
+// several levels in one launch of one workgroup (a barrier between them)
+// where they are small, one level per launch otherwise.
+__global__ void __launch_bounds__(1024) k_cells(int dhi, int dlo, int B, int nclass, int linear,
+                                                TreeBufs tb) {
+  for (int d = dhi; d >= dlo; --d) {
+    const uint2 lv = tb.levels[d];
+    const uint32_t roles = (uint32_t)(nclass * B + 1);
+    const int64_t work = (int64_t)(lv.y - lv.x) * roles;
+    for (int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; w < work;
+         w += (int64_t)gridDim.x * blockDim.x) {
+      const uint32_t p = tb.b_pre[lv.x + (uint32_t)(w / roles)];
+      if (tb.depth[p] & kDeepBig) cell_role(tb, p, (int)(w % roles), B, nclass, linear);
+    }
+    __syncthreads();
   }
 }
 
@@ -572,6 +1089,12 @@ DirTables make_dir_tables(int nside) {
     for (int c = 0; c < t.nclass; ++c)
       combine_geometry(s, l % 3, &t.ray_n[3 * rep[c]], &t.geom[((size_t)l * t.nclass + c) * 3]);
   }
+  t.block.assign(dir_block(t.nray, t.nclass), 0.0);
+  std::copy(t.ray_n.begin(), t.ray_n.end(), t.block.begin());
+  std::copy(t.geom.begin(), t.geom.end(), t.block.begin() + t.ray_n.size());
+  int32_t* ints = reinterpret_cast<int32_t*>(t.block.data() + t.ray_n.size() + t.geom.size());
+  std::copy(t.ray_class.begin(), t.ray_class.end(), ints);
+  std::copy(t.ray_anti.begin(), t.ray_anti.end(), ints + t.nray);
   return t;
 }
 
@@ -581,17 +1104,26 @@ size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, Tre
   const int64_t M = 2 * n;
   const int B = p.n_bands;
   const int nray = 12 * p.nside * p.nside;
-  const int64_t nblk = (n + SortCfg::kTile - 1) / SortCfg::kTile;
   t.hdr = cv.take<double>(8);
   t.bbox_u = cv.take<uint32_t>(8);
   t.err = cv.take<uint32_t>(4);
   t.counters = cv.take<unsigned long long>(CNT_N);
-  t.alloc = cv.take<uint32_t>(4);
+  t.words = cv.take<BuildWords>(1);
   t.keys = cv.take<uint64_t>(n);
   t.keys_alt = cv.take<uint64_t>(n);
   t.vals = cv.take<uint32_t>(n);
   t.vals_alt = cv.take<uint32_t>(n);
-  t.hist = cv.take<uint32_t>(256 * nblk + 1);
+  t.top = cv.take<uint32_t>(n);
+  t.top_alt = cv.take<uint32_t>(n);
+  t.hist = cv.take<uint32_t>(256 * sort_tiles(n));
+  t.dtot = cv.take<uint32_t>(256);
+  t.rec = cv.take<float>((size_t)n * rec_floats(B));
+  t.starts = cv.take<uint32_t>(n + 1);
+  t.tsum = cv.take<uint32_t>(n / (1024 * kScanPer) + 2);
+  t.roots = cv.take<uint32_t>(n);
+  t.r_end = t.top;          // free once the elements are gathered
+  t.r_split = t.top_alt;
+  t.r_par = t.vals_alt;
   t.x = cv.take<float>(n);
   t.y = cv.take<float>(n);
   t.z = cv.take<float>(n);
@@ -602,40 +1134,80 @@ size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, Tre
   t.h = cv.take<double>(n);
   t.lbol = cv.take<double>(n);
   t.perm = cv.take<uint32_t>(n);
-  t.b_first = cv.take<uint32_t>(M);
-  t.b_count = cv.take<uint32_t>(M);
-  t.b_c0 = cv.take<uint32_t>(M);
-  t.b_c1 = cv.take<uint32_t>(M);
-  t.b_size = cv.take<uint32_t>(M);
   t.b_pre = cv.take<uint32_t>(M);
   t.b_lown = cv.take<int32_t>(M);
   t.b_split = cv.take<int32_t>(M);
   t.nk = cv.take<uint4>(M);
   t.nlink = cv.take<uint2>(M);
   t.next = cv.take<uint32_t>(M);
+  t.depth = cv.take<uint8_t>(M);
   t.cen = cv.take<double4>(M);
   t.sl = cv.take<double4>(M);
   t.Lb = cv.take<double>(M * B);
   t.kmass = cv.take<double>(M);
   t.alpha64 = cv.take<double>(M * nclass * B);
   t.alpha32 = cv.take<float>(M * nclass * B);
-  t.ray_n = cv.take<double>(3 * nray);
-  t.ray_class = cv.take<int32_t>(nray);
-  t.ray_anti = cv.take<int32_t>(nray);
+  // the direction tables, laid out as DirTables::block
+  t.ray_n = cv.take<double>(dir_block(nray, nclass));
+  t.geom = t.ray_n ? t.ray_n + 3 * nray : nullptr;
+  t.ray_class = t.ray_n ? (int32_t*)(t.geom + (size_t)kMaxLevels * nclass * 3) : nullptr;
+  t.ray_anti = t.ray_n ? t.ray_class + nray : nullptr;
   t.csrc_d = nullptr;
   t.csrc_a = nullptr;
   if (p.flags & TREVR_COMPLEX_SRC) {
     t.csrc_d = cv.take<double>(M * nray);
     t.csrc_a = cv.take<double>(M * nray * B);
   }
-  t.geom = cv.take<double>((size_t)kMaxLevels * nclass * 3);
   t.dev = cv.take<DevTree>(1);
-  t.levels = cv.take<uint2>(kMaxLevels + 3);
+  t.levels = cv.take<uint2>(kMaxLevels + 3 + kInfoWords / 2);
+  t.info = base ? reinterpret_cast<uint32_t*>(t.levels + kMaxLevels + 3) : nullptr;
   if (o) *o = t;
   return cv.off + 256;
 }
 
 static inline unsigned grid_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+
+#define TREVR_LAUNCH_CHECK(what)                                               \
+  do {                                                                         \
+    if ((rc = hip_check(hipGetLastError(), what)) != TREVR_OK) return rc;      \
+  } while (0)
+
+// The radix passes.  Tiles of 1024 elements up to kSortTileSwitch (at 2^18
+// elements 256 tiles, one per CU; tiles of 4096 left three quarters of the
+// chip idle), of 4096 above, where the counts per tile weigh more.
+template <bool WIDE, int ITEMS>
+static trevr_status sort_pass(trevr_tree* T, const void* in, const uint32_t* vin, void* out,
+                              uint32_t* vout, int pass) {
+  trevr_status rc;
+  const TreeBufs& tb = T->buf;
+  const int nblk = (int)((T->n + 256 * ITEMS - 1) / (256 * ITEMS));
+  k_sort_hist<WIDE, ITEMS><<<nblk, 256, 0, T->stream>>>(in, T->n, pass, tb, nblk);
+  TREVR_LAUNCH_CHECK("k_sort_hist");
+  k_sort_rows<<<256, 256, 0, T->stream>>>(tb.hist, tb.dtot, nblk);
+  TREVR_LAUNCH_CHECK("k_sort_rows");
+  k_sort_scatter<WIDE, ITEMS><<<nblk, 256, 0, T->stream>>>(in, vin, out, vout, T->n, pass, tb,
+                                                          nblk);
+  TREVR_LAUNCH_CHECK("k_sort_scatter");
+  return rc;
+}
+
+template <bool WIDE> static trevr_status sort_passes(trevr_tree* T) {
+  const TreeBufs& tb = T->buf;
+  const void* in = tb.keys_alt;   // full keys in input order
+  const uint32_t* vin = nullptr;
+  for (int pass = 0; pass < (WIDE ? 8 : 4); ++pass) {
+    const bool odd = pass & 1;
+    void* out = WIDE ? (void*)(odd ? tb.keys_alt : tb.keys) : (void*)(odd ? tb.top : tb.top_alt);
+    uint32_t* vout = odd ? tb.vals : tb.vals_alt;
+    const trevr_status rc = T->n <= kSortTileSwitch
+                                ? sort_pass<WIDE, 4>(T, in, vin, out, vout, pass)
+                                : sort_pass<WIDE, 16>(T, in, vin, out, vout, pass);
+    if (rc != TREVR_OK) return rc;
+    in = out;
+    vin = vout;
+  }
+  return TREVR_OK;
+}
 
 trevr_status build_tree_impl(trevr_tree* T, const float* x, const float* y, const float* z,
                              const float* m, const float* rho, const float* kappa,
@@ -646,120 +1218,98 @@ trevr_status build_tree_impl(trevr_tree* T, const float* x, const float* y, cons
   TreeBufs& tb = T->buf;
   hipStream_t st = T->stream;
   trevr_status rc;
-#define TREVR_LAUNCH_CHECK(what)                                               \
-  do {                                                                         \
-    if ((rc = hip_check(hipGetLastError(), what)) != TREVR_OK) return rc;      \
-  } while (0)
 
-  // direction tables
-  if ((rc = hip_check(hipMemcpyAsync(tb.ray_n, T->dirs.ray_n.data(),
-                                     sizeof(double) * T->dirs.ray_n.size(),
-                                     hipMemcpyHostToDevice, st), "copy rays")) != TREVR_OK) return rc;
-  if ((rc = hip_check(hipMemcpyAsync(tb.ray_class, T->dirs.ray_class.data(),
-                                     sizeof(int32_t) * T->dirs.ray_class.size(),
-                                     hipMemcpyHostToDevice, st), "copy classes")) != TREVR_OK) return rc;
-  if ((rc = hip_check(hipMemcpyAsync(tb.ray_anti, T->dirs.ray_anti.data(),
-                                     sizeof(int32_t) * T->dirs.ray_anti.size(),
-                                     hipMemcpyHostToDevice, st), "copy antipodes")) != TREVR_OK)
+  // the device's DevTree (k_levels completes it) and the direction tables
+  if ((rc = hip_check(hipMemcpyAsync(tb.dev, &T->dev, sizeof(DevTree), hipMemcpyHostToDevice, st),
+                      "copy tree table")) != TREVR_OK) return rc;
+  if ((rc = hip_check(hipMemcpyAsync(tb.ray_n, T->dirs.block.data(),
+                                     sizeof(double) * T->dirs.block.size(),
+                                     hipMemcpyHostToDevice, st), "copy direction tables")) !=
+      TREVR_OK)
     return rc;
-  if ((rc = hip_check(hipMemcpyAsync(tb.geom, T->dirs.geom.data(),
-                                     sizeof(double) * T->dirs.geom.size(),
-                                     hipMemcpyHostToDevice, st), "copy geometry")) != TREVR_OK) return rc;
 
-  k_init<<<1, 64, 0, st>>>(tb.bbox_u, tb.err, tb.counters, tb.alloc);
+  const double* bx = T->p.box;
+  k_init<<<1, 256, 0, st>>>(tb, bx[0], bx[1], bx[2], bx[3]);
   TREVR_LAUNCH_CHECK("k_init");
-  if (!(T->p.box[3] > 0.0)) {
+  if (!(bx[3] > 0.0)) {
     k_bbox<<<std::min<int64_t>(64, grid_for(n, 256)), 256, 0, st>>>(x, y, z, n, tb.bbox_u);
     TREVR_LAUNCH_CHECK("k_bbox");
+    k_header<<<1, 64, 0, st>>>(tb.bbox_u, tb.hdr);
+    TREVR_LAUNCH_CHECK("k_header");
   }
-  k_header<<<1, 64, 0, st>>>(tb.bbox_u, T->p.box[0], T->p.box[1], T->p.box[2], T->p.box[3],
-                             tb.hdr);
-  TREVR_LAUNCH_CHECK("k_header");
-  k_keys<<<grid_for(n, 256), 256, 0, st>>>(x, y, z, m, rho, kappa, lum, n, B, tb.hdr, tb.keys,
-                                           tb.vals, tb.err);
+  const unsigned gn = grid_for(n, 256);
+  k_keys<<<gn, 256, 0, st>>>(x, y, z, m, rho, kappa, lum, n, B, tb);
   TREVR_LAUNCH_CHECK("k_keys");
-
-  // radix sort: 8 passes of 8 bits, ping-pong ending in keys/vals
-  const int nblk = (int)((n + SortCfg::kTile - 1) / SortCfg::kTile);
-  uint64_t *ka = tb.keys, *kb = tb.keys_alt;
-  uint32_t *va = tb.vals, *vb = tb.vals_alt;
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 8 * pass;
-    k_sort_hist<<<nblk, 256, 0, st>>>(ka, n, shift, tb.hist, nblk);
-    TREVR_LAUNCH_CHECK("k_sort_hist");
-    k_scan_u32<<<1, 1024, 0, st>>>(tb.hist, (int64_t)256 * nblk, nullptr);
-    TREVR_LAUNCH_CHECK("k_scan_u32");
-    k_sort_scatter<<<nblk, 256, 0, st>>>(ka, va, kb, vb, n, shift, tb.hist, nblk);
-    TREVR_LAUNCH_CHECK("k_sort_scatter");
-    std::swap(ka, kb);
-    std::swap(va, vb);
-  }
-  k_gather<<<grid_for(n, 256), 256, 0, st>>>(x, y, z, m, rho, kappa, lum, n, B, tb.vals, tb);
-  TREVR_LAUNCH_CHECK("k_gather");
-
-  // topology, top-down by level
-  k_root<<<1, 64, 0, st>>>(tb, n);
-  TREVR_LAUNCH_CHECK("k_root");
-  // levels in batches, each level's range on the device; the host reads the
-  // ranges back once per batch.  A level has at most twice the nodes of the
-  // one above, which sizes the grids from the last width read back.
-  T->levels.clear();
-  constexpr int kLevelBatch = 6;
-  uint64_t width = 1;   // nodes of level d
-  int d = 0;
-  for (bool done = false; !done;) {
-    const int nb = std::min(kLevelBatch, kMaxLevels + 2 - d);
-    if (nb <= 0) return set_error(TREVR_E_DATA, "tree deeper than the key allows");
-    uint64_t bound = width;
-    for (int k = 0; k < nb; ++k) {
-      k_level<<<grid_for((int64_t)bound, 256), 256, 0, st>>>(tb, d + k, T->p.leaf_size);
-      TREVR_LAUNCH_CHECK("k_level");
-      k_level_next<<<1, 64, 0, st>>>(tb, d + k);
-      TREVR_LAUNCH_CHECK("k_level_next");
-      bound = std::min<uint64_t>(2 * bound, 2 * (uint64_t)n);
+  const int linear = (T->p.flags & TREVR_ABSORPTION_AVG) ? 1 : 0;
+  uint32_t* info = T->host_u32 + 2 * (kMaxLevels + 3);
+  for (bool wide = false;; wide = true) {
+    // an even number of passes ends in the buffers it started from
+    if (n <= kSmallSort) {
+      k_sort_small<<<1, 1024, 0, st>>>(n, tb);
+      TREVR_LAUNCH_CHECK("k_sort_small");
+    } else {
+      rc = wide ? sort_passes<true>(T) : sort_passes<false>(T);
+      if (rc != TREVR_OK) return rc;
+      k_sort_finish<<<gn, 256, 0, st>>>(n, tb, wide ? 1 : 0);
+      TREVR_LAUNCH_CHECK("k_sort_finish");
     }
-    uint2* rb = reinterpret_cast<uint2*>(T->host_u32);   // levels d .. d + nb
-    hipError_t e = hipMemcpyAsync(rb, tb.levels + d, sizeof(uint2) * (nb + 1),
+    k_gather<<<gn, 256, 0, st>>>(n, B, tb);
+    TREVR_LAUNCH_CHECK("k_gather");
+
+    // topology, then the moments of the small subtrees; the host reads the
+    // counts back while those run
+    k_radix<<<gn, 256, 0, st>>>(n, T->p.leaf_size, tb);
+    TREVR_LAUNCH_CHECK("k_radix");
+    const unsigned tiles = grid_for(n + 1, kScanTile);
+    k_scan_tiles<<<tiles, 1024, 0, st>>>(tb.starts, n + 1, tb.tsum);
+    TREVR_LAUNCH_CHECK("k_scan_tiles");
+    if (tiles > 1) {   // (one tile: its offset is the zero of k_init)
+      k_scan_u32<<<1, 1024, 0, st>>>(tb.tsum, tiles, nullptr);
+      TREVR_LAUNCH_CHECK("k_scan_u32");
+    }
+    k_nodes<<<std::min(gn, 512u), 256, 0, st>>>(n, T->p.leaf_size, tb);
+    TREVR_LAUNCH_CHECK("k_nodes");
+    k_levels<<<std::min(gn, 512u), 256, 0, st>>>(n, tb);
+    TREVR_LAUNCH_CHECK("k_levels");
+    const unsigned gs = (unsigned)std::min<int64_t>(2 * n / kSubtree + 1, 8192);
+    k_subtrees<<<gs, 256, 0, st>>>(n, B, nclass, linear, tb);
+    TREVR_LAUNCH_CHECK("k_subtrees");
+    hipError_t e = hipMemcpyAsync(T->host_u32, tb.levels,
+                                  (2 * (kMaxLevels + 3) + kInfoWords) * sizeof(uint32_t),
                                   hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if ((rc = hip_check(e, "level readback")) != TREVR_OK) return rc;
-    for (int k = 0; k <= nb && !done; ++k) {
-      if (rb[k].x >= rb[k].y) done = true;
-      else if (k < nb) T->levels.emplace_back(rb[k].x, rb[k].y);
-    }
-    if (!done) width = rb[nb].y - rb[nb].x;
-    d += nb;
+    if (info[0] == 0u) break;
+    if (wide) return set_error(TREVR_E_HIP, "the full sort did not finish");
+    if ((rc = zero_words(st, &tb.words->resort, 1)) != TREVR_OK) return rc;
   }
-  if (T->levels.size() > (size_t)kMaxLevels + 2)
-    return set_error(TREVR_E_DATA, "tree deeper than the key allows");
-  const uint32_t total = T->levels.back().second;
-  T->num_nodes = total;
-  T->num_leaves = (total + 1) / 2;
-  T->depth = (int32_t)T->levels.size();
-  for (int d = T->depth - 1; d >= 0; --d) {
-    const auto lv = T->levels[d];
-    k_sizes<<<grid_for(lv.second - lv.first, 256), 256, 0, st>>>(tb, lv.first, lv.second);
-    TREVR_LAUNCH_CHECK("k_sizes");
+  T->levels.clear();
+  const uint2* lv = reinterpret_cast<const uint2*>(T->host_u32);
+  for (uint32_t d = 0; d < info[2]; ++d) T->levels.emplace_back(lv[d].x, lv[d].y);
+  T->num_nodes = info[1];
+  T->num_leaves = (T->num_nodes + 1) / 2;
+  T->depth = (int32_t)info[2];
+  T->dev.num_nodes = T->num_nodes;
+  T->dev.depth = T->depth;
+  // the larger cells, deepest level first; the levels next to the root that
+  // one workgroup takes in a step or two share a launch
+  int one = 0;
+  while (one < (int)info[3] &&
+         (int64_t)(lv[one].y - lv[one].x) * (nclass * B + 1) <= 2 * 1024)
+    ++one;
+  for (int d = (int)info[3] - 1; d >= one; --d) {
+    const int64_t work = (int64_t)(lv[d].y - lv[d].x) * (nclass * B + 1);
+    k_cells<<<grid_for(work, 128), 128, 0, st>>>(d, d, B, nclass, linear, tb);
+    TREVR_LAUNCH_CHECK("k_cells");
   }
-  for (int d = 0; d < T->depth; ++d) {
-    const auto lv = T->levels[d];
-    k_preorder<<<grid_for(lv.second - lv.first, 256), 256, 0, st>>>(tb, lv.first, lv.second);
-    TREVR_LAUNCH_CHECK("k_preorder");
+  if (one > 0) {
+    k_cells<<<1, 1024, 0, st>>>(one - 1, 0, B, nclass, linear, tb);
+    TREVR_LAUNCH_CHECK("k_cells");
   }
-  k_scatter_nodes<<<grid_for(total, 256), 256, 0, st>>>(tb, total);
-  TREVR_LAUNCH_CHECK("k_scatter_nodes");
-  for (int d = T->depth - 1; d >= 0; --d) {
-    const auto lv = T->levels[d];
-    k_moments<<<grid_for(lv.second - lv.first, 128), 128, 0, st>>>(tb, lv.first, lv.second, n, B,
-                                                                   nclass);
-    TREVR_LAUNCH_CHECK("k_moments");
-    const int64_t work = (int64_t)(lv.second - lv.first) * nclass;
-    k_alpha<<<grid_for(work, 128), 128, 0, st>>>(tb, lv.first, lv.second, B, nclass,
-                                                  (T->p.flags & TREVR_ABSORPTION_AVG) ? 1 : 0);
-    TREVR_LAUNCH_CHECK("k_alpha");
-    if (T->p.flags & TREVR_COMPLEX_SRC) {
-      const int64_t cw = (int64_t)(lv.second - lv.first) * T->nray;
-      k_csrc<<<grid_for(cw, 128), 128, 0, st>>>(tb, lv.first, lv.second, B, nclass, T->nray);
+  if (T->p.flags & TREVR_COMPLEX_SRC) {
+    for (int d = T->depth - 1; d >= 0; --d) {
+      const int64_t cw = (int64_t)(lv[d].y - lv[d].x) * T->nray;
+      k_csrc<<<grid_for(cw, 128), 128, 0, st>>>(tb, lv[d].x, lv[d].y, B, nclass, T->nray);
       TREVR_LAUNCH_CHECK("k_csrc");
     }
   }

@@ -201,14 +201,11 @@ __device__ inline int directed_ray(const DevTree& T, const double c[3], double u
 // with the through-both rays taking half their length in each child.
 __device__ inline double combine64(const double* g, double L, double a1, double a2) {
   const double lw1 = g[0], lw12 = g[1], d = g[2] * L;
-  double t[3];
-  int nt = 0;
-  if (lw1 > -INFINITY) { t[nt++] = lw1 - d * a1; t[nt++] = lw1 - d * a2; }
-  if (lw12 > -INFINITY) t[nt++] = lw12 - d * (a1 + a2) / 2.0;
-  double mx = t[0];
-  for (int k = 1; k < nt; ++k) mx = fmax(mx, t[k]);
-  double s = 0.0;
-  for (int k = 0; k < nt; ++k) s += exp(t[k] - mx);
+  // a missing term (log weight -inf) contributes exp(-inf) = 0; no array of
+  // the present ones, whose run-time index would put it in memory
+  const double t1 = lw1 - d * a1, t2 = lw1 - d * a2, t3 = lw12 - d * (a1 + a2) / 2.0;
+  const double mx = fmax(fmax(t1, t2), t3);
+  const double s = exp(t1 - mx) + exp(t2 - mx) + exp(t3 - mx);
   return -(mx + log(s)) / d;
 }
 
@@ -242,6 +239,15 @@ __device__ inline uint64_t ballot64(bool p) { return __ballot(p); }
 __device__ inline int mbcnt(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Order LDS writes of some lanes before reads by other lanes of the same
+// wavefront (the lanes execute together; this keeps the compiler and the
+// memory model from reordering across the hand-off).
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Exclusive prefix of v over a workgroup of 1024 threads; *total (when given)

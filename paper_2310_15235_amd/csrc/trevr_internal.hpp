@@ -40,21 +40,54 @@ struct Carve {
   }
 };
 
+// Elements of the subtrees whose moments one workgroup forms, and the mark
+// of larger cells in TreeBufs::depth.
+constexpr int kSubtree = 512;
+constexpr uint32_t kDeepBig = 128;
+static_assert(kMaxLevels + 3 < (int)kDeepBig, "a depth and its mark share a byte");
+constexpr int kInfoWords = 4;
+
+// Counters of a build on the device (zeroed at its start).
+struct BuildWords {
+  unsigned long long diff;              // bits in which some keys differ
+  uint32_t resort;                      // the short sort left a run unsorted
+  uint32_t nroots;                      // entries of roots
+  uint32_t bigdepth;                    // levels holding cells of more than kSubtree elements
+  uint32_t lcnt[kMaxLevels + 3];        // nodes per depth
+  uint32_t lcur[kMaxLevels + 3];        // nodes of each depth placed
+};
+static_assert(sizeof(BuildWords) % 4 == 0 && sizeof(BuildWords) / 4 <= 256, "cleared by 256 threads");
+
+// Floats of an element's packed record (a multiple of four).
+__host__ __device__ inline int rec_floats(int B) { return (5 + 2 * B + 3) & ~3; }
+
+// Tiles of the radix sort: 1024 elements each up to this many, 4096 above.
+constexpr int64_t kSortTileSwitch = 1 << 19;
+inline int64_t sort_tiles(int64_t n) {
+  const int64_t tile = n <= kSortTileSwitch ? 1024 : 4096;
+  return (n + tile - 1) / tile;
+}
+
 // Mutable device pointers of a tree (same memory the DevTree views).
 struct TreeBufs {
   double* hdr;
   uint32_t* bbox_u;           // ordered-uint min/max of x, y, z
-  uint64_t *keys, *keys_alt;
-  uint32_t *vals, *vals_alt, *hist;
+  BuildWords* words;          // counters of the build
+  uint64_t *keys, *keys_alt;  // sorted; in input order (build only)
+  uint32_t *vals, *vals_alt, *top, *top_alt, *hist, *dtot;   // radix passes
+  float* rec;                 // [n][rec_floats(B)] elements packed for the gather
+  uint32_t *starts, *tsum;    // nodes starting at each slot, then their prefix sum
+  uint32_t* roots;            // subtrees of at most kSubtree elements
+  uint32_t *r_end, *r_split, *r_par;   // radix tree (share the sort's buffers)
   float *x, *y, *z, *m, *rho, *kappa, *lum;
   double *h, *lbol;
   uint32_t* perm;
-  uint32_t *b_first, *b_count, *b_c0, *b_c1, *b_size, *b_pre;
+  uint32_t* b_pre;            // nodes grouped by depth (see DevTree)
   int32_t *b_lown, *b_split;
-  uint32_t* alloc;
   uint4* nk;
   uint2* nlink;
   uint32_t* next;
+  uint8_t* depth;             // per node; kDeepBig marks more than kSubtree elements
   double4 *cen, *sl;
   double *Lb, *kmass, *alpha64;
   float* alpha32;
@@ -68,12 +101,8 @@ struct TreeBufs {
   unsigned long long* counters;
   DevTree* dev;               // device copy of the tree's DevTree (one-scene table)
   uint2* levels;              // [kMaxLevels + 3] BFS index ranges per depth
-};
-
-struct SortCfg {
-  static constexpr int kThreads = 256;
-  static constexpr int kItems = 16;
-  static constexpr int kTile = kThreads * kItems;
+  uint32_t* info;             // [kInfoWords] {sort again, nodes, depth, levels of large
+                              // cells}, behind levels: read back together
 };
 
 // Direction tables of an N_side: centres, classes (rays sharing |n_x|,
@@ -85,7 +114,12 @@ struct DirTables {
   std::vector<int32_t> ray_class; // [nray]
   std::vector<int32_t> ray_anti;  // [nray] ray of the opposite direction
   std::vector<double> geom;       // [64][nclass][3]
+  std::vector<double> block;      // ray_n, geom, ray_class, ray_anti: uploaded in one copy
 };
+// Doubles of DirTables::block.
+inline size_t dir_block(int nray, int nclass) {
+  return 3 * (size_t)nray + (size_t)kMaxLevels * nclass * 3 + (size_t)nray;
+}
 DirTables make_dir_tables(int nside);
 
 size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, TreeBufs* out);
@@ -146,9 +180,6 @@ struct trevr_tree {
 
 namespace trevr {
 constexpr int kHostWords = 512;
-// Copy the host DevTree of a tree (and its level table) to the device copy
-// the kernels read; synchronises.
-trevr_status upload_dev(trevr_tree* t);
 trevr_status set_error(trevr_status s, const std::string& msg);
 trevr_status hip_check(hipError_t e, const char* what);
 trevr_status build_tree_impl(trevr_tree* t, const float* x, const float* y, const float* z,
@@ -159,6 +190,8 @@ trevr_status compute_J_impl(trevr_tree* t, const uint8_t* active, const float* b
 trevr_status compute_J_backward_impl(trevr_tree* t, const uint8_t* active, const float* bg,
                                      const double* gJ, double* gL, double* gkappa, double* grho,
                                      void* scratch, size_t scratch_bytes);
+// Clears words of device memory with a kernel (a captured graph may hold it).
+trevr_status zero_words(hipStream_t st, void* p, size_t words);
 size_t scratch_fixed_bytes(int64_t n);
 // Every call that writes a scratch buffer takes a new epoch for it; a
 // state recorded at epoch e is still in the buffer iff no call (on any

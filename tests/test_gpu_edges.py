@@ -1,12 +1,15 @@
 """Sizes at the edges of the launches' tiles and scans, against the oracle:
 one bucket, a few, and trees whose node and bucket counts lie on either side of
-a workgroup's share.  Tolerance: J within 1e-4 of the oracle (FP32 optical
-depths, floor 1e-12 of the band's largest J), work counters equal."""
+a workgroup's share; trees as tests/test_gpu_parity.py compares them (topology
+equal, FP64 moments to 1e-12, FP32 tables to 2e-6).  Tolerance: J within 1e-4
+of the oracle (FP32 optical depths, floor 1e-12 of the band's largest J), work
+counters equal."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2310_15235_amd import scenes
+from tests.test_gpu_parity import compare_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -34,7 +37,7 @@ def _check_J(sc, act, order_scene=False):
     torch.cuda.synchronize()
 
 
-# 4 nodes per thread of 256 in the bucket list (1024 nodes: about 2600 elements
+# one node per thread of 256 in the bucket list (256 nodes: about 650 elements
 # at 8 per leaf), 16 words per thread of 1024 in the offset scans
 @pytest.mark.parametrize("frac", [1.0, 0.05])
 @pytest.mark.parametrize("n", [1, 8, 9, 65, 700, 2590, 2700, 5300])
@@ -54,3 +57,48 @@ def test_scene_order(n):
 def test_offsets_past_one_scan_chunk():
     sc = scenes.uniform_scene(n=17000, seed=3, n_src=40, bands=(1.0,), nside=1, leaf_size=1)
     _check_J(sc, sc.active)
+
+
+# the LDS sort's last and the radix passes' first size, a tile's edges, the
+# switch of the tile size, one subtree's elements
+@pytest.mark.parametrize("n,leaf", [(1, 8), (8, 8), (9, 8), (64, 1), (512, 8), (513, 3), (4095, 8),
+                                    (4096, 1), (4097, 8), (5120, 12), (5121, 8), (16385, 8),
+                                    (524288, 8), (524289, 8)])
+def test_tree_sizes(n, leaf):
+    compare_tree(scenes.uniform_scene(n=n, seed=n + leaf, n_src=max(1, n // 16), bands=(1.0, 2.0, 5.0),
+                                     nside=1, leaf_size=leaf))
+
+
+# crowded keys: elements within 2^-9 .. 2^-16 of the box (32 bits of the key
+# tell few or none of them apart, so the full sort runs), one place for all, a
+# deep chain (each half of the elements eight times closer to a corner), equal
+# places in runs longer than a bucket
+# (the order and the topology, all integers: where boxes are 2^-16 of the
+# root's, the log of a transmission near 1 over such a chord has lost its digits
+# in the oracle as here, so these trees' averages are no check of the build)
+@pytest.mark.parametrize("kind", ["cluster9", "cluster13", "cluster16", "one", "chain", "runs"])
+@pytest.mark.parametrize("n", [700, 6000])
+def test_tree_crowded(kind, n):
+    sc = scenes.uniform_scene(n=n, seed=4, n_src=30, bands=(1.0,), nside=1)
+    pos = sc.positions().astype(np.float64)
+    if kind.startswith("cluster"):
+        pos[2:] = 0.3 + (pos[2:] - 0.5) * 2.0 ** -int(kind[7:])
+    elif kind == "one":
+        pos[:] = pos[0]
+    elif kind == "chain":
+        pos *= 8.0 ** -np.minimum(np.arange(n) % 7, 6)[:, None]
+    else:
+        pos = pos[np.arange(n) // 40 * 40]
+    x, y, z = (np.ascontiguousarray(pos[:, a], np.float32) for a in range(3))
+    from paper_2310_15235_amd import api
+    for box in (sc.box, None):
+        moved = sc.with_(x=x, y=y, z=z, box=box)
+        T = api.Tree.from_scene(moved)
+        g = T.export()
+        T.check()
+        O = oracle.OracleTree(moved)
+        o = O.nodes()
+        assert np.array_equal(g["perm"], O.perm()[0])
+        for k in ("first", "count", "lown", "split", "child0", "child1", "next"):
+            assert np.array_equal(g[k], o[k]), k
+        T.close()
