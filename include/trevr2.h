@@ -270,13 +270,24 @@ trevr_status trevr_compute_J_backward(trevr_tree* t, const uint8_t* active, cons
  *                     does not fit is found again by a range query (0: every
  *                     set), and its list is in traversal order instead of
  *                     slot order.
+ *   TREVR_TUNE_ADJOINT  1: compute_J also asks for the scratch that its
+ *                     adjoint needs (TREVR_E_CAPACITY when short), so that the
+ *                     buffer need not grow, and the forward's state be lost,
+ *                     between the two (default 0).  Setting it raises
+ *                     trevr_scratch_needed to an estimate for both calls
+ *                     (left as it is where that would pass 16 GiB).
  * Returns TREVR_E_INVALID for an unknown key or a value out of range.
  */
-enum { TREVR_TUNE_STACK = 0, TREVR_TUNE_CUT = 1, TREVR_TUNE_STAGE = 2 };
+enum {
+  TREVR_TUNE_STACK = 0,
+  TREVR_TUNE_CUT = 1,
+  TREVR_TUNE_STAGE = 2,
+  TREVR_TUNE_ADJOINT = 3
+};
 trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value);
 
 /* Scratch bytes the last compute_J or compute_J_backward on this tree needed
- * (0 before any). */
+ * (0 before any, or TREVR_TUNE_ADJOINT's estimate). */
 trevr_status trevr_scratch_needed(const trevr_tree* t, size_t* bytes);
 
 /* Counters of the last compute_J (synchronises the tree's stream). */

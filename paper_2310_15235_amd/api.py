@@ -34,7 +34,7 @@ EXPORTED = ("trevr_workspace_bytes", "trevr_build_tree", "trevr_compute_J",
             "trevr_compute_J_noalloc", "trevr_forest_profile_enable",
             "trevr_forest_profile_read", "trevr_forest_job_log")
 NOALLOC_SCRATCH_BYTES = 64 << 20   # the fixed device array of trevr_compute_J_noalloc
-TUNE_STACK, TUNE_CUT, TUNE_STAGE = 0, 1, 2
+TUNE_STACK, TUNE_CUT, TUNE_STAGE, TUNE_ADJOINT = 0, 1, 2, 3
 CONFIGS = 8          # launch configurations of the forest autotuner
 PROF_NAMES = ("setup", "walk", "reduce", "near", "adj_reduce", "adj_near", "adj_tree", "pp_src",
               "adj_pp_src")
@@ -268,6 +268,20 @@ class Tree:
     @property
     def scratch(self):
         return self._scratch
+
+    def reserve_adjoint(self):
+        """Room for compute_J and its adjoint in one scratch from the start: the
+        calls then find their state again instead of growing the buffer (and
+        redoing the bucket setup, then the forward) on the way."""
+        torch = _torch()
+        self.tune(TUNE_ADJOINT, 1)
+        need = ctypes.c_size_t()
+        _check(lib().trevr_scratch_needed(self.handle, ctypes.byref(need)), "trevr_scratch_needed")
+        if need.value > self._scratch.numel():
+            try:
+                self._scratch = torch.empty(need.value, dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:
+                pass   # an estimate: the calls ask for what they need
 
     def tune(self, key: int, value: int):
         _check(lib().trevr_tree_tune(self.handle, int(key), int(value)), "trevr_tree_tune")
@@ -608,6 +622,8 @@ class TrevrJ:
                 def forward(ctx, x, y, z, m, rho, kappa, lum, active, bg, opts):
                     T = Tree(x.detach(), y.detach(), z.detach(), m.detach(), rho.detach(),
                              kappa.detach(), lum.detach(), **opts)
+                    if any(ctx.needs_input_grad):
+                        T.reserve_adjoint()
                     J = T.compute_J(active, bg)
                     ctx.tree, ctx.active, ctx.bg = T, active, bg
                     ctx.dtypes = (rho.dtype, kappa.dtype, lum.dtype)

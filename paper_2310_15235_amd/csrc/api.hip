@@ -155,7 +155,7 @@ trevr_status trevr_workspace_bytes(const trevr_params* p, int64_t n, size_t* tre
                                    size_t* scratch_bytes) {
   trevr_status rc = check_params(p, n);
   if (rc != TREVR_OK) return rc;
-  const DirTables d = make_dir_tables(p->nside);
+  const DirTables& d = dir_tables(p->nside);
   if (tree_bytes) *tree_bytes = layout_tree(*p, n, d.nclass, nullptr, nullptr);
   if (scratch_bytes) *scratch_bytes = scratch_fixed_bytes(n) + sizeof(uint32_t) * 64 * (size_t)n + 512;
   return TREVR_OK;
@@ -176,9 +176,9 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   T->p = *p;
   T->n = n;
   T->B = p->n_bands;
-  T->dirs = make_dir_tables(p->nside);
-  T->nray = T->dirs.nray;
-  T->nclass = T->dirs.nclass;
+  T->dirs = &dir_tables(p->nside);
+  T->nray = T->dirs->nray;
+  T->nclass = T->dirs->nclass;
   T->stream = (hipStream_t)stream;
   T->ws = tree_ws;
   T->ws_bytes = tree_ws_bytes;
@@ -189,6 +189,7 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   T->stack_large = false;
   T->cut_default = kCutCap;
   T->stage_limit = (uint32_t)kStageCap;
+  T->adjoint_room = false;
   const size_t need = layout_tree(*p, n, T->nclass, nullptr, nullptr);
   if (tree_ws_bytes < need) {
     delete T;
@@ -223,7 +224,7 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
     std::lock_guard<std::mutex> g(g_reg_mu);
     g_live.insert(T);
   }
-  rc = hip_check(hipHostMalloc((void**)&T->host_u32, kHostWords * sizeof(uint32_t)), "hipHostMalloc");
+  rc = pinned_take(&T->host_u32);
   if (rc == TREVR_OK) rc = build_tree_impl(T, x, y, z, m, rho, kappa, lum);
   if (rc != TREVR_OK) {
     trevr_tree_destroy(T);
@@ -328,6 +329,12 @@ trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value) {
         return set_error(TREVR_E_INVALID, "staging words must be in [0, 4096]");
       t->stage_limit = (uint32_t)value;
       return TREVR_OK;
+    case TREVR_TUNE_ADJOINT:
+      if (value != 0 && value != 1)
+        return set_error(TREVR_E_INVALID, "room for the adjoint is 0 or 1");
+      t->adjoint_room = value != 0;
+      if (t->adjoint_room) t->scratch_needed = std::max(t->scratch_needed, adjoint_scratch_guess(t));
+      return TREVR_OK;
     default:
       return set_error(TREVR_E_INVALID, "unknown tuning key");
   }
@@ -390,7 +397,7 @@ trevr_status trevr_tree_destroy(trevr_tree* t) {
   t->magic = 0;
   (void)hipStreamSynchronize(t->stream);
   prof_destroy(&t->prof);
-  if (t->host_u32) (void)hipHostFree(t->host_u32);
+  if (t->host_u32) pinned_give(t->host_u32);
   delete t;
   return TREVR_OK;
 }
@@ -477,7 +484,7 @@ trevr_status trevr_tree_export(trevr_tree* t, int64_t* perm, int64_t* ints, doub
   }
   if (Lb) ok = ok && dl(Lb, t->buf.Lb, sizeof(double) * nn * B);
   if (alpha) ok = ok && dl(alpha, t->buf.alpha32, sizeof(float) * nn * C * B);
-  if (ray_class) std::memcpy(ray_class, t->dirs.ray_class.data(), sizeof(int32_t) * t->nray);
+  if (ray_class) std::memcpy(ray_class, t->dirs->ray_class.data(), sizeof(int32_t) * t->nray);
   if (kmass) ok = ok && dl(kmass, t->buf.kmass, sizeof(double) * nn);
   if ((csrc_d || csrc_a) && !t->buf.csrc_d)
     return set_error(TREVR_E_STATE, "the tree has no complex source tables");

@@ -1932,7 +1932,8 @@ trevr_status compute_J_impl(trevr_tree* T, const uint8_t* active, const float* b
   S.tpp = dyn.take<float>(tot[TOT_TPP]);
   S.ptau = dyn.take<float>(tot[TOT_PTAU]);
   take_kept(T, S, dyn, nb);
-  const size_t need = S.fixed + dyn.off + 256;
+  const size_t need =
+      T->adjoint_room ? carve_adjoint(T, S, dyn, tot).end : S.fixed + dyn.off + 256;
   T->scratch_needed = need;
   if (scratch_bytes < need) return set_error(TREVR_E_CAPACITY, "scratch too small for the p-p lists");
   if ((rc = near_fill(tree_launch(T), S)) != TREVR_OK) return rc;

@@ -1435,6 +1435,48 @@ trevr_status bwd_tree_pass(const Launch& L, const Scratch& S, const Grad& G,
   return TREVR_OK;
 }
 
+AdjointPart carve_adjoint(const trevr_tree* T, const Scratch& S, Carve dyn,
+                          const uint64_t tot[TOT_N]) {
+  AdjointPart p;
+  p.gtpp = dyn.take<float>(tot[TOT_TPP]);
+  p.jraw = dyn.take<double>(tot[TOT_JRAW]);
+  p.gbeg = (S.fixed + dyn.off + 255) & ~(size_t)255;
+  Carve gcv(dyn.base ? dyn.base - S.fixed + p.gbeg : nullptr);
+  const GradDims dims{T->B * T->n, T->n, T->num_nodes, T->num_nodes * T->B,
+                      T->num_nodes * T->nclass * T->B, T->num_leaves};
+  p.G = carve_grad(gcv, dims);
+  p.gbytes = (gcv.off + 255) & ~(size_t)255;
+  p.end = p.gbeg + p.gbytes + 256;
+  return p;
+}
+
+// The sizes a call needs are known after its bucket setup only; a scratch
+// that turns out too small costs that setup again, and one that must grow
+// between the forward and the adjoint costs the forward's whole state.  64 p-p
+// entries and 32 near sources per element cover the usual media; every
+// element is taken as a receiver.  Not more than kGuessMost: a larger one is
+// left to the calls' own sizes.
+size_t adjoint_scratch_guess(const trevr_tree* T) {
+  constexpr double kGuessMost = 16.0 * (1 << 30);
+  const double n = (double)T->n, B = (double)T->B;
+  const double col = n * T->nray * B;
+  if (2.0 * 4.0 * col + 8.0 * n * T->nclass * B > kGuessMost) return 0;
+  const Scratch S0 = carve_scratch(nullptr, T->num_leaves, default_cut_entries(T->num_leaves));
+  Scratch S = S0;
+  uint64_t tot[TOT_N] = {};
+  tot[TOT_NEAR] = (uint64_t)(64.0 * n);
+  tot[TOT_TPP] = (uint64_t)col;
+  tot[TOT_PTAU] = (uint64_t)(32.0 * n * B);
+  tot[TOT_JRAW] = (uint64_t)(n * B);
+  Carve dyn(nullptr);
+  dyn.take<uint32_t>(tot[TOT_NEAR]);
+  dyn.take<float>(tot[TOT_TPP]);
+  dyn.take<float>(tot[TOT_PTAU]);
+  take_kept(T, S, dyn, (uint32_t)T->num_leaves);
+  const size_t need = carve_adjoint(T, S, dyn, tot).end;
+  return (double)need <= kGuessMost ? need : 0;
+}
+
 // Scratch of the backward: the forward's layout (fixed part, p-p lists,
 // p-p columns, pair depths, kept depths), then the p-p column adjoints, the
 // raw J per receiver and the gradient accumulators.  When the scratch still
@@ -1487,15 +1529,11 @@ trevr_status compute_J_backward_impl(trevr_tree* T, const uint8_t* active, const
   a.gJ = gJ;
   a.kept_tau = use_kept ? S.kept_tau : nullptr;
   a.kept_tex = use_kept ? S.kept_tex : nullptr;
-  a.gtpp = dyn.take<float>(tot[TOT_TPP]);
-  a.jraw = dyn.take<double>(tot[TOT_JRAW]);
-  const size_t gbeg = (S.fixed + dyn.off + 255) & ~(size_t)255;
-  Carve gcv((char*)scratch + gbeg);
-  GradDims dims{T->B * T->n, T->n, T->num_nodes, T->num_nodes * T->B,
-                T->num_nodes * T->nclass * T->B, T->num_leaves};
-  a.G = carve_grad(gcv, dims);
-  const size_t gbytes = (gcv.off + 255) & ~(size_t)255;
-  const size_t need = gbeg + gbytes + 256;
+  const AdjointPart part = carve_adjoint(T, S, dyn, tot);
+  a.gtpp = part.gtpp;
+  a.jraw = part.jraw;
+  a.G = part.G;
+  const size_t gbeg = part.gbeg, gbytes = part.gbytes, need = part.end;
   T->scratch_needed = need;
   if (scratch_bytes < need) return set_error(TREVR_E_CAPACITY, "scratch too small for the adjoint");
   const uint64_t epoch = scratch_mark(scratch);

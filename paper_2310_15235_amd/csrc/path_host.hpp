@@ -141,6 +141,18 @@ struct GradDims {
 };
 
 Grad carve_grad(Carve& cv, const GradDims& d);
+// The adjoint's part of a lone tree's scratch, behind the forward's dynamic
+// part in dyn: the p-p column adjoints, the raw J per receiver and (zeroed at
+// the start, gbytes from byte gbeg) the gradient accumulators; end is the
+// scratch it all takes.
+struct AdjointPart {
+  float* gtpp;
+  double* jraw;
+  Grad G;
+  size_t gbeg, gbytes, end;
+};
+AdjointPart carve_adjoint(const trevr_tree* T, const Scratch& S, Carve dyn,
+                          const uint64_t tot[TOT_N]);
 // The adjoint's per-bucket kernels (p-p sources, far field, p-p columns) for
 // the items of band count B; prof (nullable) records their times.
 trevr_status bwd_items(const Launch& L, int B, const Scratch& S, const BwdArgs& a,

@@ -27,6 +27,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <mutex>
 
 #include "trevr_internal.hpp"
 
@@ -1098,6 +1100,69 @@ DirTables make_dir_tables(int nside) {
   return t;
 }
 
+namespace {
+constexpr int kSides = 5;   // N_side 1, 2, 4, 8, 16
+static_assert((1 << (kSides - 1)) == kMaxNside, "one set of tables per N_side");
+std::mutex g_dir_mu;
+std::unique_ptr<DirTables> g_dirs[kSides];
+double* g_dir_pinned[kSides] = {};
+std::mutex g_pin_mu;
+std::vector<uint32_t*> g_pins;
+constexpr size_t kPinsKept = 16;   // 2 KiB each
+int side_index(int nside) {
+  int k = 0;
+  while ((1 << k) < nside && k < kSides - 1) ++k;
+  return k;
+}
+}  // namespace
+
+const DirTables& dir_tables(int nside) {
+  std::lock_guard<std::mutex> g(g_dir_mu);
+  std::unique_ptr<DirTables>& d = g_dirs[side_index(nside)];
+  if (!d) d.reset(new DirTables(make_dir_tables(nside)));
+  return *d;
+}
+
+const double* dir_block_pinned(int nside) {
+  const DirTables& d = dir_tables(nside);
+  std::lock_guard<std::mutex> g(g_dir_mu);
+  double*& p = g_dir_pinned[side_index(nside)];
+  if (!p) {
+    void* q = nullptr;
+    if (hipHostMalloc(&q, d.block.size() * sizeof(double), hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return d.block.data();
+    }
+    p = (double*)q;
+    std::copy(d.block.begin(), d.block.end(), p);
+  }
+  return p;
+}
+
+trevr_status pinned_take(uint32_t** out) {
+  {
+    std::lock_guard<std::mutex> g(g_pin_mu);
+    if (!g_pins.empty()) {
+      *out = g_pins.back();
+      g_pins.pop_back();
+      return TREVR_OK;
+    }
+  }
+  return hip_check(hipHostMalloc((void**)out, kHostWords * sizeof(uint32_t), hipHostMallocPortable),
+                   "hipHostMalloc");
+}
+
+void pinned_give(uint32_t* block) {
+  {
+    std::lock_guard<std::mutex> g(g_pin_mu);
+    if (g_pins.size() < kPinsKept) {
+      g_pins.push_back(block);
+      return;
+    }
+  }
+  (void)hipHostFree(block);
+}
+
 size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, TreeBufs* o) {
   Carve cv(base);
   TreeBufs t{};
@@ -1219,11 +1284,15 @@ trevr_status build_tree_impl(trevr_tree* T, const float* x, const float* y, cons
   hipStream_t st = T->stream;
   trevr_status rc;
 
-  // the device's DevTree (k_levels completes it) and the direction tables
-  if ((rc = hip_check(hipMemcpyAsync(tb.dev, &T->dev, sizeof(DevTree), hipMemcpyHostToDevice, st),
+  // the device's DevTree (k_levels completes it) and the direction tables,
+  // both from pinned memory
+  static_assert(sizeof(DevTree) <= kHostWords * sizeof(uint32_t) / 2, "fits the second half");
+  uint32_t* up = T->host_u32 + kHostWords / 2;
+  std::memcpy(up, &T->dev, sizeof(DevTree));
+  if ((rc = hip_check(hipMemcpyAsync(tb.dev, up, sizeof(DevTree), hipMemcpyHostToDevice, st),
                       "copy tree table")) != TREVR_OK) return rc;
-  if ((rc = hip_check(hipMemcpyAsync(tb.ray_n, T->dirs.block.data(),
-                                     sizeof(double) * T->dirs.block.size(),
+  if ((rc = hip_check(hipMemcpyAsync(tb.ray_n, dir_block_pinned(T->p.nside),
+                                     sizeof(double) * T->dirs->block.size(),
                                      hipMemcpyHostToDevice, st), "copy direction tables")) !=
       TREVR_OK)
     return rc;

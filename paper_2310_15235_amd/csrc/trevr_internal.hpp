@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <string>
 #include <utility>
@@ -121,6 +122,19 @@ inline size_t dir_block(int nray, int nclass) {
   return 3 * (size_t)nray + (size_t)kMaxLevels * nclass * 3 + (size_t)nray;
 }
 DirTables make_dir_tables(int nside);
+// The tables of an N_side, made on first use and kept (one set per N_side up
+// to kMaxNside; constants of the method).
+const DirTables& dir_tables(int nside);
+// Their block in pinned memory, for uploads that do not wait (made on first
+// use; the pageable block where pinned memory cannot be had).
+const double* dir_block_pinned(int nside);
+
+// Pinned blocks of kHostWords words for the readbacks of trees: a few are
+// kept when trees go, since a program that builds a tree per step would
+// otherwise allocate and free pinned memory in each (any thread; a block is
+// given back after its tree's stream is synchronised).
+trevr_status pinned_take(uint32_t** out);
+void pinned_give(uint32_t* block);
 
 size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, TreeBufs* out);
 
@@ -166,7 +180,7 @@ struct trevr_tree {
   size_t ws_bytes;
   trevr::TreeBufs buf;
   trevr::DevTree dev;
-  trevr::DirTables dirs;
+  const trevr::DirTables* dirs;             // of its N_side (kept by the library)
   std::vector<std::pair<uint32_t, uint32_t>> levels;  // BFS index ranges per depth
   size_t scratch_needed;
   bool counters_valid;
@@ -175,6 +189,7 @@ struct trevr_tree {
   bool stack_large;                         // traversals need the large LDS stack
   uint32_t cut_default;                     // cut-list entries per bucket to try first
   uint32_t stage_limit;                     // most staging words per bucket for p-p sets
+  bool adjoint_room;                        // compute_J asks for the adjoint's scratch too
   trevr::Prof prof;                         // kernel timing (trevr_profile_enable)
 };
 
@@ -193,6 +208,8 @@ trevr_status compute_J_backward_impl(trevr_tree* t, const uint8_t* active, const
 // Clears words of device memory with a kernel (a captured graph may hold it).
 trevr_status zero_words(hipStream_t st, void* p, size_t words);
 size_t scratch_fixed_bytes(int64_t n);
+// Scratch that a compute_J and its adjoint are likely to need (adjoint_room).
+size_t adjoint_scratch_guess(const trevr_tree* t);
 // Every call that writes a scratch buffer takes a new epoch for it; a
 // state recorded at epoch e is still in the buffer iff no call (on any
 // tree) has written it since.

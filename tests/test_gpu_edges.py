@@ -102,3 +102,35 @@ def test_tree_crowded(kind, n):
         for k in ("first", "count", "lown", "split", "child0", "child1", "next"):
             assert np.array_equal(g[k], o[k]), k
         T.close()
+
+
+# the adjoint's scratch asked for by the forward: the buffer keeps its size and
+# the gradients equal those of the growing one (FP32 rounding of atomic sums:
+# 1e-5 of a value, 1e-6 of the array's largest).  One scene whose near sets the
+# estimate covers, one whose it does not.
+@pytest.mark.parametrize("n,nside", [(3000, 1), (1200, 4)])
+def test_adjoint_room(n, nside):
+    import torch
+    from paper_2310_15235_amd import api
+    sc = scenes.lognormal_scene(n=n, seed=2, grid=16, bands=(1.0, 10.0), nside=nside)
+    gJ = torch.as_tensor(np.random.default_rng(1).normal(size=(2, n)), device="cuda")
+    plain = api.compute_J_backward(sc, gJ.cpu().numpy())
+    for reserve in (False, True):
+        T = api.Tree.from_scene(sc)
+        if reserve:
+            T.reserve_adjoint()
+        else:
+            T.tune(api.TUNE_ADJOINT, 1)
+        T.compute_J()
+        size = T.scratch.numel()
+        got = T.compute_J_backward(gJ)
+        T.check()
+        assert T.scratch.numel() == size
+        for a, b in zip(got, plain):
+            a = a.cpu().numpy()
+            assert np.all(np.abs(a - b) <= 1e-5 * np.abs(b) + 1e-6 * np.abs(b).max())
+        T.close()
+    T = api.Tree.from_scene(sc)
+    with pytest.raises(api.TrevrError):
+        T.tune(api.TUNE_ADJOINT, 2)
+    T.close()
