@@ -215,7 +215,7 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   D.h = b.h; D.lbol = b.lbol; D.kappa = b.kappa; D.lum = b.lum; D.perm = b.perm;
   D.nk = b.nk; D.nlink = b.nlink; D.next = b.next; D.cen = b.cen; D.Lb = b.Lb;
   D.alpha = b.alpha32; D.ray_n = b.ray_n; D.ray_class = b.ray_class;
-  D.ray_anti = b.ray_anti; D.csrc_d = b.csrc_d; D.csrc_a = b.csrc_a;
+  D.ray_anti = b.ray_anti; D.rcand = b.rcand; D.csrc_d = b.csrc_d; D.csrc_a = b.csrc_a;
   D.err = b.err; D.counters = b.counters;
   D.b_pre = b.b_pre; D.b_lown = b.b_lown; D.b_split = b.b_split;
   D.alpha64 = b.alpha64; D.geom = b.geom; D.levels = b.levels;

@@ -882,65 +882,138 @@ __device__ inline uint32_t block_compact(bool pred, uint32_t* wcnt, uint32_t* to
   return base + (uint32_t)mbcnt(m);
 }
 
-// Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
-// their reciprocals and an FP32 copy (conservative candidate filter).
-// The rays that can meet a p-p element from a receiver (d = the element's
-// offset from the receiver, dd = |d|^2, h2 = its size squared): a ray meets
-// it (ahead, b < h) only if its direction lies within asin(h/|d|) of d, so
-// its z (cos of the polar angle) lies within the z-range of that cone.  The
-// HEALPix ring order lists the rays by decreasing z, ring by ring (ring i of
-// 4N - 1 at z = 1 - i^2/(3N^2) in the north cap, 4/3 - 2i/(3N) in the belt),
-// so those rays are one index range [*ka, *kb): the rings inside the cone's
-// z-range, widened by 1e-4 in sin and z and 1e-3 of a ring for FP32
-// rounding.  The receiver inside the element (h near |d|): every ray.
-__device__ inline float ring_of_z(int N, float z) {
-  if (z > 2.0f / 3.0f) return (float)N * cull_sqrt(3.0f * fmaxf(1.0f - z, 0.0f));
-  if (z < -2.0f / 3.0f) return 4.0f * N - (float)N * cull_sqrt(3.0f * fmaxf(1.0f + z, 0.0f));
-  return 2.0f * N - 1.5f * N * z;
-}
-__device__ inline int ring_start(int N, int i) {
-  if (i <= N) return 2 * i * (i - 1);
-  if (i <= 3 * N) return 2 * N * (N - 1) + 4 * N * (i - N);
-  const int ii = 4 * N - i + 1;   // rings from i to the south pole: ii
-  return 12 * N * N - 2 * ii * (ii - 1);
-}
-__device__ inline void ray_ring_range(int N, double d0, double d1, double d2, double dd, double h2,
-                                      int* ka, int* kb) {
-  const float ddf = (float)dd;
-  const float s2 = (float)h2 / ddf;
-  if (!(s2 < 0.99f)) {
-    *ka = 0;
-    *kb = 12 * N * N;
-    return;
+// The rays that can meet something seen in direction d within an angle of
+// asin(sinr): one 64-bit mask per group of 64 rays in a row of the tree's
+// candidate table (k_init fills it), for the bin of d on the octahedral map
+// and the next larger of kCandSin steps of the sine.  A mask holds every ray
+// within the bin's and the step's angle, 0.02 rad to spare, so it misses
+// none; the tests of single rays run on its few set bits.  Where the kernels
+// tested every ray (far field) or the rings of the z-range (p-p columns),
+// most of their instructions went into rays that could not meet the cell: an
+// absorbing cell meets half a ray of 48.
+__device__ inline uint32_t cand_bin(float x, float y, float z) {
+  const float inv = __builtin_amdgcn_rcpf(fabsf(x) + fabsf(y) + fabsf(z));
+  float u = x * inv, v = y * inv;
+  if (z < 0.0f) {   // the lower half folds outward
+    const float uu = copysignf(1.0f - fabsf(v), u), vv = copysignf(1.0f - fabsf(u), v);
+    u = uu;
+    v = vv;
   }
-  const float z = (float)d2 * rsqrtf(ddf);
-  const float sa = fminf(cull_sqrt(s2) * (1.0f + 1e-4f) + 1e-4f, 1.0f);
-  const float ca = cull_sqrt(fmaxf(1.0f - sa * sa, 0.0f));
-  const float st = cull_sqrt(fmaxf(1.0f - z * z, 0.0f));
-  const float zhi = (z >= ca) ? 1.0f : fminf(z * ca + st * sa + 1e-4f, 1.0f);
-  const float zlo = (-z >= ca) ? -1.0f : fmaxf(z * ca - st * sa - 1e-4f, -1.0f);
-  const int i0 = max(1, (int)ceilf(ring_of_z(N, zhi) - 1e-3f));
-  const int i1 = min(4 * N - 1, (int)floorf(ring_of_z(N, zlo) + 1e-3f));
-  if (i0 > i1) {
-    *ka = *kb = 0;
-    return;
-  }
-  *ka = ring_start(N, i0);
-  *kb = ring_start(N, i1 + 1);
+  const int i = min(kCandSide - 1, max(0, (int)((u + 1.0f) * (0.5f * kCandSide))));
+  const int j = min(kCandSide - 1, max(0, (int)((v + 1.0f) * (0.5f * kCandSide))));
+  return (uint32_t)(j * kCandSide + i);
+}
+// Row of d != 0, sinr in [0, 1) (a relative 1e-4 covers its rounding).
+__device__ inline const uint64_t* cand_row(const DevTree& T, float x, float y, float z,
+                                           float sinr) {
+  const int k = min(kCandSin - 1, (int)(sinr * (kCandSin * 1.0001f)));
+  return T.rcand + ((size_t)k * (kCandSide * kCandSide) + cand_bin(x, y, z)) *
+                       (uint32_t)((T.nray + 63) >> 6);
 }
 
-// Rays per group of the p-p column kernels.  Their pair loop computes each
-// (p-p element, receiver) pair's ring range and loads its element once per
+// A value of lane L (the same in every lane) for the whole wavefront.
+__device__ inline float lane_f32(float v, int L) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
+}
+__device__ inline double lane_f64(double v, int L) {
+  const long long x = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, L);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), L);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sum over the wavefront, the same in every lane: DPP moves within rows of 16
+// lanes, then the four rows (no LDS round trips).  Call with every lane active.
+__device__ inline float wave_sum_f32(float v) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v += dpp_mov(v, k);
+  return (lane_f32(v, 0) + lane_f32(v, 16)) + (lane_f32(v, 32) + lane_f32(v, 48));
+}
+
+// The rays of a p-p column group (GN masks of 64) that a lane's (element,
+// receiver) pair tests.
+template <int GN> struct PairRays {
+  uint64_t m[GN];
+  // Those of the candidate table for the element's offset d and angular size
+  // (s2 = h^2 / |d|^2), every one when the receiver lies inside the element (h
+  // near |d|); the directed ray kdg always; none for a lane without a pair.
+  __device__ void find(const DevTree& T, bool pair, float d0, float d1, float d2, float s2, int k0,
+                       int kn, int kdg) {
+    const uint64_t* row = pair && s2 < 0.99f ? cand_row(T, d0, d1, d2, cull_sqrt(s2)) + k0 / 64
+                                             : nullptr;
+#pragma unroll
+    for (int g = 0; g < GN; ++g) {
+      const int left = kn - 64 * g;
+      uint64_t v = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
+      if (row && left > 0) v &= row[g];
+      if (kdg >= 64 * g && kdg < 64 * g + 64) v |= 1ull << (kdg - 64 * g);
+      m[g] = pair ? v : 0ull;
+    }
+  }
+  __device__ int count() const {
+    int c = 0;
+#pragma unroll
+    for (int g = 0; g < GN; ++g) c += __popcll(m[g]);
+    return c;
+  }
+  __device__ bool any() const {
+    uint64_t v = 0ull;
+#pragma unroll
+    for (int g = 0; g < GN; ++g) v |= m[g];
+    return ballot64(v != 0ull) != 0ull;
+  }
+  // The lowest ray left (-1: none), removed.
+  __device__ int pop() {
+    int k = -1;
+#pragma unroll
+    for (int g = GN - 1; g >= 0; --g)
+      if (m[g]) k = 64 * g + __ffsll((long long)m[g]) - 1;
+#pragma unroll
+    for (int g = 0; g < GN; ++g)
+      if (k >= 64 * g && k < 64 * g + 64) m[g] &= m[g] - 1ull;
+    return k;
+  }
+  // Sets aside the pairs with more rays than the limit that makes the step
+  // cheapest: a step of single rays costs the wavefront about as much as a
+  // pair set aside and each 64 of its rays (both some 40 to 50 instructions).
+  // Returns the lanes set aside; theirs are no longer in m.
+  __device__ uint64_t take_wide() {
+    const int c = count();
+    int most = 0, cost = 1 << 30;
+#pragma unroll
+    for (int lim = 2; lim <= 16; lim *= 2) {
+      const int w = lim + (1 + GN) * __popcll(ballot64(c > lim));
+      if (w < cost) {
+        cost = w;
+        most = lim;
+      }
+    }
+    const bool wide = c > most;
+    if (wide) {
+#pragma unroll
+      for (int g = 0; g < GN; ++g) m[g] = 0ull;
+    }
+    return ballot64(wide);
+  }
+};
+
+// Rays per group of the p-p column kernels.  Their pair loop finds each
+// (p-p element, receiver) pair's candidate rays and loads its element once per
 // group, so a group holds every ray up to N_side 4 where the LDS sums of a
 // group allow it (up to four bands); the candidate masks stay 64 rays wide.
 template <int NB> struct PpRayGroup {
   static constexpr int value = NB <= 4 ? 192 : 64;
 };
 
+// Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
+// their reciprocals and an FP32 copy (conservative candidate filter).
 struct RayGroup {
   double n[64][3], inv[64][3];
   float nf[64][3];
-  int cls[64];   // direction class (transmission tables)
+  int cls[64];       // direction class (transmission tables)
+  uint64_t all;      // the group's rays
+  uint64_t aimed;    // the directed ray, if it is one of them: not where the
+                     // candidate table has it, so always a candidate
 };
 
 // The directed ray of the bucket centred at c (TREVR_DIRECTED) takes its
@@ -952,6 +1025,10 @@ __device__ inline void load_ray_group(const DevTree& T, const double c[3], int k
     const int k = k0 + t;
     double u[3];
     const int kd = directed_ray(T, c, u);
+    if (t == 0) {
+      G.all = kn >= 64 ? ~0ull : (1ull << kn) - 1ull;
+      G.aimed = kd >= k0 && kd < k0 + kn ? 1ull << (kd - k0) : 0ull;
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const double na = (k == kd) ? u[a] : T.ray_n[3 * k + a];
@@ -1119,46 +1196,64 @@ __device__ inline void sort_window(SrcWindow<CAP, NB, kSfx>& W, uint32_t nsg, bo
   __syncthreads();
 }
 
+// The rays of group g (first ray k0 = 64 g) that can meet an absorbing cell
+// beyond the p-p sphere, as a mask: those of the candidate table that pass the
+// conservative FP32 bounding-sphere test; every ray when the centre may be
+// inside the sphere.
+struct CellSight {
+  float mc[3], thr;   // the cell's middle from the bucket centre, |mc|^2 - R^2 with a margin
+  uint64_t cand;      // rays to test
+  bool every;         // the test does not apply
+};
+__device__ inline CellSight see_cell(const DevTree& T, uint32_t node, const double c[3], int g,
+                                     const RayGroup& G) {
+  CellSight S;
+  double lo[3], hi[3];
+  node_box(T.hdr, T.nk[node], lo, hi);
+  float R2 = 0.0f, D2 = 0.0f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    S.mc[a] = (float)(0.5 * (lo[a] + hi[a]) - c[a]);
+    const float hx = (float)(0.5 * (hi[a] - lo[a]));
+    R2 += hx * hx;
+    D2 += S.mc[a] * S.mc[a];
+  }
+  const float marg = 1e-5f * D2 + 1e-30f;
+  S.every = !(D2 - R2 > marg);
+  S.thr = D2 - R2 - marg;
+  S.cand = S.every ? G.all
+                   : (cand_row(T, S.mc[0], S.mc[1], S.mc[2],
+                               cull_sqrt(R2 * __builtin_amdgcn_rcpf(D2)))[g] & G.all) | G.aimed;
+  return S;
+}
+__device__ inline bool sees(const CellSight& S, const RayGroup& G, int kq) {
+  const float nm = G.nf[kq][0] * S.mc[0] + G.nf[kq][1] * S.mc[1] + G.nf[kq][2] * S.mc[2];
+  return S.every || (nm > 0.0f && nm * nm >= S.thr);
+}
+
 // Every (absorbing cut entry, ray of the group) hit found by the thread
 // holding the entry, with no barriers: threads take the cut entries in
-// turn; for an absorbing one the conservative FP32 bounding-sphere test
-// gives its candidate rays, the exact FP64 ray-box test keeps those that
-// meet the cell beyond the p-p sphere, and the same thread calls
-// on_hit(node, ray, t0, t1, clipped) with t0 = max(t_in, r), clipped =
-// (t_in < r).  Hits of one ray arrive from many threads in no fixed order,
-// so on_hit must update shared state atomically.
+// turn; of an absorbing one's candidate rays (see_cell) the exact FP64
+// ray-box test keeps those that meet the cell beyond the p-p sphere, and the
+// same thread calls on_hit(node, ray, t0, t1, clipped) with t0 = max(t_in, r),
+// clipped = (t_in < r).  Hits of one ray arrive from many threads in no fixed
+// order, so on_hit must update shared state atomically.
 template <class F>
 __device__ inline void for_each_hit_lane(const DevTree& T, const uint2* mycut, uint32_t ncut,
-                                         const double c[3], double r, int kn, const RayGroup& G,
+                                         const double c[3], double r, int g, const RayGroup& G,
                                          F&& on_hit) {
-  const uint64_t all = (kn >= 64) ? ~0ull : ((1ull << kn) - 1ull);
   for (uint32_t e = threadIdx.x; e < ncut; e += kFT) {
     const uint2 ent = mycut[e];
     if (!(ent.y & CUT_ABS)) continue;
     const uint32_t node = ent.x;
+    CellSight S = see_cell(T, node, c, g, G);
+    if (S.cand == 0ull) continue;
     double lo[3], hi[3];
     node_box(T.hdr, T.nk[node], lo, hi);
-    float mc[3], R2 = 0.0f, D2 = 0.0f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      mc[a] = (float)(0.5 * (lo[a] + hi[a]) - c[a]);
-      const float hx = (float)(0.5 * (hi[a] - lo[a]));
-      R2 += hx * hx;
-      D2 += mc[a] * mc[a];
-    }
-    const float marg = 1e-5f * D2 + 1e-30f;
-    uint64_t cand = all;
-    if (D2 - R2 > marg) {
-      const float thr = D2 - R2 - marg;
-      cand = 0ull;
-      for (int kq = 0; kq < kn; ++kq) {
-        const float nm = G.nf[kq][0] * mc[0] + G.nf[kq][1] * mc[1] + G.nf[kq][2] * mc[2];
-        if (nm > 0.0f && nm * nm >= thr) cand |= 1ull << kq;
-      }
-    }
-    while (cand) {
-      const int kq = __ffsll((long long)cand) - 1;
-      cand &= cand - 1ull;
+    while (S.cand) {
+      const int kq = __ffsll((long long)S.cand) - 1;
+      S.cand &= S.cand - 1ull;
+      if (!sees(S, G, kq)) continue;
       double tin, tout;
       if (slab(lo, hi, c, G.n[kq], G.inv[kq], tin, tout) && tout > fmax(tin, r))
         on_hit(node, kq, fmax(tin, r), tout, tin < r);
@@ -1168,19 +1263,18 @@ __device__ inline void for_each_hit_lane(const DevTree& T, const uint2* mycut, u
 
 // The same hits, queued: for light callbacks (the forward's), where lanes
 // with few candidate rays would otherwise wait for the busiest.  No workgroup
-// barriers: threads take the cut entries in turn; for each ray of the group
-// the conservative FP32 bounding-sphere test marks the thread's entry as a
-// candidate, candidates are queued per wavefront in Q (kHitQ words) and run
-// 64 at a time, one per lane: the exact FP64 ray-box test keeps those that
-// meet the cell beyond the p-p sphere and that lane calls on_hit(node, ray,
-// t0, t1, clipped) with t0 = max(t_in, r), clipped = (t_in < r).  Hits of
-// one ray arrive from many lanes in no fixed order, so on_hit must update
-// shared state atomically.
+// barriers: threads take the cut entries in turn; each step every lane tests
+// the next of its entry's candidate rays, those that pass are queued per
+// wavefront in Q (kHitQ words) and run 64 at a time, one per lane: the exact
+// FP64 ray-box test keeps those that meet the cell beyond the p-p sphere and
+// that lane calls on_hit(node, ray, t0, t1, clipped) with t0 = max(t_in, r),
+// clipped = (t_in < r).  Hits of one ray arrive from many lanes in no fixed
+// order, so on_hit must update shared state atomically.
 constexpr uint32_t kHitQ = 128;   // one batch of 64 plus one step's 64
 
 template <class F>
 __device__ inline void for_each_hit_queued(const DevTree& T, const uint2* mycut, uint32_t ncut,
-                                           const double c[3], double r, int kn, const RayGroup& G,
+                                           const double c[3], double r, int g, const RayGroup& G,
                                            uint32_t* Q, F&& on_hit) {
   const int lane = threadIdx.x & 63;
   uint32_t head = 0, tail = 0;   // wave-uniform queue cursors
@@ -1200,34 +1294,15 @@ __device__ inline void for_each_hit_queued(const DevTree& T, const uint2* mycut,
   const uint32_t rounds = (ncut + kFT - 1) / kFT;
   for (uint32_t rd = 0; rd < rounds; ++rd) {
     const uint32_t e = rd * kFT + threadIdx.x;
-    bool live = false, every = false;
-    float mc[3] = {0.0f, 0.0f, 0.0f}, thr = 0.0f;
+    CellSight S{};
     if (e < ncut) {
       const uint2 ent = mycut[e];
-      if (ent.y & CUT_ABS) {
-        live = true;
-        double lo[3], hi[3];
-        node_box(T.hdr, T.nk[ent.x], lo, hi);
-        float R2 = 0.0f, D2 = 0.0f;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          mc[a] = (float)(0.5 * (lo[a] + hi[a]) - c[a]);
-          const float hx = (float)(0.5 * (hi[a] - lo[a]));
-          R2 += hx * hx;
-          D2 += mc[a] * mc[a];
-        }
-        const float marg = 1e-5f * D2 + 1e-30f;
-        every = !(D2 - R2 > marg);   // the centre may be inside: every ray
-        thr = D2 - R2 - marg;
-      }
+      if (ent.y & CUT_ABS) S = see_cell(T, ent.x, c, g, G);
     }
-    if (ballot64(live) == 0ull) continue;
-    for (int kq = 0; kq < kn; ++kq) {
-      bool cand = false;
-      if (live) {
-        const float nm = G.nf[kq][0] * mc[0] + G.nf[kq][1] * mc[1] + G.nf[kq][2] * mc[2];
-        cand = every || (nm > 0.0f && nm * nm >= thr);
-      }
+    while (ballot64(S.cand != 0ull) != 0ull) {
+      const int kq = S.cand ? __ffsll((long long)S.cand) - 1 : 0;
+      const bool cand = S.cand != 0ull && sees(S, G, kq);
+      S.cand &= S.cand - 1ull;
       const uint64_t m = ballot64(cand);
       if (m == 0ull) continue;
       if (cand) Q[(tail + (uint32_t)mbcnt(m)) & (kHitQ - 1)] = (e << 6) | (uint32_t)kq;

@@ -45,19 +45,73 @@ __device__ inline float ord2f(uint32_t u) {
 __device__ inline bool finite_pos(float v) { return isfinite(v) && v > 0.0f; }
 
 // ------------------------------------------------------------- root cube
-// Zeroes the build's counters; with a box from the caller also writes the
-// header.  One workgroup.
-__global__ void k_init(TreeBufs tb, double bx, double by, double bz, double bL) {
-  const int t = threadIdx.x;
-  if (t < 3) { tb.bbox_u[t] = 0xFFFFFFFFu; tb.bbox_u[3 + t] = 0u; }
-  if (t < 4) tb.err[t] = 0u;
-  if (t < CNT_N) tb.counters[t] = 0ull;
-  if (t < (int)(sizeof(BuildWords) / 4)) reinterpret_cast<uint32_t*>(tb.words)[t] = 0u;
-  if (t == 0) tb.tsum[0] = 0u;
-  if (t == 0 && bL > 0.0) {
-    tb.hdr[0] = bx; tb.hdr[1] = by; tb.hdr[2] = bz; tb.hdr[3] = bL;
-    tb.hdr[4] = ldexp(1.0, kKeyBits) / bL;
+// Direction of a point of the octahedral map (not normalised).
+__device__ inline void octahedral(float u, float v, float d[3]) {
+  d[2] = 1.0f - fabsf(u) - fabsf(v);
+  d[0] = u;
+  d[1] = v;
+  if (d[2] < 0.0f) {
+    d[0] = copysignf(1.0f - fabsf(v), u);
+    d[1] = copysignf(1.0f - fabsf(u), v);
   }
+  const float inv = rsqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+  d[0] *= inv;
+  d[1] *= inv;
+  d[2] *= inv;
+}
+
+// Workgroup 0 zeroes the build's counters and, with a box from the caller,
+// writes the header.  The others fill the table of candidate rays, one
+// wavefront per (bin, group of 64 rays): the bin's angular radius is the
+// farthest of 8 x 8 points of it from its middle, plus what lies between them
+// (half a step's diagonal, 0.0063 of the map, which stretches angles up to
+// threefold), and each step of the sine takes the rays within that angle and
+// its own.
+constexpr float kCandSlack = 0.02f;
+static_assert(kCandSide == 32, "kCandSlack holds for bins of 1/16 of the map's half width");
+__global__ void __launch_bounds__(256) k_init(TreeBufs tb, double bx, double by, double bz,
+                                              double bL, int nray) {
+  const int t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    if (t < 3) { tb.bbox_u[t] = 0xFFFFFFFFu; tb.bbox_u[3 + t] = 0u; }
+    if (t < 4) tb.err[t] = 0u;
+    if (t < CNT_N) tb.counters[t] = 0ull;
+    if (t < (int)(sizeof(BuildWords) / 4)) reinterpret_cast<uint32_t*>(tb.words)[t] = 0u;
+    if (t == 0) tb.tsum[0] = 0u;
+    if (t == 0 && bL > 0.0) {
+      tb.hdr[0] = bx; tb.hdr[1] = by; tb.hdr[2] = bz; tb.hdr[3] = bL;
+      tb.hdr[4] = ldexp(1.0, kKeyBits) / bL;
+    }
+    return;
+  }
+  const int lane = t & 63, groups = (nray + 63) / 64;
+  const int w = (int)(blockIdx.x - 1) * 4 + (t >> 6);
+  const int bin = w / groups, g = w % groups;
+  if (bin >= kCandSide * kCandSide) return;
+  constexpr float kWidth = 2.0f / kCandSide;
+  const float u0 = -1.0f + kWidth * (float)(bin % kCandSide);
+  const float v0 = -1.0f + kWidth * (float)(bin / kCandSide);
+  float mid[3], d[3];
+  octahedral(u0 + 0.5f * kWidth, v0 + 0.5f * kWidth, mid);
+  octahedral(u0 + kWidth * (float)(lane & 7) / 7.0f, v0 + kWidth * (float)(lane >> 3) / 7.0f, d);
+  float rad = acosf(fminf(1.0f, mid[0] * d[0] + mid[1] * d[1] + mid[2] * d[2]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) rad = fmaxf(rad, __shfl_xor(rad, o));
+  const int k = 64 * g + lane;
+  float ang = 4.0f;   // past every limit: no such ray
+  if (k < nray) {
+    const double* n = tb.ray_n + 3 * k;
+    const float dp = mid[0] * (float)n[0] + mid[1] * (float)n[1] + mid[2] * (float)n[2];
+    ang = acosf(fmaxf(-1.0f, fminf(1.0f, dp)));
+  }
+  uint64_t mine = 0ull;
+#pragma unroll
+  for (int q = 0; q < kCandSin; ++q) {
+    const uint64_t m = ballot64(ang <= rad + asinf((float)(q + 1) / kCandSin) + kCandSlack);
+    if (lane == q) mine = m;
+  }
+  if (lane < kCandSin)
+    tb.rcand[((size_t)lane * (kCandSide * kCandSide) + bin) * groups + g] = mine;
 }
 
 __global__ void __launch_bounds__(256) k_bbox(const float* x, const float* y, const float* z,
@@ -1217,6 +1271,7 @@ size_t layout_tree(const trevr_params& p, int64_t n, int nclass, void* base, Tre
   t.geom = t.ray_n ? t.ray_n + 3 * nray : nullptr;
   t.ray_class = t.ray_n ? (int32_t*)(t.geom + (size_t)kMaxLevels * nclass * 3) : nullptr;
   t.ray_anti = t.ray_n ? t.ray_class + nray : nullptr;
+  t.rcand = cv.take<uint64_t>((size_t)kCandSin * kCandSide * kCandSide * ((nray + 63) / 64));
   t.csrc_d = nullptr;
   t.csrc_a = nullptr;
   if (p.flags & TREVR_COMPLEX_SRC) {
@@ -1298,7 +1353,8 @@ trevr_status build_tree_impl(trevr_tree* T, const float* x, const float* y, cons
     return rc;
 
   const double* bx = T->p.box;
-  k_init<<<1, 256, 0, st>>>(tb, bx[0], bx[1], bx[2], bx[3]);
+  const int cand_waves = kCandSide * kCandSide * ((T->nray + 63) / 64);
+  k_init<<<1 + (cand_waves + 3) / 4, 256, 0, st>>>(tb, bx[0], bx[1], bx[2], bx[3], T->nray);
   TREVR_LAUNCH_CHECK("k_init");
   if (!(bx[3] > 0.0)) {
     k_bbox<<<std::min<int64_t>(64, grid_for(n, 256)), 256, 0, st>>>(x, y, z, n, tb.bbox_u);

@@ -15,6 +15,13 @@ constexpr int kKeyBits = 21;           // bits per axis of the Morton key
 constexpr int kMaxLevels = 64;         // prefix lengths 0..63
 constexpr double kPi = 3.14159265358979323846;
 
+// Table of candidate rays by direction (octahedral map, kCandSide^2 bins) and
+// angular size (kCandSin steps of the sine): 1024 bins are 4 degrees across,
+// against 29 and 15 between rays at N_side 2 and 4; 128 KiB per 64 rays, read
+// from the L2.
+constexpr int kCandSide = 32;
+constexpr int kCandSin = 16;
+
 // Sticky device error bits.
 enum : uint32_t {
   ERR_DATA = 1u,         // non-positive or non-finite element data
@@ -70,6 +77,7 @@ struct DevTree {
   const double* ray_n;        // [nray][3]
   const int32_t* ray_class;   // [nray]
   const int32_t* ray_anti;    // [nray] ray of the opposite direction
+  const uint64_t* rcand;      // [kCandSin][kCandSide^2][(nray + 63) / 64] candidate rays
   const double* csrc_d;       // complex source model (TREVR_COMPLEX_SRC): [node][nray]
   const double* csrc_a;       //   lengths and [node][nray][B] absorption of the
                               //   rays from each node's luminosity centre

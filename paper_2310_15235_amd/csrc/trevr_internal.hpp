@@ -95,6 +95,7 @@ struct TreeBufs {
   double* ray_n;
   int32_t* ray_class;
   int32_t* ray_anti;          // [nray] ray of the opposite direction
+  uint64_t* rcand;            // candidate rays (see DevTree)
   double *csrc_d, *csrc_a;    // complex source model: [node][nray] lengths,
                               // [node][nray][B] absorption (null when off)
   double* geom;               // [64][nclass][3]: log w1, log w12, chord / L

@@ -134,3 +134,17 @@ def test_adjoint_room(n, nside):
     with pytest.raises(api.TrevrError):
         T.tune(api.TUNE_ADJOINT, 2)
     T.close()
+
+
+# the candidate rays of cells and elements in every direction and at every
+# angular size: a ray missed would lose segments or optical depth.  Elements
+# around an off-centre source at N_side 1 to 16 (one to 48 groups of rays), the
+# last group not full at 1, 2 and 8; with a directed ray, which is off its place
+# in the table.
+@pytest.mark.parametrize("directed", [False, True])
+@pytest.mark.parametrize("nside,n", [(1, 3000), (2, 3000), (4, 2000), (8, 900), (16, 300)])
+def test_candidate_rays(nside, n, directed):
+    sc = scenes.lognormal_scene(n=n, seed=nside, grid=16, bands=(1.0, 10.0), nside=nside)
+    if directed:
+        sc = sc.with_(directed=(0.31, 0.72, 0.44))
+    _check_J(sc, scenes.active_subset(sc, 0.3 if nside <= 4 else 0.1, 2))
