@@ -500,19 +500,20 @@ __global__ void __launch_bounds__(64) k_walk(const DevTree* __restrict__ TT, Ite
 // three bands 2.36 -> 1.93 ms, 2^21 at N_side 4 with 1% active 1.11 -> 0.74,
 // 9973 clumpy elements at N_side 4 1.90 -> 1.27.
 template <int NB>
-__global__ void __launch_bounds__(kNT) k_pp_rays(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays(const DevTree* __restrict__ TT, Items I,
                                                 const uint32_t* blist, const uint32_t* bscene,
                                                 const uint32_t* noff, const uint32_t* nidx,
                                                 const uint32_t* toff, const uint8_t* active,
-                                                float* tpp) {
+                                                float* tpp, double* Jall,
+                                                const uint32_t* bparts) {
   constexpr int RGN = PpRayGroup<NB>::value, GN = RGN / 64;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   __shared__ RecvInfo recv[kRMax];
   __shared__ uint32_t nrecv_s, s_item;
   __shared__ double rn[RGN][3];
   __shared__ float acc[kRMax][RGN][NB];
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
+  for (bool first = true;;) {
+  const uint32_t bucket = next_item(I, &s_item, first);
   if (bucket == kNoItem) break;
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
@@ -527,6 +528,7 @@ __global__ void __launch_bounds__(kNT) k_pp_rays(const DevTree* __restrict__ TT,
   float* tppb = tpp + toff[bucket];
   double ud[3];
   const int kd = directed_ray(T, c, ud);   // the bucket's directed ray, if any
+  const bool zero = Jall && bparts[bucket] > 1u;
   uint32_t ract = 0;
   uint32_t member = lk.x;
   for (;;) {
@@ -537,6 +539,9 @@ __global__ void __launch_bounds__(kNT) k_pp_rays(const DevTree* __restrict__ TT,
     const int my_i = lane % nrecv;
     const double r0 = recv[my_i].x[0], r1 = recv[my_i].x[1], r2 = recv[my_i].x[2];
     const uint32_t rslot = recv[my_i].slot;
+    // J of a bucket whose p-p sources run in parts starts at zero: they add to it
+    if (zero && t < nrecv * NB)
+      Jall[T.joff + (int64_t)(t % NB) * n + T.perm[recv[t / NB].slot]] = 0.0;
     for (int k0 = 0; k0 < nray; k0 += RGN) {
       const int kn = min(RGN, nray - k0);
       // the directed ray, when it is in this group: its direction is not a
@@ -660,7 +665,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
   NearTile<NB>& S = U.S;
   double (*red)[NB] = U.red;
   __shared__ RecvInfo recv[kRMax];
-  __shared__ uint32_t nrecv_s, s_item;
+  __shared__ uint32_t nrecv_s, s_part[4];
   // each thread's pair, for lanes that test it on the thread's behalf; the
   // optical depths gathered for it by other lanes (tacc)
   __shared__ float pd_xj[kNT][3];   // FP32 as stored, widened where read
@@ -686,9 +691,10 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
   uint32_t hits = 0;   // this thread's exact-test passes in the current bucket
   uint32_t logn = 0;   // the wavefront's job-log entries in the current bucket
   LogPos lp{kLogFresh, 0u};   // the wavefront's job-log stream
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
-  if (bucket == kNoItem) break;
+  WorkPart wp;
+  for (bool first = true; next_part(I, s_part, &wp, first);) {
+  const uint32_t bucket = wp.bucket;
+  uint32_t pass = 0;   // of the bucket; this part's are wp.part, wp.part + wp.parts, ...
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
   double* J = Jall ? Jall + T.joff : nullptr;
@@ -715,7 +721,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
     const uint32_t si = ri.slot;
     const bool em = nnear >= kPpElementMajor || (uint32_t)nrecv * nl <= (uint32_t)kNT;
     if (JL.log) {
-      if ((!em || nnear >= kLogMaxNear) && t == 0) s_logbad = 1u;
+      if ((!em || nnear >= kLogMaxNear || wp.item >= JL.items) && t == 0) s_logbad = 1u;
       if (em && lbeg.blk == kLogNone && log_ready(JL, lp)) lbeg = lp;
     }
     float reach = 0.0f;   // largest receiver distance from the centre
@@ -727,6 +733,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
     for (int b = 0; b < NB; ++b) acc[b] = 0.0;
     const uint32_t P = (uint32_t)nrecv * nl;
     for (uint32_t pb = 0; pb < P; pb += (uint32_t)stride) {
+      if (pass++ % wp.parts != wp.part) continue;
       const uint32_t p = pb + (uint32_t)t;
       const bool ok = t < stride && p < P;
       const uint32_t j = ok ? near[p / nrecv] : near[0];
@@ -1060,7 +1067,9 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
       const int ii = t / NB, b = t % NB;
       double v = 0.0;
       for (int u = ii; u < stride; u += nrecv) v += red[u][b];
-      J[(int64_t)b * n + T.perm[recv[ii].slot]] = v;
+      double* o = &J[(int64_t)b * n + T.perm[recv[ii].slot]];
+      if (wp.parts == 1u) *o = v;
+      else if (v != 0.0) unsafeAtomicAdd(o, v);   // k_pp_rays left zero
     }
   }
   if (J && t == 0) {
@@ -1068,9 +1077,11 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
       pp_counters_flush(cdst, csum);
       cdst = T.counters;
     }
-    csum[0] += (unsigned long long)nact * nnear;
-    csum[1] += (unsigned long long)nact * nl * nnear;
-    csum[2] = max(csum[2], (unsigned long long)nnear);
+    if (wp.part == 0u) {
+      csum[0] += (unsigned long long)nact * nnear;
+      csum[1] += (unsigned long long)nact * nl * nnear;
+      csum[2] = max(csum[2], (unsigned long long)nnear);
+    }
     csum[3] += s_hits;
     csum[4] += s_logn;
   }
@@ -1078,11 +1089,11 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src(const DevTree* __restrict__ T
     s_hits = 0ull;
     s_logn = 0ull;
   }
-  if (JL.log) {
-    // the bucket's stream starts, or none when the log does not cover it
+  if (JL.log && wp.item < JL.items) {
+    // the item's stream starts, or none when the log does not cover it
     if (lane == 0 && (lbeg.blk == kLogNone || lp.blk == kLogNone)) s_logbad = 1u;
     __syncthreads();
-    if (lane == 0) JL.tab[4 * bucket + wv] = make_uint2(s_logbad ? kLogNone : lbeg.blk, lbeg.pos);
+    if (lane == 0) JL.tab[4 * wp.item + wv] = make_uint2(s_logbad ? kLogNone : lbeg.blk, lbeg.pos);
   }
   }
   if (Jall && threadIdx.x == 0) pp_counters_flush(cdst, csum);
@@ -1152,8 +1163,8 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
     cdst = nullptr;
     far_counters_flush(nullptr, csum);
   }
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
+  for (bool first = true;;) {
+  const uint32_t bucket = next_item(I, &s_item, first);
   if (bucket == kNoItem) break;
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
@@ -1382,12 +1393,12 @@ __global__ void __launch_bounds__(256) k_cost_bins(const DevTree* __restrict__ T
                                                    const uint32_t* bnact, const uint32_t* ncnt,
                                                    const uint32_t* nlumc, uint32_t order,
                                                    uint32_t nscenes, uint32_t* bbin,
-                                                   uint32_t* bins) {
-  __shared__ uint32_t lcnt[kLocalBins];
+                                                   uint32_t* bins, uint32_t* bpass) {
+  __shared__ uint32_t lcnt[kLocalBins], lpass[kLocalBins];
   const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   const bool local = order == ORDER_COST;
   if (local)
-    for (int i = threadIdx.x; i < kLocalBins; i += blockDim.x) lcnt[i] = 0u;
+    for (int i = threadIdx.x; i < kLocalBins; i += blockDim.x) lcnt[i] = lpass[i] = 0u;
   __syncthreads();
   if (b < *nbp) {
   const uint32_t sc = bscene[b];
@@ -1402,13 +1413,24 @@ __global__ void __launch_bounds__(256) k_cost_bins(const DevTree* __restrict__ T
   }
   const uint32_t bin = (uint32_t)(T.B - 1) * kOrderBins + key;
   bbin[b] = bin;
-  if (local) atomicAdd(&lcnt[local_bin(bin)], 1u);
-  else atomicAdd(&bins[bin], 1u);
+  if (local) {
+    atomicAdd(&lcnt[local_bin(bin)], 1u);
+    // the p-p source kernel's passes: whole receiver chunks, then the rest
+    const uint32_t na = bnact[b], nl = nlumc[b], r = na % kRMax;
+    uint32_t passes = (na / kRMax) * ((kRMax * nl + kNT - 1) / kNT);
+    if (r) passes += (nl + kNT / r - 1) / (kNT / r);
+    atomicMax(&lpass[local_bin(bin)], passes);
+  } else {
+    atomicAdd(&bins[bin], 1u);
+  }
   }
   if (local) {
     __syncthreads();
     for (int i = threadIdx.x; i < kLocalBins; i += blockDim.x)
-      if (lcnt[i]) atomicAdd(&bins[(i / kCostBins) * kOrderBins + i % kCostBins], lcnt[i]);
+      if (lcnt[i]) {
+        atomicAdd(&bins[(i / kCostBins) * kOrderBins + i % kCostBins], lcnt[i]);
+        atomicMax(&bpass[i], lpass[i]);
+      }
   }
 }
 
@@ -1417,18 +1439,52 @@ __global__ void __launch_bounds__(256) k_cost_bins(const DevTree* __restrict__ T
 // Heaviest-first order uses the first kCostBins bins of each band count only,
 // fewer than the threads, so one step scans them (scanning all 65536 words
 // took 61 us of every call, a quarter of the smallest one; now 4 us).
-__global__ void __launch_bounds__(1024) k_scan_bins(uint32_t* bins, uint32_t order,
-                                                    uint32_t* rng) {
+//
+// Also the parts of the buckets of each bin for the p-p sources (split): a
+// bucket's parts are doubled, up to kMostParts and the passes its bin's buckets
+// have, while one would cost more than the band count's total over kSplitItems
+// items per workgroup slot.  (Scene by scene: whole buckets.)
+__global__ void __launch_bounds__(1024) k_scan_bins(uint32_t* bins, uint32_t order, uint32_t* rng,
+                                                    const uint32_t* bpass, uint4* split) {
   static_assert(kMaxBands * kCostBins <= 1024, "one bin per thread");
+  __shared__ float total[kMaxBands];
+  __shared__ uint32_t several[kMaxBands];
   const int t = threadIdx.x;
+  const bool in = t < kMaxBands * kCostBins;
+  uint4* info = split + kMaxBands * kCostBins;
+  if (t < kMaxBands) several[t] = 0u;
   if (order == ORDER_COST) {
-    const bool in = t < kMaxBands * kCostBins;
+    if (t < kMaxBands) total[t] = 0.0f;
+    __syncthreads();
     uint32_t* a = bins + (t / kCostBins) * kOrderBins + t % kCostBins;
     const uint32_t v = in ? *a : 0u;
     const uint32_t e = block_excl_u32(v, nullptr);
     if (in) *a = e;
+    const float cost = ldexpf(1.0f, kCostBins - 1 - t % kCostBins);   // at least, below twice it
+    if (v) atomicAdd(&total[t / kCostBins], 1.5f * cost * (float)v);
+    __syncthreads();
+    uint32_t parts = 1;
+    if (v) {
+      const float aim = total[t / kCostBins] * (1.0f / (kSplitSlots * kSplitItems));
+      const uint32_t most = min(kMostParts, bpass[t]);
+      while (parts < most && 2.0f * cost > aim * (float)parts) parts *= 2;
+    }
+    const uint32_t item = block_excl_u32(v * parts, nullptr);
+    if (in) split[t] = make_uint4(item, e, parts, v);
+    if (parts > 1u) several[t / kCostBins] = 1u;
+    __syncthreads();
+    if (in && t % kCostBins == 0)
+      info[t / kCostBins] = make_uint4(several[t / kCostBins], item - e, 0u, 0u);
   } else {
     block_scan_u32(bins, (int64_t)kMaxBands * kOrderBins, nullptr);
+    __syncthreads();
+    if (in) {
+      const int cl = t / kCostBins;   // the first entry takes the band count's buckets
+      const uint32_t e = bins[cl * kOrderBins];
+      const uint32_t end = cl + 1 < kMaxBands ? bins[(cl + 1) * kOrderBins] : rng[1];
+      split[t] = make_uint4(e, e, 1u, t % kCostBins ? 0u : end - e);
+      if (t % kCostBins == 0) info[cl] = make_uint4(0u, 0u, 0u, 0u);
+    }
   }
   __syncthreads();
   if (t < kMaxBands) {
@@ -1458,7 +1514,8 @@ __global__ void __launch_bounds__(256) k_reorder(const DevTree* __restrict__ TT,
                           uint32_t* bscene2,
                           uint32_t* bnact2, uint32_t* ncnt2, uint32_t* nlumc2, double* brad2,
                           double* bprev2, uint32_t* barg2, uint32_t* tcnt2,
-                          uint32_t* jcnt2, uint32_t* pcnt2, unsigned long long* tot) {
+                          uint32_t* jcnt2, uint32_t* pcnt2, const uint4* split,
+                          uint32_t* bparts2, unsigned long long* tot) {
   __shared__ uint32_t lcnt[kLocalBins], lbase[kLocalBins];
   const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   const bool local = order == ORDER_COST;
@@ -1482,6 +1539,7 @@ __global__ void __launch_bounds__(256) k_reorder(const DevTree* __restrict__ TT,
     const DevTree& T = TT[sc];
     const uint32_t na = bnact[b], B = (uint32_t)T.B;
     bsrc2[pos] = b;
+    bparts2[pos] = local ? split[local_bin(bbin[b])].z : 1u;
     blist2[pos] = blist[b];
     bscene2[pos] = sc;
     bnact2[pos] = na;
@@ -1563,11 +1621,13 @@ Scratch carve_scratch(void* base, int64_t leaves, size_t cut_entries) {
   s.ahash = cv.take<unsigned long long>(2);
   s.head_words = (cv.off - (size_t)((char*)s.rng - (char*)base)) / 4;
   s.bins = cv.take<uint32_t>(kMaxBands * kOrderBins);
+  s.bpass = cv.take<uint32_t>(kMaxBands * kCostBins);
   s.ncnt = cv.take<uint32_t>(L + 1);
   s.tcnt = cv.take<uint32_t>(L + 1);
   s.jcnt = cv.take<uint32_t>(L + 1);
   s.pcnt = cv.take<uint32_t>(L + 1);
   s.zero_words = (cv.off - (size_t)((char*)s.rng - (char*)base)) / 4;
+  s.split = cv.take<uint4>(kMaxBands * kCostBins + kMaxBands);
   s.blist = cv.take<uint32_t>(L);
   s.bscene = cv.take<uint32_t>(L);
   s.bnact = cv.take<uint32_t>(L);
@@ -1577,6 +1637,7 @@ Scratch carve_scratch(void* base, int64_t leaves, size_t cut_entries) {
   s.bprev = cv.take<double>(L);
   s.barg = cv.take<uint32_t>(L);
   s.bsrc = cv.take<uint32_t>(L);
+  s.bparts = cv.take<uint32_t>(L);
   s.blist_raw = cv.take<uint32_t>(L);
   s.bscene_raw = cv.take<uint32_t>(L);
   s.bnact_raw = cv.take<uint32_t>(L);
@@ -1683,7 +1744,7 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
   (few ? k_active_buckets<1> : k_active_buckets<4>)<<<gn, 256, 0, st>>>(
       L.TT, active, S.blist_raw, S.bscene_raw, S.bnact_raw, S.rng + 1, S.ahash);
   TREVR_LAUNCH_CHECK("k_active_buckets");
-  const Items I{0u, 0xFFFFFFFFu, S.rng, nullptr};
+  const Items I{0u, 0xFFFFFFFFu, S.rng, nullptr, nullptr, nullptr};
   const unsigned gb = light_grid((uint64_t)L.leaves);
   if (L.stack_large)
     k_setup<kStackLarge><<<gb, 64, 0, st>>>(L.TT, I, S.blist_raw, S.bscene_raw, S.brad_raw,
@@ -1696,15 +1757,15 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
   TREVR_LAUNCH_CHECK("k_setup");
   const unsigned gl = grid_of(L.leaves, 256);
   k_cost_bins<<<gl, 256, 0, st>>>(L.TT, S.rng + 1, S.bscene_raw, S.bnact_raw, S.ncnt_raw,
-                                  S.nlumc_raw, L.cfg.order, (uint32_t)L.S, S.bbin, S.bins);
+                                  S.nlumc_raw, L.cfg.order, (uint32_t)L.S, S.bbin, S.bins, S.bpass);
   TREVR_LAUNCH_CHECK("k_cost_bins");
-  k_scan_bins<<<1, 1024, 0, st>>>(S.bins, L.cfg.order, S.rng);
+  k_scan_bins<<<1, 1024, 0, st>>>(S.bins, L.cfg.order, S.rng, S.bpass, S.split);
   TREVR_LAUNCH_CHECK("k_scan_bins");
   k_reorder<<<gl, 256, 0, st>>>(L.TT, S.rng + 1, L.cfg.order, S.bbin, S.bins, S.blist_raw,
                                 S.bscene_raw, S.bnact_raw, S.ncnt_raw, S.nlumc_raw, S.brad_raw,
                                 S.bprev_raw, S.barg_raw, S.bsrc, S.blist, S.bscene, S.bnact,
                                 S.ncnt, S.nlumc, S.brad, S.bprev, S.barg, S.tcnt, S.jcnt, S.pcnt,
-                                S.tot);
+                                S.split, S.bparts, S.tot);
   TREVR_LAUNCH_CHECK("k_reorder");
   const int64_t Lp = std::max<int64_t>(L.leaves, 1) + 1;
   k_scan_arrays<<<4, 1024, 0, st>>>(ScanArrays{{S.ncnt, S.tcnt, S.jcnt, S.pcnt}}, Lp, S.rng + 1);
@@ -1805,7 +1866,7 @@ trevr_status walk_batch(trevr_tree* T, const Scratch& S, uint32_t b0, uint32_t c
   uint32_t* hbuf = T->host_u32;
   for (;;) {
     hipEvent_t ev = prof_begin(T);
-    if ((rc = walk_launch(tree_launch(T), S, Items{b0, b0 + cnt, nullptr, nullptr}, cnt,
+    if ((rc = walk_launch(tree_launch(T), S, Items{b0, b0 + cnt, nullptr, nullptr, nullptr, nullptr}, cnt,
                           T->cut_default, clean)) != TREVR_OK)
       return rc;
     clean = false;
@@ -1833,7 +1894,7 @@ trevr_status walk_batch(trevr_tree* T, const Scratch& S, uint32_t b0, uint32_t c
   for (uint32_t s0 = b0; s0 < b0 + cnt; s0 += per) {
     const uint32_t scnt = std::min<uint32_t>(per, b0 + cnt - s0);
     hipEvent_t ev = prof_begin(T);
-    if ((rc = walk_launch(tree_launch(T), S, Items{s0, s0 + scnt, nullptr, nullptr}, scnt,
+    if ((rc = walk_launch(tree_launch(T), S, Items{s0, s0 + scnt, nullptr, nullptr, nullptr, nullptr}, scnt,
                           (uint32_t)cap2)) != TREVR_OK)
       return rc;
     prof_end(T, TREVR_PROF_WALK, ev);
@@ -1844,11 +1905,11 @@ trevr_status walk_batch(trevr_tree* T, const Scratch& S, uint32_t b0, uint32_t c
 
 template <int NB>
 static trevr_status pp_rays_nb(const Launch& L, const Scratch& S, const Items& I, uint64_t count,
-                               const uint8_t* active) {
+                               const uint8_t* active, double* J) {
   trevr_status rc;
   const void* fn = (const void*)&k_pp_rays<NB>;
   k_pp_rays<NB><<<persistent_grid(fn, kNT, count, L.cfg.grid_div), kNT, 0, L.st>>>(
-      L.TT, I, S.blist, S.bscene, S.ncnt, S.nidx, S.tcnt, active, S.tpp);
+      L.TT, I, S.blist, S.bscene, S.ncnt, S.nidx, S.tcnt, active, S.tpp, J, S.bparts);
   TREVR_LAUNCH_CHECK("k_pp_rays");
   return rc;
 }
@@ -1858,8 +1919,9 @@ static trevr_status pp_src_nb(const Launch& L, const Scratch& S, const Items& I,
                               const uint8_t* active, double* J) {
   trevr_status rc;
   const void* fn = (const void*)&k_pp_src<NB>;
-  k_pp_src<NB><<<persistent_grid(fn, kNT, count, L.cfg.grid_div), kNT, 0, L.st>>>(
-      L.TT, I, S.blist, S.bscene, S.ncnt, S.nlumc, S.nidx, S.pcnt, active, J, S.ptau,
+  const Items Ip = in_parts(I, S, NB);
+  k_pp_src<NB><<<persistent_grid(fn, kNT, count * kMostParts, L.cfg.grid_div), kNT, 0, L.st>>>(
+      L.TT, Ip, S.blist, S.bscene, S.ncnt, S.nlumc, S.nidx, S.pcnt, active, J, S.ptau,
       L.cfg.pp_sub, S.jlog);
   TREVR_LAUNCH_CHECK("k_pp_src");
   return rc;
@@ -1898,8 +1960,8 @@ static trevr_status far_nb(const Launch& L, const Scratch& S, const Items& I, ui
   }
 
 trevr_status launch_pp_rays(const Launch& L, int B, const Scratch& S, const Items& I,
-                            uint64_t count, const uint8_t* active) {
-  TREVR_BAND_SWITCH(B, pp_rays_nb<NB>(L, S, I, count, active))
+                            uint64_t count, const uint8_t* active, double* J) {
+  TREVR_BAND_SWITCH(B, pp_rays_nb<NB>(L, S, I, count, active, J))
 }
 
 trevr_status launch_pp_src(const Launch& L, int B, const Scratch& S, const Items& I,
@@ -1950,7 +2012,7 @@ trevr_status compute_J_impl(trevr_tree* T, const uint8_t* active, const float* b
       const Launch L = tree_launch(T);
       trevr_status r;
       hipEvent_t e0 = prof_begin(T);
-      if ((r = launch_pp_rays(L, T->B, S, host_items(S, Q_PPR, s0, scnt), scnt, active)) !=
+      if ((r = launch_pp_rays(L, T->B, S, host_items(S, Q_PPR, s0, scnt), scnt, active, J)) !=
           TREVR_OK)
         return r;
       hipEvent_t e2 = prof_begin(T);

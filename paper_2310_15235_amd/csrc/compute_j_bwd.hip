@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
   const int t = threadIdx.x;
   __shared__ PairTile<NB> PT;
   __shared__ RecvInfo recv[kRMax];
-  __shared__ uint32_t nrecv_s, s_item;
+  __shared__ uint32_t nrecv_s, s_part[4];
   __shared__ float gw[kRMax][NB], rinvh[kRMax];
   __shared__ double red[kNT][NB];
   __shared__ double redh[kNT];
@@ -161,9 +161,10 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
   __shared__ float eacc[kNT / 64][64][NB + 1];     // per wavefront: element sums
   __shared__ float egrp[kNT / 64][4][5];   // per wavefront: element spheres of its quarters
   const int lane = t & 63, wv = t >> 6;
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
-  if (bucket == kNoItem) break;
+  WorkPart wp;
+  for (bool first = true; next_part(I, s_part, &wp, first);) {
+  const uint32_t bucket = wp.bucket;
+  uint32_t pass = 0;   // of the bucket; this part's are wp.part, wp.part + wp.parts, ...
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
   const double* gJ = gJall + T.joff;
@@ -178,12 +179,12 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
   const int64_t n = T.n;
   uint32_t member = lk.x;
   uint32_t nact = 0;
-  // the forward's job log of this bucket, where it covers it: the element-
+  // the forward's job log of this part, where it covers it: the element-
   // major sweep then reads its jobs instead of culling again
-  const bool logged = JL.log && JL.tab[4 * bucket].x != kLogNone;
+  const bool logged = JL.log && wp.item < JL.items && JL.tab[4 * wp.item].x != kLogNone;
   LogPos lp{0u, 0u};
   if (logged) {
-    const uint2 s = JL.tab[4 * bucket + wv];
+    const uint2 s = JL.tab[4 * wp.item + wv];
     lp.blk = (uint32_t)__builtin_amdgcn_readfirstlane((int)(s.x < JL.blocks ? s.x : 0u));
     lp.pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)min(s.y, kLogData));
   }
@@ -206,6 +207,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
     redh[t] = 0.0;
     const uint32_t P = (uint32_t)nrecv * nl;
     for (uint32_t pb = 0; pb < P; pb += (uint32_t)stride) {
+      if (pass++ % wp.parts != wp.part) continue;
       // ---- pairs: terms and column adjoints
       const uint32_t p = pb + (uint32_t)t;
       const bool ok = t < stride && p < P;
@@ -493,7 +495,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
       const int ii = t / NB, b = t % NB;
       double v = 0.0;
       for (int u = ii; u < stride; u += nrecv) v += red[u][b];
-      jrawb[(int64_t)(nact + ii) * NB + b] = v;
+      if (v != 0.0) gadd(&jrawb[(int64_t)(nact + ii) * NB + b], v);   // zero at the start
     }
     if (t < nrecv) {
       double v = 0.0;
@@ -534,8 +536,8 @@ __global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays_bwd(const DevT
   __shared__ float g[kRMax][RGN][NB];
   __shared__ float ek[kPRChunk][NB], eh[kPRChunk];
   __shared__ int gz;
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
+  for (bool first = true;;) {
+  const uint32_t bucket = next_item(I, &s_item, first);
   if (bucket == kNoItem) break;
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
@@ -732,8 +734,8 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
   __shared__ uint32_t nrecv_s, wcnt[kFT / 64], s_item;
   __shared__ double red[kFT / 64][kRMax][NB], redh[kFT / 64][kRMax], redr[kFT / 64];
 
-  for (;;) {
-  const uint32_t bucket = next_item(I, &s_item);
+  for (bool first = true;;) {
+  const uint32_t bucket = next_item(I, &s_item, first);
   if (bucket == kNoItem) break;
   const DevTree& T = TT[bscene[bucket]];
   const uint8_t* act = active ? active + T.eoff : nullptr;
@@ -1357,9 +1359,11 @@ static trevr_status bwd_items_nb(const Launch& L, const Scratch& S, const BwdArg
   trevr_status rc;
   hipEvent_t e0 = prof_begin(prof, L.st);
   {
-    const Items Ii{I.lo, I.hi, I.rng, S.q + 2 * Q_PPS_BWD};
+    const Items Ii =
+        in_parts(Items{I.lo, I.hi, I.rng, S.q + 2 * Q_PPS_BWD, nullptr, nullptr}, S, NB);
     const void* fn = (const void*)&k_pp_src_bwd<NB>;
-    k_pp_src_bwd<NB><<<persistent_grid(fn, kNT, count, L.cfg.grid_div), kNT, 0, L.st>>>(
+    k_pp_src_bwd<NB><<<persistent_grid(fn, kNT, count * kMostParts, L.cfg.grid_div), kNT, 0,
+                       L.st>>>(
         L.TT, Ii, S.blist, S.bscene, S.ncnt, S.nlumc, S.nidx, S.jcnt, S.pcnt, S.ptau, a.active,
         a.gJ, a.G, a.jraw, S.jlog);
     TREVR_LAUNCH_CHECK("k_pp_src_bwd");
@@ -1370,7 +1374,7 @@ static trevr_status bwd_items_nb(const Launch& L, const Scratch& S, const BwdArg
     prof->pending.push_back({TREVR_PROF_ADJ_PP_SRC, prof->pending.back().second});
   hipEvent_t e1 = prof_begin(prof, L.st);
   {
-    const Items Ii{I.lo, I.hi, I.rng, S.q + 2 * Q_FAR_BWD};
+    const Items Ii{I.lo, I.hi, I.rng, S.q + 2 * Q_FAR_BWD, nullptr, nullptr};
     const void* fn = (const void*)&k_far_bwd<NB>;
     k_far_bwd<NB><<<persistent_grid(fn, kFT, count, L.cfg.grid_div), kFT, 0, L.st>>>(
         L.TT, Ii, S.blist, S.bscene, S.brad, S.tcnt, S.jcnt, S.cut, cap, S.bstat, S.tpp, a.bg,
@@ -1380,7 +1384,7 @@ static trevr_status bwd_items_nb(const Launch& L, const Scratch& S, const BwdArg
   prof_end(prof, L.st, TREVR_PROF_ADJ_REDUCE, e1);
   hipEvent_t e2 = prof_begin(prof, L.st);
   {
-    const Items Ii{I.lo, I.hi, I.rng, S.q + 2 * Q_PPR_BWD};
+    const Items Ii{I.lo, I.hi, I.rng, S.q + 2 * Q_PPR_BWD, nullptr, nullptr};
     const void* fn = (const void*)&k_pp_rays_bwd<NB>;
     k_pp_rays_bwd<NB><<<persistent_grid(fn, kNT, count, L.cfg.grid_div), kNT, 0, L.st>>>(
         L.TT, Ii, S.blist, S.bscene, S.ncnt, S.nidx, S.tcnt, a.active, a.gtpp, a.G);
@@ -1448,9 +1452,9 @@ AdjointPart carve_adjoint(const trevr_tree* T, const Scratch& S, Carve dyn,
                           const uint64_t tot[TOT_N]) {
   AdjointPart p;
   p.gtpp = dyn.take<float>(tot[TOT_TPP]);
-  p.jraw = dyn.take<double>(tot[TOT_JRAW]);
   p.gbeg = (S.fixed + dyn.off + 255) & ~(size_t)255;
   Carve gcv(dyn.base ? dyn.base - S.fixed + p.gbeg : nullptr);
+  p.jraw = gcv.take<double>(tot[TOT_JRAW]);
   const GradDims dims{T->B * T->n, T->n, T->num_nodes, T->num_nodes * T->B,
                       T->num_nodes * T->nclass * T->B, T->num_leaves};
   p.G = carve_grad(gcv, dims);
@@ -1554,7 +1558,7 @@ trevr_status compute_J_backward_impl(trevr_tree* T, const uint8_t* active, const
     const Launch L = tree_launch(T);
     if (!reuse) {   // the forward's p-p columns and pair optical depths
       hipEvent_t ev_near = prof_begin(T);
-      if ((r = launch_pp_rays(L, T->B, S, host_items(S, Q_PPR, s0, scnt), scnt, active)) !=
+      if ((r = launch_pp_rays(L, T->B, S, host_items(S, Q_PPR, s0, scnt), scnt, active, nullptr)) !=
           TREVR_OK)
         return r;
       if ((r = launch_pp_src(L, T->B, S, host_items(S, Q_PPS, s0, scnt), scnt, active,
@@ -1562,7 +1566,7 @@ trevr_status compute_J_backward_impl(trevr_tree* T, const uint8_t* active, const
         return r;
       prof_end(T, TREVR_PROF_NEAR, ev_near);
     }
-    return bwd_items(L, T->B, S, a, Items{s0, s0 + scnt, nullptr, nullptr}, scnt, cap,
+    return bwd_items(L, T->B, S, a, Items{s0, s0 + scnt, nullptr, nullptr, nullptr, nullptr}, scnt, cap,
                      &T->prof);
   };
   bool whole = reuse && T->fwd.cuts_kept;

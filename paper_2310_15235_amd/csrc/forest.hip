@@ -169,19 +169,24 @@ ForestScratch forest_carve(const trevr_forest* f, void* base) {
   fs.S.ptau = dyn.take<float>(f->tot[TOT_PTAU]);
   fs.fwd_end = fs.S.fixed + dyn.off + 256;
   fs.a.gtpp = dyn.take<float>(f->tot[TOT_TPP]);
-  fs.a.jraw = dyn.take<double>(f->tot[TOT_JRAW]);
   fs.gbeg = align256(fs.S.fixed + dyn.off);
-  Carve gcv(base ? (char*)base + fs.gbeg : nullptr);
+  Carve gcv(base ? (char*)base + fs.gbeg : nullptr);   // zeroed by the adjoint
+  fs.a.jraw = gcv.take<double>(f->tot[TOT_JRAW]);
   const GradDims dims{f->jn_total, f->n_total, f->nodes_total, f->nodesB_total, f->alpha_total,
                       f->leaves_total};
   fs.a.G = carve_grad(gcv, dims);
   fs.gbytes = align256(gcv.off);
   fs.bwd_end = fs.gbeg + fs.gbytes + 256;
-  // the p-p job log: stream starts per bucket, the block counter, the blocks
+  // the p-p job log: stream starts per item (a bucket or a part of one), the
+  // block counter, the blocks
   const uint64_t blocks = std::min<uint64_t>(f->job_log_bytes / (2ull * kLogBlock), 0xFFFFFF00ull);
   if (blocks > 0) {
     Carve lcv(base ? (char*)base + fs.bwd_end : nullptr);
-    fs.S.jlog.tab = lcv.take<uint2>((size_t)4 * std::max<int64_t>(f->leaves_total, 1));
+    int64_t items = std::max<int64_t>(f->leaves_total, 1);
+    for (int b = 0; b < kMaxBands; ++b)
+      if (f->class_leaves[b] > 0) items += kSplitExtra;
+    fs.S.jlog.tab = lcv.take<uint2>((size_t)4 * items);
+    fs.S.jlog.items = (uint32_t)std::min<int64_t>(items, 0x3FFFFFFF);
     fs.S.jlog.next = lcv.take<uint32_t>(64);
     fs.S.jlog.log = lcv.take<uint16_t>((size_t)blocks * kLogBlock);
     fs.S.jlog.blocks = (uint32_t)blocks;
@@ -191,7 +196,7 @@ ForestScratch forest_carve(const trevr_forest* f, void* base) {
 }
 
 Items class_items(const Scratch& S, int B, int slot) {
-  return Items{0u, 0xFFFFFFFFu, S.rng + 2 + 2 * (B - 1), S.q + 2 * slot};
+  return Items{0u, 0xFFFFFFFFu, S.rng + 2 + 2 * (B - 1), S.q + 2 * slot, nullptr, nullptr};
 }
 
 // The forward's per-bucket work after the setup: p-p lists, walks of every
@@ -206,7 +211,7 @@ trevr_status forward_body(trevr_forest* f, const Scratch& S, const uint8_t* acti
   if ((rc = near_fill(L, S)) != TREVR_OK) return rc;
   prof_end(P, L.st, TREVR_PROF_SETUP, e);
   e = prof_begin(P, L.st);
-  if ((rc = walk_launch(L, S, Items{0u, 0xFFFFFFFFu, S.rng, nullptr},
+  if ((rc = walk_launch(L, S, Items{0u, 0xFFFFFFFFu, S.rng, nullptr, nullptr, nullptr},
                         (uint64_t)f->leaves_total, f->cut_cap)) != TREVR_OK)
     return rc;
   prof_end(P, L.st, TREVR_PROF_WALK, e);
@@ -215,7 +220,7 @@ trevr_status forward_body(trevr_forest* f, const Scratch& S, const uint8_t* acti
     const uint64_t cnt = (uint64_t)f->class_leaves[B - 1];
     if (cnt == 0) continue;
     e = prof_begin(P, L.st);
-    if ((rc = launch_pp_rays(L, B, S, class_items(S, B, Q_PPR), cnt, active)) != TREVR_OK)
+    if ((rc = launch_pp_rays(L, B, S, class_items(S, B, Q_PPR), cnt, active, J)) != TREVR_OK)
       return rc;
     prof_end(P, L.st, TREVR_PROF_NEAR, e);
     e = prof_begin(P, L.st);
@@ -284,7 +289,7 @@ trevr_status forest_plan_impl(trevr_forest* f, void* scratch, size_t bytes) {
     // its capacity, so one pass gives the longest cut list
     for (uint32_t b0 = 0; b0 < nb && !over; b0 += kBatch) {
       const uint32_t cnt = std::min<uint32_t>(kBatch, nb - b0);
-      if ((rc = walk_launch(L, S, Items{b0, b0 + cnt, nullptr, nullptr}, cnt,
+      if ((rc = walk_launch(L, S, Items{b0, b0 + cnt, nullptr, nullptr, nullptr, nullptr}, cnt,
                             kCutCap)) != TREVR_OK)
         return rc;
       e = hipMemcpyAsync(hb, S.ovf, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st);

@@ -32,21 +32,42 @@ constexpr double kR = 0.48860251190291992;   // (3/(4 pi))^(1/2)
 // Work items of one launch (active buckets, each with its scene): indices
 // [lo, hi), narrowed by the device-resident range rng[0..1] when given, so a
 // launch can cover a count only the device knows.  A fixed grid of
-// workgroups (as many as are resident on the chip at once) takes the items
-// in order through the counter q[0]; q[1] counts the workgroups that found
-// none left, and the last of them clears both, so the pair is zero before
-// and after every launch (the caller zeroes it once per scratch use).  A plain
-// grid launch (grid_item) leaves q unused; it may be null there.
+// workgroups (as many as are resident on the chip at once) takes the first
+// items by workgroup index and the others in order through the counter q[0];
+// q[1] counts the workgroups that found none left, and the last of them clears
+// both, so the pair is zero before and after every launch (the caller zeroes it
+// once per scratch use).  A launch of no more items than workgroups makes no
+// claim: two device-wide atomics per workgroup, one after the other, were 4 us
+// of the smallest launches' 15 to 30.  A plain grid launch (grid_item) leaves q
+// unused; it may be null there.
 constexpr uint32_t kNoItem = 0xFFFFFFFFu;
 struct Items {
   uint32_t lo, hi;
   const uint32_t* rng;
   uint32_t* q;
+  const uint4* split;   // parts of the buckets by cost bin (next_part), or null
+  const uint4* info;    // {some bucket has several parts, item of bucket b less b if none}
 };
+
+__device__ inline uint32_t wave_excl(uint32_t v, int lane);
+
+// Which of `items` items a workgroup takes next (kNoItem: none is left); first
+// on its first call.  One thread calls it.
+__device__ inline uint32_t claim_item(const Items& I, uint32_t items, bool first) {
+  if (first) return blockIdx.x < items ? blockIdx.x : kNoItem;
+  if (items <= gridDim.x) return kNoItem;
+  const uint32_t k = gridDim.x + atomicAdd(&I.q[0], 1u);
+  if (k < items) return k;
+  if (atomicAdd(&I.q[1], 1u) == gridDim.x - 1u) {
+    atomicExch(&I.q[0], 0u);
+    atomicExch(&I.q[1], 0u);
+  }
+  return kNoItem;
+}
 
 // Next item for the whole workgroup (kNoItem when none is left); a barrier
 // first, so the previous item's LDS is free.
-__device__ inline uint32_t next_item(const Items& I, uint32_t* s_item) {
+__device__ inline uint32_t next_item(const Items& I, uint32_t* s_item, bool& first) {
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t b = I.lo, e = I.hi;
@@ -54,18 +75,79 @@ __device__ inline uint32_t next_item(const Items& I, uint32_t* s_item) {
       b = max(b, I.rng[0]);
       e = min(e, I.rng[1]);
     }
-    const uint32_t k = atomicAdd(&I.q[0], 1u);
-    uint32_t it = kNoItem;
-    if (b < e && k < e - b) {
-      it = b + k;
-    } else if (atomicAdd(&I.q[1], 1u) == gridDim.x - 1u) {
-      atomicExch(&I.q[0], 0u);
-      atomicExch(&I.q[1], 0u);
-    }
-    *s_item = it;
+    const uint32_t k = claim_item(I, b < e ? e - b : 0u, first);
+    *s_item = k == kNoItem ? kNoItem : b + k;
   }
+  first = false;
   __syncthreads();
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
+}
+
+// Heavy buckets in parts: split[k] = {first item, first bucket, parts per
+// bucket, buckets} of cost bin k of the launch's band count (k_scan_bins).
+// Part p of a bucket takes its passes p, p + parts, ...  With a whole bucket as
+// the smallest item, a launch whose heaviest buckets hold a large share of the
+// work ended with most of the chip idle: p-p sources of 9973 clumpy elements at
+// N_side 4 8.13 -> 5.60 ms, of 4096 at N_side 2 248 -> 155 us (adjoint 257 ->
+// 148), of 48 small scenes 3.95 -> 2.75 ms.  Within a bin the items run through
+// the buckets' first parts, then their second, ...: parts of one bucket at work
+// together add to the same elements in the adjoint (8% of its time).
+struct WorkPart {
+  uint32_t item, bucket, part, parts;   // item: over all band counts (job log)
+};
+__device__ inline uint32_t lane_u32(uint32_t v, int L) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, L);
+}
+// The next part for the whole workgroup (false when none is left), as
+// next_item (which serves where every bucket is whole).
+__device__ inline bool next_part(const Items& I, uint32_t* s_part, WorkPart* w, bool& first) {
+  if (I.info->x == 0u) {
+    w->bucket = next_item(I, s_part, first);
+    w->item = w->bucket + I.info->y;
+    w->part = 0u;
+    w->parts = 1u;
+    return w->bucket != kNoItem;
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const uint4 e = lane < kCostBins ? I.split[lane] : make_uint4(0u, 0u, 1u, 0u);
+    uint32_t b = I.lo, end = I.hi;
+    if (I.rng) {
+      b = max(b, I.rng[0]);
+      end = min(end, I.rng[1]);
+    }
+    // the launch's buckets of this lane's bin, and the items before them
+    const uint32_t lo = max(b, e.y), hi = min(end, e.y + e.w);
+    const uint32_t n = lo < hi ? hi - lo : 0u;
+    const uint32_t start = wave_excl(n * e.z, lane);
+    const uint32_t items = lane_u32(start + n * e.z, 63);
+    uint32_t k = 0;
+    if (lane == 0) k = claim_item(I, items, first);
+    k = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
+    uint32_t item = kNoItem, bucket = 0, part = 0, parts = 1;
+    if (k != kNoItem) {
+      const int q = (int)__builtin_ctzll(ballot64(k - start < n * e.z));
+      const uint32_t at = k - lane_u32(start, q), nq = lane_u32(n, q);
+      parts = lane_u32(e.z, q);
+      part = at / nq;
+      bucket = lane_u32(lo, q) + at % nq;
+      item = lane_u32(e.x, q) + part * lane_u32(e.w, q) + (bucket - lane_u32(e.y, q));
+    }
+    if (lane == 0) {
+      s_part[0] = item;
+      s_part[1] = bucket;
+      s_part[2] = part;
+      s_part[3] = parts;
+    }
+  }
+  first = false;
+  __syncthreads();
+  w->item = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[0]);
+  w->bucket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[1]);
+  w->part = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[2]);
+  w->parts = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[3]);
+  return w->item != kNoItem;
 }
 
 // The first item of this workgroup in a plain grid launch (blockIdx.x counts
@@ -86,6 +168,14 @@ __device__ inline uint32_t grid_next(const Items& I, uint32_t b) {
   const uint32_t e = I.rng ? min(I.hi, I.rng[1]) : I.hi;
   return e - b > gridDim.x ? b + gridDim.x : kNoItem;
 }
+
+// Most parts of a bucket, and the items per workgroup slot that splitting
+// aims at (kSplitSlots slots: four workgroups on each of 256 CUs).  The extra
+// items of a band count are below 2.7 kSplitItems kSplitSlots (parts are
+// doubled while one costs more than the aim), which kSplitExtra rounds up.
+constexpr uint32_t kMostParts = 16;
+constexpr uint32_t kSplitSlots = 1024, kSplitItems = 4;
+constexpr int64_t kSplitExtra = 12288;
 
 // Queue counter pairs of a scratch, one per item kernel.
 enum { Q_PPR = 0, Q_PPS, Q_FAR, Q_PPS_BWD, Q_FAR_BWD, Q_PPR_BWD, Q_N };
@@ -392,10 +482,10 @@ constexpr uint32_t kPpElementMajor = 256;
 // followed by the jobs (element lane << 8 | first pair of the source run).
 // A stream lives in blocks of kLogBlock entries taken from a device counter
 // as it grows; the last two entries of a block hold the index of the
-// stream's next block.  tab[4 bucket + wave] is where a bucket's stream
-// starts (block, entry); block kLogNone in tab[4 bucket] marks a bucket the
-// log does not cover (a pair-major receiver chunk, or no block left), which
-// the adjoint culls again itself.
+// stream's next block.  A bucket's parts (next_part) have streams of their own:
+// tab[4 item + wave] is where an item's stream starts (block, entry); block
+// kLogNone in tab[4 item] marks an item the log does not cover (a pair-major
+// receiver chunk, or no block left), which the adjoint culls again itself.
 constexpr uint32_t kLogBlock = 1u << 14;
 constexpr uint32_t kLogData = kLogBlock - 2;   // entries per block before the link
 constexpr uint32_t kLogNone = 0xFFFFFFFFu;     // no block: the stream is dead
@@ -404,9 +494,10 @@ constexpr uint32_t kLogMaxNear = 1u << 24;     // larger p-p sets are not logged
 
 struct JobLog {
   uint16_t* log;       // blocks * kLogBlock entries (null: no log)
-  uint2* tab;          // [bucket][4] stream starts
+  uint2* tab;          // [item][4] stream starts
   uint32_t* next;      // blocks taken (zeroed before the forward)
   uint32_t blocks;
+  uint32_t items;      // rows of tab
 };
 
 // A wavefront's place in its stream (wave-uniform).

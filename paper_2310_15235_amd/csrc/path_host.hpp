@@ -26,14 +26,18 @@ struct Scratch {
   uint32_t* ovf;                // overflow bits, largest cut of a walk
   unsigned long long* ahash;    // [2] active-set fingerprints
   uint32_t* bins;               // cost bins per band count
+  uint32_t* bpass;              // most p-p source passes of a bucket per band count and bin
   uint32_t *ncnt, *tcnt, *jcnt, *pcnt;   // sizes, scanned in place into offsets
   size_t zero_words;            // words from rng to the end of pcnt
   size_t head_words;            // words from rng to the end of ahash (read back together)
+  uint4* split;                 // [kMaxBands][kCostBins] parts of heavy buckets (k_scan_bins),
+                                // then one Items::info per band count
   // processing order
   uint32_t *blist, *bscene, *bnact, *nlumc, *bstat;
   double *brad, *bprev;         // p-p radius; before its last growth (-1: none)
   uint32_t* barg;               // element that set the radius by that growth
   uint32_t* bsrc;               // discovery index of each bucket
+  uint32_t* bparts;             // parts of each bucket
   // discovery order
   uint32_t *blist_raw, *bscene_raw, *bnact_raw, *ncnt_raw, *nlumc_raw, *bbin, *barg_raw;
   double *brad_raw, *bprev_raw;
@@ -104,8 +108,10 @@ trevr_status walk_launch(const Launch& L, const Scratch& S, const Items& I, uint
                          uint32_t cap, bool clean = false);
 // p-p columns per (receiver, ray, band) and, for the sources, pair optical
 // depths and (with J) the p-p part of J, of the items of band count B.
+// (With J, launch_pp_rays zeroes the receivers' rows, which the parts of a
+// bucket in launch_pp_src add to: it comes first.)
 trevr_status launch_pp_rays(const Launch& L, int B, const Scratch& S, const Items& I,
-                            uint64_t count, const uint8_t* active);
+                            uint64_t count, const uint8_t* active, double* J);
 trevr_status launch_pp_src(const Launch& L, int B, const Scratch& S, const Items& I,
                            uint64_t count, const uint8_t* active, double* J);
 // The far field of the items of band count B (J already holds their p-p part).
@@ -142,8 +148,8 @@ struct GradDims {
 
 Grad carve_grad(Carve& cv, const GradDims& d);
 // The adjoint's part of a lone tree's scratch, behind the forward's dynamic
-// part in dyn: the p-p column adjoints, the raw J per receiver and (zeroed at
-// the start, gbytes from byte gbeg) the gradient accumulators; end is the
+// part in dyn: the p-p column adjoints and (zeroed at the start, gbytes from
+// byte gbeg) the raw J per receiver and the gradient accumulators; end is the
 // scratch it all takes.
 struct AdjointPart {
   float* gtpp;
@@ -151,6 +157,7 @@ struct AdjointPart {
   Grad G;
   size_t gbeg, gbytes, end;
 };
+
 AdjointPart carve_adjoint(const trevr_tree* T, const Scratch& S, Carve dyn,
                           const uint64_t tot[TOT_N]);
 // The adjoint's per-bucket kernels (p-p sources, far field, p-p columns) for
@@ -165,7 +172,15 @@ trevr_status bwd_tree_pass(const Launch& L, const Scratch& S, const Grad& G,
                            double* grho);
 
 inline Items host_items(const Scratch& S, int slot, uint32_t b0, uint32_t cnt) {
-  return Items{b0, b0 + cnt, nullptr, S.q + 2 * slot};
+  return Items{b0, b0 + cnt, nullptr, S.q + 2 * slot, nullptr, nullptr};
+}
+
+// The items in parts, of band count B.
+inline Items in_parts(const Items& I, const Scratch& S, int B) {
+  Items P = I;
+  P.split = S.split + (B - 1) * kCostBins;
+  P.info = S.split + kMaxBands * kCostBins + (B - 1);
+  return P;
 }
 
 }  // namespace trevr

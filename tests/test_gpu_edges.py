@@ -148,3 +148,31 @@ def test_candidate_rays(nside, n, directed):
     if directed:
         sc = sc.with_(directed=(0.31, 0.72, 0.44))
     _check_J(sc, scenes.active_subset(sc, 0.3 if nside <= 4 else 0.1, 2))
+
+
+# heavy buckets in parts: few buckets with large near sets and many near sources
+# (each with passes of 256 pairs to share out), one and several receiver chunks
+# per bucket, in a lone tree and in a forest whose job log the adjoint reads.
+# Gradients against the forest without a log (culled again): FP32 rounding of
+# atomic sums, 1e-5 of a value + 1e-6 of the array's largest.
+@pytest.mark.parametrize("leaf", [8, 20])
+def test_parts(leaf):
+    import torch
+    from paper_2310_15235_amd import api
+    scs = [scenes.lognormal_scene(n=n, seed=n, grid=16, bands=(1.0, 10.0, 3.0)[:b], nside=4,
+                                  leaf_size=leaf, src_frac=0.4)
+           for n, b in ((1500, 2), (700, 1), (1100, 2))]
+    _check_J(scs[0], scs[0].active)
+    _check_J(scs[0], scenes.active_subset(scs[0], 0.1, 3))
+    F = api.Forest(scs)
+    gJ = torch.as_tensor(np.random.default_rng(3).normal(size=int(F.boff[-1])), device="cuda")
+    J0 = F.compute_J()
+    plain = F.compute_J_backward(gJ)
+    for room in (2 * F.counters()["pp_log_entries"] + (1 << 26), 1 << 19):
+        F.set_job_log(room)
+        J1 = F.compute_J()
+        logged = F.compute_J_backward(gJ)
+        F.check()
+        for a, b in zip((J1,) + tuple(logged), (J0,) + tuple(plain)):
+            assert bool(((a - b).abs() <= 1e-5 * b.abs() + 1e-6 * b.abs().max()).all())
+    F.close()
