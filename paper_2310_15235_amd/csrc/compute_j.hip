@@ -175,6 +175,7 @@ __global__ void __launch_bounds__(64) k_setup(const DevTree* __restrict__ TT, It
                                               uint32_t* ncnt, uint32_t* nlumc, uint32_t* ovf,
                                               uint32_t* stage, uint32_t stage_cap) {
   __shared__ uint32_t stack[SC];
+  __shared__ uint2 leafq[kLeafQ];
   const int lane = threadIdx.x;
   for (uint32_t b = grid_item(I); b != kNoItem; b = grid_next(I, b)) {
   const DevTree& T = TT[bscene[b]];
@@ -200,7 +201,8 @@ __global__ void __launch_bounds__(64) k_setup(const DevTree* __restrict__ TT, It
     for (;;) {
       double hm = 0.0;
       uint32_t ha = 0xFFFFFFFFu, nl = 0;
-      cnt += wave_near(T, c, r * r, stack, stack_cap<SC>(T), &hm, &nl, o, &overflow, &ha, r2in);
+      cnt += wave_near(T, c, r * r, stack, stack_cap<SC>(T), leafq, &hm, &nl, o, &overflow, &ha,
+                       r2in);
       nlum += nl;
       if (hm > hw || (hm == hw && ha < hwa)) {
         hw = hm;
@@ -248,6 +250,7 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
                                                   uint32_t* __restrict__ nidx) {
   constexpr int kWords = SC / 2 > (int)kSortRuns ? SC / 2 : (int)kSortRuns;
   __shared__ unsigned long long lds[kWords];   // the traversal stack, or sort keys
+  __shared__ uint2 leafq[kLeafQ];
   const uint32_t lane = threadIdx.x;
   for (uint32_t b = blockIdx.x; b < rng[1]; b += gridDim.x, __syncthreads()) {
   const DevTree& T = TT[bscene[b]];
@@ -303,8 +306,8 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
   const double r = brad[b];
   bool overflow = false;
   NearOut o{out, false, 0u, nl, 0u, 0u};
-  wave_near(T, c, r * r, reinterpret_cast<uint32_t*>(lds), stack_cap<SC>(T), nullptr, nullptr, o,
-            &overflow);
+  wave_near(T, c, r * r, reinterpret_cast<uint32_t*>(lds), stack_cap<SC>(T), leafq, nullptr,
+            nullptr, o, &overflow);
   // the queried list into slot order as well, when a bitmap of the tree's
   // slots fits the LDS: each part (luminous, others) marked, then read back
   // in order, a contiguous range of bitmap words per lane

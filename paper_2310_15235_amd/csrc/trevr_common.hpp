@@ -7,13 +7,14 @@
 
 #include "trevr2.h"
 
+#include "healpix.hpp"
+
 namespace trevr {
 
 constexpr int kMaxBands = 16;
 constexpr int kMaxNside = 16;   // 3072 rays (pixel ids keep 16 bits in cut entries)
 constexpr int kKeyBits = 21;           // bits per axis of the Morton key
 constexpr int kMaxLevels = 64;         // prefix lengths 0..63
-constexpr double kPi = 3.14159265358979323846;
 
 // Table of candidate rays by direction (octahedral map, kCandSide^2 bins) and
 // angular size (kCandSin steps of the sine): 1024 bins are 4 degrees across,
@@ -156,37 +157,6 @@ __device__ inline bool slab(const double lo[3], const double hi[3], const double
     }
   }
   return tin < tout;
-}
-
-// HEALPix ring-scheme pixel containing direction v (Gorski et al. 2005).
-__device__ inline int healpix_pixel(int N, double x, double y, double zz) {
-  const double r = sqrt(x * x + y * y + zz * zz);
-  const double z = zz / r;
-  const double za = fabs(z);
-  double phi = atan2(y, x);
-  if (phi < 0.0) phi += 2.0 * kPi;
-  const double tt = phi / (0.5 * kPi);
-  const int ncap = 2 * N * (N - 1);
-  if (za <= 2.0 / 3.0) {
-    const double t1 = N * (0.5 + tt);
-    const double t2 = N * z * 0.75;
-    const long jp = (long)floor(t1 - t2);
-    const long jm = (long)floor(t1 + t2);
-    const long ir = N + 1 + jp - jm;
-    const long kshift = 1 - (ir & 1);
-    long ip = (jp + jm - N + kshift + 1) / 2;
-    ip = ((ip % (4 * N)) + 4 * N) % (4 * N);
-    return (int)(ncap + (ir - 1) * 4 * N + ip);
-  }
-  const double tp = tt - floor(tt);
-  const double tmp = N * sqrt(3.0 * (1.0 - za));
-  const long jp = (long)floor(tp * tmp);
-  const long jm = (long)floor((1.0 - tp) * tmp);
-  const long ir = jp + jm + 1;
-  long ip = (long)floor(tt * ir);
-  ip = ((ip % (4 * ir)) + 4 * ir) % (4 * ir);
-  if (z > 0) return (int)(2 * ir * (ir - 1) + ip);
-  return (int)(12 * N * N - 2 * ir * (ir + 1) + ip);
 }
 
 // Directed rays (TREVR_DIRECTED; Sections 3.4.1, 4): the ray of a bucket
