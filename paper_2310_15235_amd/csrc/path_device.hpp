@@ -1331,45 +1331,15 @@ __device__ inline bool sees(const CellSight& S, const RayGroup& G, int kq) {
   return S.every || (nm > 0.0f && nm * nm >= S.thr);
 }
 
-// Every (absorbing cut entry, ray of the group) hit found by the thread
-// holding the entry, with no barriers: threads take the cut entries in
-// turn; of an absorbing one's candidate rays (see_cell) the exact FP64
-// ray-box test keeps those that meet the cell beyond the p-p sphere, and the
-// same thread calls on_hit(node, ray, t0, t1, clipped) with t0 = max(t_in, r),
-// clipped = (t_in < r).  Hits of one ray arrive from many threads in no fixed
-// order, so on_hit must update shared state atomically.
-template <class F>
-__device__ inline void for_each_hit_lane(const DevTree& T, const uint2* mycut, uint32_t ncut,
-                                         const double c[3], double r, int g, const RayGroup& G,
-                                         F&& on_hit) {
-  for (uint32_t e = threadIdx.x; e < ncut; e += kFT) {
-    const uint2 ent = mycut[e];
-    if (!(ent.y & CUT_ABS)) continue;
-    const uint32_t node = ent.x;
-    CellSight S = see_cell(T, node, c, g, G);
-    if (S.cand == 0ull) continue;
-    double lo[3], hi[3];
-    node_box(T.hdr, T.nk[node], lo, hi);
-    while (S.cand) {
-      const int kq = __ffsll((long long)S.cand) - 1;
-      S.cand &= S.cand - 1ull;
-      if (!sees(S, G, kq)) continue;
-      double tin, tout;
-      if (slab(lo, hi, c, G.n[kq], G.inv[kq], tin, tout) && tout > fmax(tin, r))
-        on_hit(node, kq, fmax(tin, r), tout, tin < r);
-    }
-  }
-}
-
-// The same hits, queued: for light callbacks (the forward's), where lanes
-// with few candidate rays would otherwise wait for the busiest.  No workgroup
+// Every (absorbing cut entry, ray of the group) hit, with no workgroup
 // barriers: threads take the cut entries in turn; each step every lane tests
-// the next of its entry's candidate rays, those that pass are queued per
-// wavefront in Q (kHitQ words) and run 64 at a time, one per lane: the exact
-// FP64 ray-box test keeps those that meet the cell beyond the p-p sphere and
-// that lane calls on_hit(node, ray, t0, t1, clipped) with t0 = max(t_in, r),
-// clipped = (t_in < r).  Hits of one ray arrive from many lanes in no fixed
-// order, so on_hit must update shared state atomically.
+// the next of its entry's candidate rays (see_cell), those that pass are queued
+// per wavefront in Q (kHitQ words) and run 64 at a time, one per lane, since
+// most entries have no hit in a group: the exact FP64 ray-box test keeps those
+// that meet the cell beyond the p-p sphere and that lane calls on_hit(node,
+// ray, t0, t1, clipped) with t0 = max(t_in, r), clipped = (t_in < r).  Hits of
+// one ray arrive from many lanes in no fixed order, so on_hit must update
+// shared state atomically.
 constexpr uint32_t kHitQ = 128;   // one batch of 64 plus one step's 64
 
 template <class F>
