@@ -1156,7 +1156,7 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
   __shared__ float tpp[kRMax][64][NB];
   __shared__ float tex[64][NB];
   __shared__ RecvInfo recv[kRMax];
-  __shared__ uint32_t nrecv_s, wcnt[kFT / 64], abs_count, s_item;
+  __shared__ uint32_t nrecv_s, wcnt[kStagePer * (kFT / 64)], abs_count, s_item;
   __shared__ double red[kFT / 64][kRMax][NB];
   __shared__ uint32_t hitq[kFT / 64][kHitQ];   // per wavefront: queued (entry, ray) tests
   __shared__ unsigned long long csum[kFarCounters];
@@ -1224,10 +1224,9 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
           for (int b = 0; b < NB; ++b) tex[t][b] = 0.0f;
         }
         const uint32_t nsg_all =
-            stage_window<kSrcCap, NB>(T, mycut, ncut, c, k0, kn, skip, W, wcnt, nullptr);
+            stage_window<kSrcCap, NB>(T, mycut, ncut, c, k0, kn, skip, W, wcnt, nullptr, nullptr);
         const uint32_t nsg = min(nsg_all - skip, (uint32_t)kSrcCap);
-        uint32_t q0, q1;
-        sort_window<kSrcCap, NB>(W, nsg, rt, q0, q1);
+        const uint32_t q0 = rt ? W.ray_beg[t] : 0u, q1 = rt ? W.ray_beg[t + 1] : 0u;
 
         // ---- cell absorption along each ray (Sections 2.5.1, 2.6).  Each
         // hit is applied by the thread that found it: sources on its ray
@@ -1236,7 +1235,7 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
         // sorted by distance).  The LDS atomics make the FP32 sums depend on
         // the order of the hits at the level of rounding.
         uint32_t nabs = 0;
-        for_each_hit_queued(T, mycut, ncut, c, r, g, G, hitq[wv],
+        for_each_hit_queued<true>(T, mycut, ncut, c, r, g, G, hitq[wv],
                           [&](uint32_t node, int kq, double ht0, double ht1, bool) {
           const float len = (float)(ht1 - ht0);
           const float* al = &T.alpha[((int64_t)node * T.nclass + G.cls[kq]) * NB];
@@ -1251,21 +1250,19 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
           uint32_t lo_p = r0, hi_p = r1;     // first source beyond t0
           while (lo_p < hi_p) {
             const uint32_t mid = (lo_p + hi_p) >> 1;
-            if ((double)W.s[W.order[mid]] > ht0) hi_p = mid; else lo_p = mid + 1;
+            if ((double)W.s[mid] > ht0) hi_p = mid; else lo_p = mid + 1;
           }
           uint32_t pq = lo_p;
           for (; pq < r1; ++pq) {
-            const uint32_t si = W.order[pq];
-            const double sq = (double)W.s[si];
+            const double sq = (double)W.s[pq];
             if (!(sq < ht1)) break;
             const float part = (float)(sq - ht0);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) atomicAdd(&W.tau[si][b], av[b] * part);
+            for (int b = 0; b < NB; ++b) atomicAdd(&W.tau[pq][b], av[b] * part);
           }
           if (pq < r1) {
-            const uint32_t si = W.order[pq];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) atomicAdd(&W.sfx[si][b], av[b] * len);
+            for (int b = 0; b < NB; ++b) atomicAdd(&W.sfx[pq][b], av[b] * len);
           }
         });
         if (skip == 0 && first_chunk && nabs) atomicAdd(&abs_count, nabs);
@@ -1275,11 +1272,10 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
 #pragma unroll
           for (int b = 0; b < NB; ++b) run[b] = 0.0f;
           for (uint32_t pq = q0; pq < q1; ++pq) {
-            const uint32_t si = W.order[pq];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-              run[b] += W.sfx[si][b];
-              W.tau[si][b] += run[b];
+              run[b] += W.sfx[pq][b];
+              W.tau[pq][b] += run[b];
             }
           }
         }

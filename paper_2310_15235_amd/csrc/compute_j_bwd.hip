@@ -730,12 +730,13 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
   __shared__ SrcWindow<CAP, NB, false> W;   // suffix adds kept in sgtau
   __shared__ RayGroup RG;
   __shared__ uint32_t sid[CAP];
+  __shared__ uint16_t sslot[CAP];
   __shared__ float sgtau[CAP][NB], sgs[CAP];
   __shared__ float tpp[kRMax][64][NB], gtpp[kRMax][64][NB];
   __shared__ float tex[64][NB], gtex[64][NB];
   __shared__ RecvInfo recv[kRMax];
   __shared__ float gw[kRMax][NB], rinvh[kRMax];
-  __shared__ uint32_t nrecv_s, wcnt[kFT / 64], s_item;
+  __shared__ uint32_t nrecv_s, wcnt[kStagePer * (kFT / 64)], s_item;
   __shared__ double redr[kFT / 64];
   // the sweeps' hit queues and, after them, the receivers' sums
   __shared__ union {
@@ -817,15 +818,15 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
 #pragma unroll
           for (int b = 0; b < NB; ++b) tex[t][b] = 0.0f;
         }
-        const uint32_t nsg_all = stage_window<CAP, NB>(T, mycut, ncut, c, k0, kn, skip, W, wcnt, sid);
+        const uint32_t nsg_all =
+            stage_window<CAP, NB>(T, mycut, ncut, c, k0, kn, skip, W, wcnt, sid, sslot);
         const uint32_t nsg = min(nsg_all - skip, (uint32_t)CAP);
         for (uint32_t q = t; q < nsg; q += kFT) {
 #pragma unroll
           for (int b = 0; b < NB; ++b) sgtau[q][b] = 0.0f;
           sgs[q] = 0.0f;
         }
-        uint32_t q0, q1;
-        sort_window<CAP, NB>(W, nsg, rt, q0, q1);
+        const uint32_t q0 = rt ? W.ray_beg[t] : 0u, q1 = rt ? W.ray_beg[t + 1] : 0u;
 
         // ---- cell optical depths: recomputed by a first sweep over the hits,
         // or read where the forward kept them (TREVR_KEEP_DEPTHS, the group
@@ -844,7 +845,7 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
           // thread that found it: sources on its ray inside the chord get the
           // partial length, the nearest source beyond it a suffix add (resolved
           // below along the ray's sources sorted by distance).
-          for_each_hit_queued(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
+          for_each_hit_queued<false>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
                             [&](uint32_t node, int kq, double ht0, double ht1, bool) {
             const float len = (float)(ht1 - ht0);
             const float* al = &T.alpha[((int64_t)node * T.nclass + RG.cls[kq]) * NB];
@@ -858,21 +859,19 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
             uint32_t lo_p = r0, hi_p = r1;
             while (lo_p < hi_p) {
               const uint32_t mid = (lo_p + hi_p) >> 1;
-              if ((double)W.s[W.order[mid]] > ht0) hi_p = mid; else lo_p = mid + 1;
+              if ((double)W.s[mid] > ht0) hi_p = mid; else lo_p = mid + 1;
             }
             uint32_t pq = lo_p;
             for (; pq < r1; ++pq) {
-              const uint32_t si = W.order[pq];
-              const double sq = (double)W.s[si];
+              const double sq = (double)W.s[pq];
               if (!(sq < ht1)) break;
               const float part = (float)(sq - ht0);
   #pragma unroll
-              for (int b = 0; b < NB; ++b) atomicAdd(&W.tau[si][b], av[b] * part);
+              for (int b = 0; b < NB; ++b) atomicAdd(&W.tau[pq][b], av[b] * part);
             }
             if (pq < r1) {
-              const uint32_t si = W.order[pq];
   #pragma unroll
-              for (int b = 0; b < NB; ++b) atomicAdd(&sgtau[si][b], av[b] * len);
+              for (int b = 0; b < NB; ++b) atomicAdd(&sgtau[pq][b], av[b] * len);
             }
           });
           __syncthreads();
@@ -881,22 +880,23 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
   #pragma unroll
             for (int b = 0; b < NB; ++b) run[b] = 0.0f;
             for (uint32_t pq = q0; pq < q1; ++pq) {
-              const uint32_t si = W.order[pq];
   #pragma unroll
               for (int b = 0; b < NB; ++b) {
-                run[b] += sgtau[si][b];
-                W.tau[si][b] += run[b];
-                sgtau[si][b] = 0.0f;
+                run[b] += sgtau[pq][b];
+                W.tau[pq][b] += run[b];
+                sgtau[pq][b] = 0.0f;
               }
             }
           }
           __syncthreads();
         }
 
-        // ---- (receiver, source) pairs
+        // ---- (receiver, source) pairs, in the order of the cut list: next to
+        // each other, the sources of a ray would add to the same column adjoints
         {
           const RecvInfo& ri = recv[ii];
-          for (uint32_t q = (uint32_t)my_q; q < nsg; q += (uint32_t)per_round) {
+          for (uint32_t o = (uint32_t)my_q; o < nsg; o += (uint32_t)per_round) {
+            const uint32_t q = sslot[o];
             const float dx = W.rel[q][0] - ri.rel[0];
             const float dy = W.rel[q][1] - ri.rel[1];
             const float dz = W.rel[q][2] - ri.rel[2];
@@ -1016,17 +1016,16 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
 #pragma unroll
           for (int b = 0; b < NB; ++b) run[b] = 0.0f;
           for (uint32_t pq = q1; pq > q0; --pq) {
-            const uint32_t si = W.order[pq - 1];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-              run[b] += sgtau[si][b];
+              run[b] += sgtau[pq - 1][b];
               W.tau[pq - 1][b] = run[b];
             }
           }
         }
         __syncthreads();
         const bool bg_here = use_bg && skip == 0;
-        for_each_hit_queued(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
+        for_each_hit_queued<false>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
                           [&](uint32_t node, int kq, double ht0, double ht1, bool clipped) {
           const float len = (float)(ht1 - ht0);
           const int cls = RG.cls[kq];
@@ -1041,22 +1040,21 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
           uint32_t lo_p = r0, hi_p = r1;
           while (lo_p < hi_p) {
             const uint32_t mid = (lo_p + hi_p) >> 1;
-            if ((double)W.s[W.order[mid]] > ht0) hi_p = mid; else lo_p = mid + 1;
+            if ((double)W.s[mid] > ht0) hi_p = mid; else lo_p = mid + 1;
           }
           const uint32_t first = lo_p;
           uint32_t pq = first;
           for (; pq < r1; ++pq) {
-            const uint32_t si = W.order[pq];
-            const double sq = (double)W.s[si];
+            const double sq = (double)W.s[pq];
             if (!(sq < ht1)) break;
             const float part = (float)(sq - ht0);
             float gs = 0.0f;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-              ga[b] += sgtau[si][b] * part;
-              gs += sgtau[si][b] * av[b];
+              ga[b] += sgtau[pq][b] * part;
+              gs += sgtau[pq][b] * av[b];
             }
-            if (gs != 0.0f) atomicAdd(&sgs[si], gs);
+            if (gs != 0.0f) atomicAdd(&sgs[pq], gs);
           }
           if (pq < r1) {
 #pragma unroll
