@@ -487,33 +487,24 @@ __global__ void __launch_bounds__(64) k_walk(const DevTree* __restrict__ TT, Ite
 // (1 - b/h_l).  Written to tpp[receiver][ray][band] for the far field.
 //
 // Element-major: per receiver chunk and group of rays (all of them up to
-// N_side 4 and four bands, else 64), the lanes of a wavefront take (p-p
-// element, receiver) pairs, a lane keeping its receiver, and test the pair's
-// rays of the candidate table (and the directed ray) with the exact FP64 test;
-// each hit's kappa Sigma is added to the (receiver, ray) sums in LDS, written
-// out once per group.
-//
-// VALU-bound, and what it issued was divergence: a pair whose element is seen
-// small has one to four candidate rays, one whose element holds or nearly
-// holds the receiver has all of them, and one such pair among 64 (86% of the
-// steps at 2^18 elements) made the wavefront step through every ray for it.
-// Pairs of many candidates are therefore set aside and take the whole
-// wavefront, a ray per lane; the limit between the two is chosen per step from
-// what either costs (PairRays::take_wide).  Before -> now: 2^18 elements of
-// three bands 2.36 -> 1.93 ms, 2^21 at N_side 4 with 1% active 1.11 -> 0.74,
-// 9973 clumpy elements at N_side 4 1.90 -> 1.27.
+// N_side 4 and four bands, else 64), threads take (p-p element, receiver)
+// pairs; a pair tests only the group's rays in the element's ring range (and
+// the directed ray), 64 at a time first with a conservative FP32 test, then
+// with the exact FP64 one, and adds each hit's kappa Sigma to the (receiver,
+// ray) sums in LDS, written out once per group.
 template <int NB>
-__global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(kNT) k_pp_rays(const DevTree* __restrict__ TT, Items I,
                                                 const uint32_t* blist, const uint32_t* bscene,
                                                 const uint32_t* noff, const uint32_t* nidx,
                                                 const uint32_t* toff, const uint8_t* active,
                                                 float* tpp, double* Jall,
                                                 const uint32_t* bparts) {
-  constexpr int RGN = PpRayGroup<NB>::value, GN = RGN / 64;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  constexpr int RGN = PpRayGroup<NB>::value;
+  const int t = threadIdx.x;
   __shared__ RecvInfo recv[kRMax];
   __shared__ uint32_t nrecv_s, s_item;
   __shared__ double rn[RGN][3];
+  __shared__ float rnf[RGN][3];
   __shared__ float acc[kRMax][RGN][NB];
   for (bool first = true;;) {
   const uint32_t bucket = next_item(I, &s_item, first);
@@ -537,71 +528,78 @@ __global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays(const DevTree*
   for (;;) {
     const int nrecv = load_receivers(T, act, c, member, lk.x + lk.y, recv, &nrecv_s);
     if (nrecv == 0) break;
-    const uint32_t per = 64u / (uint32_t)nrecv;      // elements per wavefront step
-    const uint32_t my_u = (uint32_t)lane / (uint32_t)nrecv;
-    const int my_i = lane % nrecv;
-    const double r0 = recv[my_i].x[0], r1 = recv[my_i].x[1], r2 = recv[my_i].x[2];
-    const uint32_t rslot = recv[my_i].slot;
     // J of a bucket whose p-p sources run in parts starts at zero: they add to it
     if (zero && t < nrecv * NB)
       Jall[T.joff + (int64_t)(t % NB) * n + T.perm[recv[t / NB].slot]] = 0.0;
     for (int k0 = 0; k0 < nray; k0 += RGN) {
       const int kn = min(RGN, nray - k0);
       // the directed ray, when it is in this group: its direction is not a
-      // HEALPix centre, so it is tested whatever the table says
+      // HEALPix centre, so it is tested whatever the ring range
       const int kdg = (kd >= k0 && kd < k0 + kn) ? kd - k0 : -1;
       if (t < kn) {
         const int k = k0 + t;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) rn[t][a] = (k == kd) ? ud[a] : T.ray_n[3 * k + a];
+        for (int a = 0; a < 3; ++a) {
+          const double na = (k == kd) ? ud[a] : T.ray_n[3 * k + a];
+          rn[t][a] = na;
+          rnf[t][a] = (float)na;
+        }
       }
       for (int q = t; q < kRMax * RGN * NB; q += kNT) (&acc[0][0][0])[q] = 0.0f;
       __syncthreads();
-      // hit of ray kq (in the group) by the pair of receiver i: adds kappa Sigma
-      auto test = [&](int i, int kq, double d0, double d1, double d2, double dd, double h2,
-                      float sig, float iv, const float* kap) {
-        const double proj = d0 * rn[kq][0] + d1 * rn[kq][1] + d2 * rn[kq][2];
-        const double b2 = dd - proj * proj;
-        if (!(proj > 0.0 && b2 < h2)) return;
-        const float bb = __builtin_amdgcn_sqrtf((float)fmax(b2, 0.0));
-        const float sg = sig * (1.0f - bb * iv);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) atomicAdd(&acc[i][kq][b], kap[b] * sg);
-      };
-      for (uint32_t u0 = (uint32_t)wv * per; u0 < nnear; u0 += (kNT / 64) * per) {
-        const uint32_t u = u0 + my_u;
-        const bool in = my_u < per && u < nnear;
-        const uint32_t l = near[in ? u : u0];
-        const double d0 = (double)T.x[l] - r0, d1 = (double)T.y[l] - r1, d2 = (double)T.z[l] - r2;
+      for (uint32_t pq = (uint32_t)t; pq < nnear * (uint32_t)nrecv; pq += kNT) {
+        const uint32_t u = pq / (uint32_t)nrecv;
+        const int i = (int)(pq % (uint32_t)nrecv);
+        const uint32_t l = near[u];
+        if (l == recv[i].slot) continue;
+        const double d0 = (double)T.x[l] - recv[i].x[0];
+        const double d1 = (double)T.y[l] - recv[i].x[1];
+        const double d2 = (double)T.z[l] - recv[i].x[2];
         const double dd = d0 * d0 + d1 * d1 + d2 * d2;
         const double hl = T.h[l];
         const double h2 = hl * hl;
-        // column density scale 3m/(pi h^2) and 1/h in FP32 (values, not
-        // decisions; no FP64 divisions in this VALU-bound loop)
-        const float iv = __builtin_amdgcn_rcpf((float)hl);
-        const float sig = (float)(3.0 / kPi) * T.m[l] * iv * iv;
-        float kap[NB];
+        const float df[3] = {(float)d0, (float)d1, (float)d2};
+        const float ddf = (float)dd;
+        const float lim = (float)(dd - h2) - 1e-5f * ddf - 1e-30f;
+        const float neg = -1e-5f * cull_sqrt(ddf);
+        int ka, kb;
+        ray_ring_range(T.nside, d0, d1, d2, dd, h2, &ka, &kb);
+        const int lo = max(ka - k0, 0), hi = min(kb - k0, kn);
+        bool loaded = false;
+        float sig = 0.0f, iv = 0.0f, kap[NB];
+        // candidates 64 rays at a time: the FP32 test, then the exact one
+        for (int s0 = 0; s0 < kn; s0 += 64) {
+          uint64_t cand = 0ull;
+          for (int kq = max(lo, s0); kq < min(hi, s0 + 64); ++kq) {
+#pragma clang fp contract(fast)   // FP32 test with margins: fused products are fine
+            const float pf = rnf[kq][0] * df[0] + rnf[kq][1] * df[1] + rnf[kq][2] * df[2];
+            if (pf > neg && pf * pf >= lim) cand |= 1ull << (kq - s0);
+          }
+          if (kdg >= s0 && kdg < s0 + 64) {
+            const float pf = rnf[kdg][0] * df[0] + rnf[kdg][1] * df[1] + rnf[kdg][2] * df[2];
+            if (pf > neg && pf * pf >= lim) cand |= 1ull << (kdg - s0);
+          }
+          if (cand == 0ull) continue;
+          if (!loaded) {
+            // column density scale 3m/(pi h^2) and 1/h in FP32 (values,
+            // not decisions; no FP64 divisions in this VALU-bound loop)
+            iv = __builtin_amdgcn_rcpf((float)hl);
+            sig = (float)(3.0 / kPi) * T.m[l] * iv * iv;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) kap[b] = T.kappa[(int64_t)b * n + l];
-        PairRays<GN> R;
-        R.find(T, in && l != rslot, (float)d0, (float)d1, (float)d2, (float)h2 / (float)dd, k0, kn,
-               kdg);
-        uint64_t wide = R.take_wide();
-        while (R.any()) {
-          const int kq = R.pop();
-          if (kq >= 0) test(my_i, kq, d0, d1, d2, dd, h2, sig, iv, kap);
-        }
-        for (; wide; wide &= wide - 1ull) {
-          const int L = (int)__builtin_ctzll(wide);
-          float wk[NB];
+            for (int b = 0; b < NB; ++b) kap[b] = T.kappa[(int64_t)b * n + l];
+            loaded = true;
+          }
+          while (cand) {
+            const int kq = s0 + __ffsll((long long)cand) - 1;
+            cand &= cand - 1ull;
+            const double proj = d0 * rn[kq][0] + d1 * rn[kq][1] + d2 * rn[kq][2];
+            const double b2 = dd - proj * proj;
+            if (!(proj > 0.0 && b2 < h2)) continue;
+            const float bb = __builtin_amdgcn_sqrtf((float)fmax(b2, 0.0));
+            const float sg = sig * (1.0f - bb * iv);
 #pragma unroll
-          for (int b = 0; b < NB; ++b) wk[b] = lane_f32(kap[b], L);
-          const double w0 = lane_f64(d0, L), w1 = lane_f64(d1, L), w2 = lane_f64(d2, L);
-          const double wdd = lane_f64(dd, L), wh2 = lane_f64(h2, L);
-          const float wsig = lane_f32(sig, L), wiv = lane_f32(iv, L);
-          const int wi = __builtin_amdgcn_readlane(my_i, L);
-          for (int kq = lane; kq < kn; kq += 64)
-            test(wi, kq, w0, w1, w2, wdd, wh2, wsig, wiv, wk);
+            for (int b = 0; b < NB; ++b) atomicAdd(&acc[i][kq][b], kap[b] * sg);
+          }
         }
       }
       __syncthreads();

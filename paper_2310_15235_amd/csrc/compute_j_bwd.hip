@@ -511,28 +511,27 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
 // ------------------------------------------------------ p-p columns
 // Adjoint of k_pp_rays: tau_ikb = sum_l kappa_lb Sigma_l(b_ilk) with the
 // adjoint g_ikb of the far-field kernel: dkappa_lb += g Sigma, dh_l +=
-// g kappa_lb dSigma/dh.  Element-major: the lanes of a wavefront take (p-p
-// element l, receiver i) pairs and run the exact FP64 test (the forward's
-// operation sequence) over the pair's candidate rays, pairs of many set aside
-// for the whole wavefront as in the forward; a pair's contributions are summed
-// in registers, one LDS atomic per pair collects them per element, one FP64
-// atomic per element and group writes them out.  Up to four bands it takes 136
-// registers left to itself, so four workgroups per CU are asked for (128, no
-// spills: 1.5M elements, 10% active, 5.84 -> 5.09 ms; 6.31 before the candidate
-// table).
+// g kappa_lb dSigma/dh.  Element-major: threads take (p-p element l,
+// receiver i) pairs and, per group of rays (as in the forward) 64 at a time,
+// mark the rays that a conservative FP32 test cannot rule out (within h_l of
+// l), then run the exact FP64 test (the forward's operation sequence) over
+// their own marked rays only; each thread sums its pair's contributions in
+// registers, one LDS atomic per pair collects them per element, one FP64
+// atomic per element and group writes them out.
 constexpr int kPRChunk = 256;   // p-p elements per LDS chunk
 
 template <int NB>
-__global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays_bwd(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(kNT) k_pp_rays_bwd(const DevTree* __restrict__ TT, Items I,
                                                     const uint32_t* blist, const uint32_t* bscene,
                                                     const uint32_t* noff, const uint32_t* nidx,
                                                     const uint32_t* toff, const uint8_t* active,
                                                     const float* gtppg, Grad Gall) {
-  constexpr int RGN = PpRayGroup<NB>::value, GN = RGN / 64;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  constexpr int RGN = PpRayGroup<NB>::value;
+  const int t = threadIdx.x;
   __shared__ RecvInfo recv[kRMax];
   __shared__ uint32_t nrecv_s, s_item;
   __shared__ double rn[RGN][3];
+  __shared__ float rnf[RGN][3];
   __shared__ float g[kRMax][RGN][NB];
   __shared__ float ek[kPRChunk][NB], eh[kPRChunk];
   __shared__ int gz;
@@ -558,39 +557,20 @@ __global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays_bwd(const DevT
   for (;;) {
     const int nrecv = load_receivers(T, act, c, member, lk.x + lk.y, recv, &nrecv_s);
     if (nrecv == 0) break;
-    const uint32_t per = 64u / (uint32_t)nrecv;      // elements per wavefront step
-    const uint32_t my_u = (uint32_t)lane / (uint32_t)nrecv;
-    const int my_i = lane % nrecv;
-    const double r0 = recv[my_i].x[0], r1 = recv[my_i].x[1], r2 = recv[my_i].x[2];
-    const uint32_t rslot = recv[my_i].slot;
-    // ray kq (in the group) of the pair of receiver i: a hit adds to the
-    // element's kappa and size adjoints
-    auto test = [&](int i, int kq, double d0, double d1, double d2, double dd, double h2, float sig,
-                    float iv, const float* kap, float* ck, float* gh) {
-      const double proj = d0 * rn[kq][0] + d1 * rn[kq][1] + d2 * rn[kq][2];
-      const double b2 = dd - proj * proj;
-      if (!(proj > 0.0 && b2 < h2)) return;
-      const float bb = __builtin_amdgcn_sqrtf((float)fmax(b2, 0.0));
-      const float sg = sig * (1.0f - bb * iv);
-      const float dsg = sig * iv * (3.0f * bb * iv - 2.0f);
-      float gq = 0.0f;
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        ck[b] += g[i][kq][b] * sg;
-        gq += g[i][kq][b] * kap[b];
-      }
-      *gh += gq * dsg;
-    };
     for (int k0 = 0; k0 < nray; k0 += RGN) {
       const int kn = min(RGN, nray - k0);
       // the directed ray, when it is in this group: its direction is not a
-      // HEALPix centre, so it is tested whatever the table says
+      // HEALPix centre, so it is tested whatever the ring range
       const int kdg = (kd >= k0 && kd < k0 + kn) ? kd - k0 : -1;
       if (t == 0) gz = 0;
       if (t < kn) {
         const int k = k0 + t;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) rn[t][a] = (k == kd) ? ud[a] : T.ray_n[3 * k + a];
+        for (int a = 0; a < 3; ++a) {
+          const double na = (k == kd) ? ud[a] : T.ray_n[3 * k + a];
+          rn[t][a] = na;
+          rnf[t][a] = (float)na;
+        }
       }
       __syncthreads();
       int nz = 0;
@@ -614,14 +594,21 @@ __global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays_bwd(const DevT
           eh[u] = 0.0f;
         }
         __syncthreads();
-        for (uint32_t u0 = (uint32_t)wv * per; u0 < cl; u0 += (kNT / 64) * per) {
-          const uint32_t u = u0 + my_u;
-          const bool in = my_u < per && u < cl;
-          const uint32_t l = near[c0 + (in ? u : u0)];
-          const double d0 = (double)T.x[l] - r0, d1 = (double)T.y[l] - r1, d2 = (double)T.z[l] - r2;
+        for (uint32_t pq = t; pq < cl * (uint32_t)nrecv; pq += kNT) {
+          const uint32_t u = pq / nrecv;
+          const int i = (int)(pq % nrecv);
+          const uint32_t l = near[c0 + u];
+          if (l == recv[i].slot) continue;
+          const double d0 = (double)T.x[l] - recv[i].x[0];
+          const double d1 = (double)T.y[l] - recv[i].x[1];
+          const double d2 = (double)T.z[l] - recv[i].x[2];
           const double dd = d0 * d0 + d1 * d1 + d2 * d2;
           const double hl = T.h[l];
           const double h2 = hl * hl;
+          const float df[3] = {(float)d0, (float)d1, (float)d2};
+          const float ddf = (float)dd;
+          const float lim = (float)(dd - h2) - 1e-5f * ddf - 1e-30f;
+          const float neg = -1e-5f * cull_sqrt(ddf);
           // column density scale 3m/(pi h^2) and 1/h in FP32 (values, not
           // decisions; no FP64 divisions in this VALU-bound loop)
           const float iv = __builtin_amdgcn_rcpf((float)hl);
@@ -629,40 +616,44 @@ __global__ void __launch_bounds__(kNT, NB <= 4 ? 4 : 1) k_pp_rays_bwd(const DevT
           float kap[NB];
 #pragma unroll
           for (int b = 0; b < NB; ++b) kap[b] = T.kappa[(int64_t)b * n + l];
-          PairRays<GN> R;
-          R.find(T, in && l != rslot, (float)d0, (float)d1, (float)d2, (float)h2 / (float)dd, k0,
-                 kn, kdg);
-          uint64_t wide = R.take_wide();
+          int ka, kb;
+          ray_ring_range(T.nside, d0, d1, d2, dd, h2, &ka, &kb);
+          const int lo = max(ka - k0, 0), hi = min(kb - k0, kn);
           float ck[NB], gh = 0.0f;
 #pragma unroll
           for (int b = 0; b < NB; ++b) ck[b] = 0.0f;
-          while (R.any()) {   // in ray order
-            const int kq = R.pop();
-            if (kq >= 0) test(my_i, kq, d0, d1, d2, dd, h2, sig, iv, kap, ck, &gh);
-          }
-          for (; wide; wide &= wide - 1ull) {   // a ray per lane, their sums back to the pair
-            const int L = (int)__builtin_ctzll(wide);
-            float wk[NB], wc[NB], wg = 0.0f;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-              wk[b] = lane_f32(kap[b], L);
-              wc[b] = 0.0f;
+          // the FP32 test over the group's rays in the element's ring range
+          // (and the directed ray) first, 64 rays at a time, then the exact
+          // test for this lane's candidates only (in ray order)
+          for (int s0 = 0; s0 < kn; s0 += 64) {
+            uint64_t cand = 0ull;
+            for (int kq = max(lo, s0); kq < min(hi, s0 + 64); ++kq) {
+#pragma clang fp contract(fast)   // FP32 test with margins: fused products are fine
+              const float pf = rnf[kq][0] * df[0] + rnf[kq][1] * df[1] + rnf[kq][2] * df[2];
+              if (pf > neg && pf * pf >= lim) cand |= 1ull << (kq - s0);
             }
-            const double w0 = lane_f64(d0, L), w1 = lane_f64(d1, L), w2 = lane_f64(d2, L);
-            const double wdd = lane_f64(dd, L), wh2 = lane_f64(h2, L);
-            const float wsig = lane_f32(sig, L), wiv = lane_f32(iv, L);
-            const int wi = __builtin_amdgcn_readlane(my_i, L);
-            for (int kq = lane; kq < kn; kq += 64)
-              test(wi, kq, w0, w1, w2, wdd, wh2, wsig, wiv, wk, wc, &wg);
-            wg = wave_sum_f32(wg);
-            if (lane == L) gh = wg;
+            if (kdg >= s0 && kdg < s0 + 64) {
+              const float pf = rnf[kdg][0] * df[0] + rnf[kdg][1] * df[1] + rnf[kdg][2] * df[2];
+              if (pf > neg && pf * pf >= lim) cand |= 1ull << (kdg - s0);
+            }
+            while (cand) {
+              const int kq = s0 + __ffsll((long long)cand) - 1;
+              cand &= cand - 1ull;
+              const double proj = d0 * rn[kq][0] + d1 * rn[kq][1] + d2 * rn[kq][2];
+              const double b2 = dd - proj * proj;
+              if (!(proj > 0.0 && b2 < h2)) continue;
+              const float bb = __builtin_amdgcn_sqrtf((float)fmax(b2, 0.0));
+              const float sg = sig * (1.0f - bb * iv);
+              const float dsg = sig * iv * (3.0f * bb * iv - 2.0f);
+              float gq = 0.0f;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-              const float v = wave_sum_f32(wc[b]);
-              if (lane == L) ck[b] = v;
+              for (int b = 0; b < NB; ++b) {
+                ck[b] += g[i][kq][b] * sg;
+                gq += g[i][kq][b] * kap[b];
+              }
+              gh += gq * dsg;
             }
           }
-          if (!in) continue;
 #pragma unroll
           for (int b = 0; b < NB; ++b)
             if (ck[b] != 0.0f) atomicAdd(&ek[u][b], ck[b]);

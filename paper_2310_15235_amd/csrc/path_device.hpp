@@ -969,10 +969,9 @@ template <int NB> struct SrcCap {
 // candidate table (k_init fills it), for the bin of d on the octahedral map
 // and the next larger of kCandSin steps of the sine.  A mask holds every ray
 // within the bin's and the step's angle, 0.02 rad to spare, so it misses
-// none; the tests of single rays run on its few set bits.  Where the kernels
-// tested every ray (far field) or the rings of the z-range (p-p columns),
-// most of their instructions went into rays that could not meet the cell: an
-// absorbing cell meets half a ray of 48.
+// none; the tests of single rays run on its few set bits.  Where the far field
+// tested every ray, most of its instructions went into rays that could not
+// meet the cell: an absorbing cell meets half a ray of 48.
 __device__ inline uint32_t cand_bin(float x, float y, float z) {
   const float inv = __builtin_amdgcn_rcpf(fabsf(x) + fabsf(y) + fabsf(z));
   float u = x * inv, v = y * inv;
@@ -993,100 +992,61 @@ __device__ inline const uint64_t* cand_row(const DevTree& T, float x, float y, f
                        (uint32_t)((T.nray + 63) >> 6);
 }
 
-// A value of lane L (the same in every lane) for the whole wavefront.
-__device__ inline float lane_f32(float v, int L) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), L));
+// The rays that can meet a p-p element from a receiver (d = the element's
+// offset from the receiver, dd = |d|^2, h2 = its size squared): a ray meets
+// it (ahead, b < h) only if its direction lies within asin(h/|d|) of d, so
+// its z (cos of the polar angle) lies within the z-range of that cone.  The
+// HEALPix ring order lists the rays by decreasing z, ring by ring (ring i of
+// 4N - 1 at z = 1 - i^2/(3N^2) in the north cap, 4/3 - 2i/(3N) in the belt),
+// so those rays are one index range [*ka, *kb): the rings inside the cone's
+// z-range, widened by 1e-4 in sin and z and 1e-3 of a ring for FP32
+// rounding.  The receiver inside the element (h near |d|): every ray.
+__device__ inline float ring_of_z(int N, float z) {
+  if (z > 2.0f / 3.0f) return (float)N * cull_sqrt(3.0f * fmaxf(1.0f - z, 0.0f));
+  if (z < -2.0f / 3.0f) return 4.0f * N - (float)N * cull_sqrt(3.0f * fmaxf(1.0f + z, 0.0f));
+  return 2.0f * N - 1.5f * N * z;
 }
-__device__ inline double lane_f64(double v, int L) {
-  const long long x = __double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, L);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), L);
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+__device__ inline int ring_start(int N, int i) {
+  if (i <= N) return 2 * i * (i - 1);
+  if (i <= 3 * N) return 2 * N * (N - 1) + 4 * N * (i - N);
+  const int ii = 4 * N - i + 1;   // rings from i to the south pole: ii
+  return 12 * N * N - 2 * ii * (ii - 1);
+}
+__device__ inline void ray_ring_range(int N, double d0, double d1, double d2, double dd, double h2,
+                                      int* ka, int* kb) {
+  const float ddf = (float)dd;
+  const float s2 = (float)h2 / ddf;
+  if (!(s2 < 0.99f)) {
+    *ka = 0;
+    *kb = 12 * N * N;
+    return;
+  }
+  const float z = (float)d2 * rsqrtf(ddf);
+  const float sa = fminf(cull_sqrt(s2) * (1.0f + 1e-4f) + 1e-4f, 1.0f);
+  const float ca = cull_sqrt(fmaxf(1.0f - sa * sa, 0.0f));
+  const float st = cull_sqrt(fmaxf(1.0f - z * z, 0.0f));
+  const float zhi = (z >= ca) ? 1.0f : fminf(z * ca + st * sa + 1e-4f, 1.0f);
+  const float zlo = (-z >= ca) ? -1.0f : fmaxf(z * ca - st * sa - 1e-4f, -1.0f);
+  const int i0 = max(1, (int)ceilf(ring_of_z(N, zhi) - 1e-3f));
+  const int i1 = min(4 * N - 1, (int)floorf(ring_of_z(N, zlo) + 1e-3f));
+  if (i0 > i1) {
+    *ka = *kb = 0;
+    return;
+  }
+  *ka = ring_start(N, i0);
+  *kb = ring_start(N, i1 + 1);
 }
 
-// Sum over the wavefront, the same in every lane: DPP moves within rows of 16
-// lanes, then the four rows (no LDS round trips).  Call with every lane active.
-__device__ inline float wave_sum_f32(float v) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) v += dpp_mov(v, k);
-  return (lane_f32(v, 0) + lane_f32(v, 16)) + (lane_f32(v, 32) + lane_f32(v, 48));
-}
-
-// The rays of a p-p column group (GN masks of 64) that a lane's (element,
-// receiver) pair tests.
-template <int GN> struct PairRays {
-  uint64_t m[GN];
-  // Those of the candidate table for the element's offset d and angular size
-  // (s2 = h^2 / |d|^2), every one when the receiver lies inside the element (h
-  // near |d|); the directed ray kdg always; none for a lane without a pair.
-  __device__ void find(const DevTree& T, bool pair, float d0, float d1, float d2, float s2, int k0,
-                       int kn, int kdg) {
-    const uint64_t* row = pair && s2 < 0.99f ? cand_row(T, d0, d1, d2, cull_sqrt(s2)) + k0 / 64
-                                             : nullptr;
-#pragma unroll
-    for (int g = 0; g < GN; ++g) {
-      const int left = kn - 64 * g;
-      uint64_t v = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
-      if (row && left > 0) v &= row[g];
-      if (kdg >= 64 * g && kdg < 64 * g + 64) v |= 1ull << (kdg - 64 * g);
-      m[g] = pair ? v : 0ull;
-    }
-  }
-  __device__ int count() const {
-    int c = 0;
-#pragma unroll
-    for (int g = 0; g < GN; ++g) c += __popcll(m[g]);
-    return c;
-  }
-  __device__ bool any() const {
-    uint64_t v = 0ull;
-#pragma unroll
-    for (int g = 0; g < GN; ++g) v |= m[g];
-    return ballot64(v != 0ull) != 0ull;
-  }
-  // The lowest ray left (-1: none), removed.
-  __device__ int pop() {
-    int k = -1;
-#pragma unroll
-    for (int g = GN - 1; g >= 0; --g)
-      if (m[g]) k = 64 * g + __ffsll((long long)m[g]) - 1;
-#pragma unroll
-    for (int g = 0; g < GN; ++g)
-      if (k >= 64 * g && k < 64 * g + 64) m[g] &= m[g] - 1ull;
-    return k;
-  }
-  // Sets aside the pairs with more rays than the limit that makes the step
-  // cheapest: a step of single rays costs the wavefront about as much as a
-  // pair set aside and each 64 of its rays (both some 40 to 50 instructions).
-  // Returns the lanes set aside; theirs are no longer in m.
-  __device__ uint64_t take_wide() {
-    const int c = count();
-    int most = 0, cost = 1 << 30;
-#pragma unroll
-    for (int lim = 2; lim <= 16; lim *= 2) {
-      const int w = lim + (1 + GN) * __popcll(ballot64(c > lim));
-      if (w < cost) {
-        cost = w;
-        most = lim;
-      }
-    }
-    const bool wide = c > most;
-    if (wide) {
-#pragma unroll
-      for (int g = 0; g < GN; ++g) m[g] = 0ull;
-    }
-    return ballot64(wide);
-  }
-};
-
-// Rays per group of the p-p column kernels.  Their pair loop finds each
-// (p-p element, receiver) pair's candidate rays and loads its element once per
+// Rays per group of the p-p column kernels.  Their pair loop computes each
+// (p-p element, receiver) pair's ring range and loads its element once per
 // group, so a group holds every ray up to N_side 4 where the LDS sums of a
 // group allow it (up to four bands); the candidate masks stay 64 rays wide.
 template <int NB> struct PpRayGroup {
   static constexpr int value = NB <= 4 ? 192 : 64;
 };
 
+// Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
+// their reciprocals and an FP32 copy (conservative candidate filter).
 // Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
 // their reciprocals and an FP32 copy (conservative candidate filter).
 struct RayGroup {
