@@ -1233,14 +1233,12 @@ __global__ void __launch_bounds__(kFT, FarCfg<NB>::waves) k_far(const DevTree* _
         // sorted by distance).  The LDS atomics make the FP32 sums depend on
         // the order of the hits at the level of rounding.
         uint32_t nabs = 0;
-        for_each_hit_queued<true>(T, mycut, ncut, c, r, g, G, hitq[wv],
-                          [&](uint32_t node, int kq, double ht0, double ht1, bool) {
+        for_each_hit_queued<true, NB>(T, mycut, ncut, c, r, g, G, hitq[wv],
+                          [&](uint32_t node, int kq, double ht0, double ht1, bool,
+                              const float* av) {
           const float len = (float)(ht1 - ht0);
-          const float* al = &T.alpha[((int64_t)node * T.nclass + G.cls[kq]) * NB];
-          float av[NB];
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            av[b] = al[b];
             if (use_bg) atomicAdd(&tex[kq][b], av[b] * len);
           }
           ++nabs;

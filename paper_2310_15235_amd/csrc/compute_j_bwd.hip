@@ -836,14 +836,12 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
           // thread that found it: sources on its ray inside the chord get the
           // partial length, the nearest source beyond it a suffix add (resolved
           // below along the ray's sources sorted by distance).
-          for_each_hit_queued<false>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
-                            [&](uint32_t node, int kq, double ht0, double ht1, bool) {
+          for_each_hit_queued<false, NB>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
+                            [&](uint32_t node, int kq, double ht0, double ht1, bool,
+                              const float* av) {
             const float len = (float)(ht1 - ht0);
-            const float* al = &T.alpha[((int64_t)node * T.nclass + RG.cls[kq]) * NB];
-            float av[NB];
   #pragma unroll
             for (int b = 0; b < NB; ++b) {
-              av[b] = al[b];
               if (use_bg) atomicAdd(&tex[kq][b], av[b] * len);
             }
             const uint32_t r0 = W.ray_beg[kq], r1 = W.ray_beg[kq + 1];
@@ -1016,15 +1014,14 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
         }
         __syncthreads();
         const bool bg_here = use_bg && skip == 0;
-        for_each_hit_queued<false>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
-                          [&](uint32_t node, int kq, double ht0, double ht1, bool clipped) {
+        for_each_hit_queued<false, NB>(T, mycut, ncut, c, r, g, RG, X.hitq[wv],
+                          [&](uint32_t node, int kq, double ht0, double ht1, bool clipped,
+                              const float* av) {
           const float len = (float)(ht1 - ht0);
           const int cls = RG.cls[kq];
-          const float* al = &T.alpha[((int64_t)node * T.nclass + cls) * NB];
-          float av[NB], ga[NB];
+          float ga[NB];
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
-            av[b] = al[b];
             ga[b] = 0.0f;
           }
           const uint32_t r0 = W.ray_beg[kq], r1 = W.ray_beg[kq + 1];

@@ -1342,17 +1342,21 @@ __device__ inline uint64_t wave_transpose(uint64_t v) {
 // in Q (kHitQ words) and run 64 at a time, one per lane, since most entries
 // have no hit in a group: the exact FP64 ray-box test keeps those that meet
 // the cell beyond the p-p sphere and that lane calls on_hit(node, ray, t0, t1,
-// clipped) with t0 = max(t_in, r), clipped = (t_in < r).  Hits of one ray
-// arrive from many lanes in no fixed order, so on_hit must update shared state
-// atomically.  A wavefront's own hits of 64 entries are queued ray by ray, or
-// (kByRay false) each entry's first, then each entry's second, and so on:
+// clipped, alpha) with t0 = max(t_in, r), clipped = (t_in < r) and the cell's
+// absorption along the ray.  Hits of one ray arrive from many lanes in no fixed
+// order, so on_hit must update shared state atomically.  The absorption is
+// read before the test is decided, not by the hits alone, so that its wait is
+// the key's (2^21, 1% active: k_far 3.29 -> 3.17 ms; 1.5M elements, 10% active:
+// 17.9 -> 17.4 and the adjoint 37.5 -> 36.0; entries and keys read a round
+// ahead gave 1%).  A wavefront's own hits of 64 entries are queued ray by ray,
+// or (kByRay false) each entry's first, then each entry's second, and so on:
 // FP32 sums over them depend on the order at the level of rounding, and these
 // are the orders in which a loop over the rays, and one over each entry's own
 // rays, would add them (2% of k_far, against an order that falls out of the
 // queue: 2.78 -> 2.83 ms, 3.17 -> 3.29).
 constexpr uint32_t kHitQ = 128;   // one batch of 64 plus one step's 64
 
-template <bool kByRay, class F>
+template <bool kByRay, int NB, class F>
 __device__ inline void for_each_hit_queued(const DevTree& T, const uint2* mycut, uint32_t ncut,
                                            const double c[3], double r, int g, const RayGroup& G,
                                            uint32_t* Q, F&& on_hit) {
@@ -1364,11 +1368,15 @@ __device__ inline void for_each_hit_queued(const DevTree& T, const uint2* mycut,
       const uint32_t e = job >> 6;
       const int kq = (int)(job & 63u);
       const uint32_t node = mycut[e].x;
+      const float* al = &T.alpha[((int64_t)node * T.nclass + G.cls[kq]) * NB];
+      float av[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) av[b] = al[b];   // read along with the cell's key
       double lo[3], hi[3];
       node_box(T.hdr, T.nk[node], lo, hi);
       double tin, tout;
       if (slab(lo, hi, c, G.n[kq], G.inv[kq], tin, tout) && tout > fmax(tin, r))
-        on_hit(node, kq, fmax(tin, r), tout, tin < r);
+        on_hit(node, kq, fmax(tin, r), tout, tin < r, av);
     }
   };
   const uint32_t rounds = (ncut + kFT - 1) / kFT;
