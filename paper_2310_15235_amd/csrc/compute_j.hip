@@ -168,8 +168,11 @@ __global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restric
 // Also records the radius before the last growth (-1 if it never grew) and
 // the element whose size set the final radius by that growth (the smallest
 // sorted slot among equal sizes), for the adjoint.
+// Bound by its chain of dependent reads: five wavefronts per SIMD (102
+// registers of the 106 it would take) beat four, 2^18 clumpy elements 0.86 ->
+// 0.82 ms; six (85, with spills) took 0.97.
 template <int SC>
-__global__ void __launch_bounds__(64) k_setup(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(64, 5) k_setup(const DevTree* __restrict__ TT, Items I,
                                               const uint32_t* blist, const uint32_t* bscene,
                                               double* brad, double* bprev, uint32_t* barg,
                                               uint32_t* ncnt, uint32_t* nlumc, uint32_t* ovf,
@@ -345,9 +348,11 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
 // ------------------------------------------------------------- the walk
 // Cut lists hold cap entries per bucket; a bucket that needs more still
 // counts them all (bstat, and the batch maximum in ovf[1]) so the host can
-// walk it again with room for them.
+// walk it again with room for them.  Five wavefronts per SIMD, as in k_setup:
+// 2^18 clumpy elements 0.85 -> 0.77 ms (six: 0.76, but 2^21 with 1% active
+// 0.46 -> 0.47).
 template <int SC>
-__global__ void __launch_bounds__(64) k_walk(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(64, 5) k_walk(const DevTree* __restrict__ TT, Items I,
                                              const uint32_t* blist, const uint32_t* bscene,
                                              const double* brad, uint2* cut, uint32_t cap,
                                              uint32_t* bstat, uint32_t* ovf) {
