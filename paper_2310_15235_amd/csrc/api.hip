@@ -1,6 +1,7 @@
 // C ABI of the library (declared in include/trevr2.h): parameter checks,
 // workspace sizing, tree handles, counters, sticky errors and table export.
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -247,8 +248,12 @@ trevr_status trevr_compute_J(trevr_tree* t, const uint8_t* active, const float* 
 // Scratch of trevr_compute_J_noalloc: a fixed device array, one copy per GPU.
 // Host code never passes the array's name to the device: its device address
 // on each GPU is looked up once (hipGetSymbolAddress, with that GPU current)
-// and kept in g_noalloc_ptr.
-static __device__ __align__(256) unsigned char noalloc_scratch[TREVR_NOALLOC_SCRATCH_BYTES];
+// and kept in g_noalloc_ptr.  Behind the bytes that callers know of lies the
+// room for the p-p sources' parts (below 64 KiB at the 4096 buckets whose cut
+// lists alone fill the rest).
+constexpr size_t kNoallocParts = 64 << 10;
+static __device__ __align__(256) unsigned char
+    noalloc_scratch[TREVR_NOALLOC_SCRATCH_BYTES + kNoallocParts];
 constexpr int kMaxDevices = 64;
 static std::mutex g_noalloc_mu;
 static void* g_noalloc_ptr[kMaxDevices] = {};
@@ -280,7 +285,9 @@ trevr_status trevr_compute_J_noalloc(trevr_tree* t, const uint8_t* active, const
   trevr_status rc = noalloc_scratch_ptr(&ptr);
   if (rc != TREVR_OK) return rc;
   t->stream = (hipStream_t)stream;
-  rc = compute_J_impl(t, active, bg, J, ptr, TREVR_NOALLOC_SCRATCH_BYTES);
+  rc = compute_J_impl(t, active, bg, J, ptr,
+                      TREVR_NOALLOC_SCRATCH_BYTES +
+                          std::min(kNoallocParts, parts_bytes(t->num_leaves)));
   if (rc == TREVR_E_CAPACITY) {
     char msg[160];
     std::snprintf(msg, sizeof msg,

@@ -1610,6 +1610,13 @@ size_t default_cut_entries(int64_t leaves) {
   return (size_t)std::min<int64_t>(std::max<int64_t>(leaves, 1), kBatch) * kCutCap;
 }
 
+size_t parts_bytes(int64_t leaves) {
+  auto padded = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  return padded(sizeof(uint32_t) * kMaxBands * kCostBins) +
+         padded(sizeof(uint4) * (kMaxBands * kCostBins + kMaxBands)) +
+         padded(sizeof(uint32_t) * (size_t)std::max<int64_t>(leaves, 1));
+}
+
 Scratch carve_scratch(void* base, int64_t leaves, size_t cut_entries) {
   Carve cv(base);
   Scratch s{};

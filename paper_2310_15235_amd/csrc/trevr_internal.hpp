@@ -196,6 +196,8 @@ struct trevr_tree {
 
 namespace trevr {
 constexpr int kHostWords = 512;
+// What the p-p sources' parts take of a scratch's fixed part.
+size_t parts_bytes(int64_t leaves);
 trevr_status set_error(trevr_status s, const std::string& msg);
 trevr_status hip_check(hipError_t e, const char* what);
 trevr_status build_tree_impl(trevr_tree* t, const float* x, const float* y, const float* z,
