@@ -1583,14 +1583,20 @@ static unsigned grid_of(int64_t work, int threads) {
   return (unsigned)std::max<int64_t>(1, (work + threads - 1) / threads);
 }
 
-// Grid of the kernels of one wavefront per bucket (setup, p-p list fill,
-// walk): at most kLightGrid workgroups, which take buckets a grid's width
-// apart.  A workgroup per leaf of the tree spent most of a launch starting
-// workgroups without a bucket when few elements are active (2^21 elements, 1%
-// active, 18 thousand buckets of 405 thousand leaves).
-constexpr uint64_t kLightGrid = 32768;
-static unsigned light_grid(uint64_t buckets) {
-  return (unsigned)std::max<uint64_t>(1, std::min(buckets, kLightGrid));
+// Grids of the kernels of one wavefront per bucket (setup, p-p list fill,
+// walk), whose bucket count is on the device: a workgroup per leaf of the
+// trees, up to a bound, beyond which they take buckets a grid's width apart.
+// Setup and walk read the tree, and buckets next to each other read the same
+// parts of it: workgroups that go on to buckets far away spread an XCD's L2
+// over many scenes (20 scenes of 2^12 to 2^17 elements: 6.10 and 1.50 ms with
+// 32768 workgroups, 5.24 and 1.37 with one per leaf; 1.5M elements, 10% active:
+// 2.96 and 4.25 -> 2.84 and 4.08).  The list fill reads lists, holds 17 KiB of
+// LDS per workgroup, and loses more by starting workgroups without a bucket
+// (2^21 elements, 1% active, 18 thousand buckets of 405 thousand leaves: 0.15
+// ms with one per leaf, 0.08 with 32768).
+constexpr uint64_t kWalkGrid = 1 << 20, kFillGrid = 32768;
+static unsigned light_grid(uint64_t buckets, uint64_t most) {
+  return (unsigned)std::max<uint64_t>(1, std::min(buckets, most));
 }
 
 #define TREVR_LAUNCH_CHECK(what)                                               \
@@ -1752,7 +1758,7 @@ trevr_status setup_kernels(const Launch& L, const uint8_t* active, const Scratch
       L.TT, active, S.blist_raw, S.bscene_raw, S.bnact_raw, S.rng + 1, S.ahash);
   TREVR_LAUNCH_CHECK("k_active_buckets");
   const Items I{0u, 0xFFFFFFFFu, S.rng, nullptr, nullptr, nullptr};
-  const unsigned gb = light_grid((uint64_t)L.leaves);
+  const unsigned gb = light_grid((uint64_t)L.leaves, kWalkGrid);
   if (L.stack_large)
     k_setup<kStackLarge><<<gb, 64, 0, st>>>(L.TT, I, S.blist_raw, S.bscene_raw, S.brad_raw,
                                              S.bprev_raw, S.barg_raw, S.ncnt_raw, S.nlumc_raw,
@@ -1840,7 +1846,7 @@ trevr_status active_hash(trevr_tree* T, const uint8_t* active, unsigned long lon
 
 trevr_status near_fill(const Launch& L, const Scratch& S) {
   trevr_status rc = TREVR_OK;
-  const unsigned g = light_grid((uint64_t)L.leaves);
+  const unsigned g = light_grid((uint64_t)L.leaves, kFillGrid);
   if (L.stack_large)
     k_near_fill<kStackLarge><<<g, 64, 0, L.st>>>(L.TT, S.rng, S.blist, S.bscene, S.brad, S.ncnt,
                                                   S.nlumc, S.bsrc, S.stage, S.stage_cap, S.nidx);
@@ -1855,7 +1861,7 @@ trevr_status walk_launch(const Launch& L, const Scratch& S, const Items& I, uint
                          uint32_t cap, bool clean) {
   trevr_status rc = TREVR_OK;
   if (!clean && (rc = zero_words(L.st, S.ovf, 2)) != TREVR_OK) return rc;
-  const unsigned gb = light_grid(count);
+  const unsigned gb = light_grid(count, kWalkGrid);
   if (L.stack_large)
     k_walk<kStackLarge><<<gb, 64, 0, L.st>>>(L.TT, I, S.blist, S.bscene, S.brad, S.cut, cap,
                                               S.bstat, S.ovf);
