@@ -176,3 +176,25 @@ def test_parts(leaf):
         for a, b in zip((J1,) + tuple(logged), (J0,) + tuple(plain)):
             assert bool(((a - b).abs() <= 1e-5 * b.abs() + 1e-6 * b.abs().max()).all())
     F.close()
+
+
+# far-field windows: cut lists on either side of a listing round (2048 entries),
+# more sources on a group of rays than a window holds (448 and more: several
+# windows) and fewer.  The adjoint by Euler's identity: J is homogeneous of degree
+# one in the luminosities (their centres do not move when all are scaled), so
+# sum L dE/dL = sum gJ J for E = sum gJ J; with gJ > 0 every term is positive
+# and carries some FP32 roundings: 1e-5.
+@pytest.mark.parametrize("n,theta,n_src,windows", [(30000, 0.2, 6000, True), (6000, 0.6, 40, False)])
+def test_source_windows(n, theta, n_src, windows):
+    from paper_2310_15235_amd import api
+    sc = scenes.uniform_scene(n=n, seed=7, n_src=n_src, bands=(1.0, 10.0), nside=1, theta=theta)
+    act = scenes.active_subset(sc, 0.005, 4)
+    _check_J(sc, act)
+    Jg, c = api.compute_J(sc, active=act)
+    assert (c["max_cut"] > 2048 and c["source_entries"] > 448 * c["buckets"]) == windows
+    a = act.astype(bool)
+    gJ = np.zeros((2, n))
+    gJ[:, a] = 1.0 / np.maximum(Jg[:, a], 1e-300)
+    gL = api.compute_J_backward(sc, gJ, active=act)[0]
+    want = float((gJ[:, a] * Jg[:, a]).sum())
+    assert abs(float((gL * sc.lum).sum()) - want) <= 1e-5 * want
