@@ -172,7 +172,10 @@ trevr_status trevr_workspace_bytes(const trevr_params* p, int64_t n, size_t* tre
  *   tree_ws         : device buffer of >= tree_bytes, caller-owned.
  * The inputs are copied (sorted) into tree_ws and may be freed once the
  * stream work completes.  On success *out receives a new handle that borrows
- * tree_ws.  Synchronises `stream` a few times (one per tree level).
+ * tree_ws.  Synchronises `stream` once (twice for elements crowded into a small
+ * part of the box) and returns with the last kernels of the build queued on
+ * it: calls with the handle on any stream are ordered behind them, and
+ * trevr_tree_destroy waits for them.
  */
 trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, const float* y,
                               const float* z, const float* m, const float* rho,

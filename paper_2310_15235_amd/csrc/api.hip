@@ -181,6 +181,8 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   T->nray = T->dirs->nray;
   T->nclass = T->dirs->nclass;
   T->stream = (hipStream_t)stream;
+  T->built = nullptr;
+  T->building = false;
   T->ws = tree_ws;
   T->ws_bytes = tree_ws_bytes;
   T->scratch_needed = 0;
@@ -235,14 +237,33 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   return TREVR_OK;
 }
 
+// The stream of a call becomes the tree's.  A build returns with its last
+// kernels queued, and a call may come on any stream: it waits for them.
+static trevr_status use_stream(trevr_tree* t, void* stream) {
+  if (t->building) {
+    const trevr_status rc =
+        hip_check(hipStreamWaitEvent((hipStream_t)stream, t->built, 0), "wait for the build");
+    if (rc != TREVR_OK) return rc;
+  }
+  t->stream = (hipStream_t)stream;
+  return TREVR_OK;
+}
+
+// A call that succeeded has synchronised its stream, so the build has ended.
+static trevr_status used(trevr_tree* t, trevr_status rc) {
+  if (rc == TREVR_OK) t->building = false;
+  return rc;
+}
+
 trevr_status trevr_compute_J(trevr_tree* t, const uint8_t* active, const float* bg, double* J,
                              void* scratch, size_t scratch_bytes, void* stream) {
   if (!live(t)) return set_error(TREVR_E_STATE, "unknown or destroyed tree handle");
   if (!J || !scratch) return set_error(TREVR_E_INVALID, "NULL J or scratch");
   if ((t->p.flags & TREVR_BACKGROUND) && !bg)
     return set_error(TREVR_E_INVALID, "TREVR_BACKGROUND needs bg");
-  t->stream = (hipStream_t)stream;
-  return compute_J_impl(t, active, bg, J, scratch, scratch_bytes);
+  const trevr_status rc = use_stream(t, stream);
+  if (rc != TREVR_OK) return rc;
+  return used(t, compute_J_impl(t, active, bg, J, scratch, scratch_bytes));
 }
 
 // Scratch of trevr_compute_J_noalloc: a fixed device array, one copy per GPU.
@@ -284,10 +305,10 @@ trevr_status trevr_compute_J_noalloc(trevr_tree* t, const uint8_t* active, const
   void* ptr = nullptr;
   trevr_status rc = noalloc_scratch_ptr(&ptr);
   if (rc != TREVR_OK) return rc;
-  t->stream = (hipStream_t)stream;
-  rc = compute_J_impl(t, active, bg, J, ptr,
-                      TREVR_NOALLOC_SCRATCH_BYTES +
-                          std::min(kNoallocParts, parts_bytes(t->num_leaves)));
+  if ((rc = use_stream(t, stream)) != TREVR_OK) return rc;
+  rc = used(t, compute_J_impl(t, active, bg, J, ptr,
+                              TREVR_NOALLOC_SCRATCH_BYTES +
+                                  std::min(kNoallocParts, parts_bytes(t->num_leaves))));
   if (rc == TREVR_E_CAPACITY) {
     char msg[160];
     std::snprintf(msg, sizeof msg,
@@ -310,8 +331,10 @@ trevr_status trevr_compute_J_backward(trevr_tree* t, const uint8_t* active, cons
     return set_error(TREVR_E_INVALID, "the adjoint does not cover the complex source model");
   if ((t->p.flags & TREVR_BACKGROUND) && !bg)
     return set_error(TREVR_E_INVALID, "TREVR_BACKGROUND needs bg");
-  t->stream = (hipStream_t)stream;
-  return compute_J_backward_impl(t, active, bg, gJ, gL, gkappa, grho, scratch, scratch_bytes);
+  const trevr_status rc = use_stream(t, stream);
+  if (rc != TREVR_OK) return rc;
+  return used(t, compute_J_backward_impl(t, active, bg, gJ, gL, gkappa, grho, scratch,
+                                         scratch_bytes));
 }
 
 trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value) {
@@ -402,7 +425,9 @@ trevr_status trevr_tree_destroy(trevr_tree* t) {
     g_live.erase(t);
   }
   t->magic = 0;
+  if (t->building) (void)hipEventSynchronize(t->built);
   (void)hipStreamSynchronize(t->stream);
+  if (t->built) (void)hipEventDestroy(t->built);
   prof_destroy(&t->prof);
   if (t->host_u32) pinned_give(t->host_u32);
   delete t;

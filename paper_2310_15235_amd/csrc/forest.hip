@@ -499,6 +499,8 @@ trevr_status trevr_build_forest(const trevr_params* params, int32_t S, const int
     if (e == hipSuccess) e = hipMemsetAsync(f->ferr, 0, 16, f->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(f->stream);
     rc = hip_check(e, "forest table upload");
+    if (rc == TREVR_OK)
+      for (trevr_tree* t : f->trees) t->building = false;
   }
   if (rc != TREVR_OK) {
     const std::string msg = trevr_last_error();

@@ -1439,6 +1439,14 @@ trevr_status build_tree_impl(trevr_tree* T, const float* x, const float* y, cons
     }
   }
 #undef TREVR_LAUNCH_CHECK
+  // the kernels launched since the readback may still run when the call
+  // returns: an event that calls on other streams wait for
+  if (info[3] > 0u || (T->p.flags & TREVR_COMPLEX_SRC)) {
+    hipError_t e = hipEventCreateWithFlags(&T->built, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(T->built, st);
+    if ((rc = hip_check(e, "build event")) != TREVR_OK) return rc;
+    T->building = true;
+  }
   return TREVR_OK;
 }
 

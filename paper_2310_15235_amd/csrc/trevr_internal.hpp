@@ -177,6 +177,8 @@ struct trevr_tree {
   int32_t B, nray, nclass, depth;
   int64_t num_nodes, num_leaves;
   hipStream_t stream;
+  hipEvent_t built;                         // end of the build's last kernels (or null)
+  bool building;                            // they may still run: other streams wait for it
   void* ws;
   size_t ws_bytes;
   trevr::TreeBufs buf;

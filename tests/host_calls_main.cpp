@@ -1,0 +1,135 @@
+// The C ABI's host code in whole calls, on the runtime of fake_hip.cpp: what
+// the calls wait for and the sizes that they ask for.  Run with the name of a
+// case; exit status 0 when it holds.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../include/trevr2.h"
+#include "fake_hip.h"
+
+namespace {
+int failures = 0;
+#define EXPECT(c)                                        \
+  do {                                                   \
+    if (!(c)) {                                          \
+      std::printf("FAIL line %d: %s\n", __LINE__, #c);   \
+      ++failures;                                        \
+    }                                                    \
+  } while (0)
+
+void* const A = (void*)0x1000;   // streams
+void* const B = (void*)0x2000;
+
+// The level table and counts that a build reads back, as (67 ranges, {sort
+// again, nodes, depth, levels of large cells}), for a tree of two levels of
+// large cells over four buckets; every other readback is left zero but for
+// its second word: a compute's active buckets.
+constexpr size_t kLevelBytes = (2 * 67 + 4) * sizeof(uint32_t);
+uint32_t active_buckets = 0;
+void readback(void* dst, const void*, size_t bytes) {
+  uint32_t* w = (uint32_t*)dst;
+  std::memset(w, 0, bytes);
+  if (bytes == kLevelBytes) {
+    const uint32_t ends[4] = {0, 1, 3, 7};
+    for (int d = 0; d < 67; ++d) {
+      w[2 * d] = d < 3 ? ends[d] : 7;
+      w[2 * d + 1] = d < 3 ? ends[d + 1] : 7;
+    }
+    w[134] = 0;
+    w[135] = 7;
+    w[136] = 3;
+    w[137] = 2;
+  } else if (bytes > 8) {
+    w[1] = active_buckets;
+  }
+}
+
+struct Case {
+  trevr_params p{};
+  int64_t n = 4000;
+  std::vector<float> in;
+  std::vector<char> ws, scratch;
+  std::vector<double> out;
+  trevr_tree* t = nullptr;
+  explicit Case(uint32_t flags = TREVR_NEAR_FIELD, int bands = 1, int nside = 1) {
+    p.nside = nside;
+    p.leaf_size = 8;
+    p.n_bands = bands;
+    p.flags = flags;
+    p.theta = 0.75;
+    size_t tb = 0, sb = 0;
+    EXPECT(trevr_workspace_bytes(&p, n, &tb, &sb) == TREVR_OK);
+    in.assign((size_t)n * (bands + 1), 1.0f);
+    ws.resize(tb);
+    scratch.resize(sb);
+    out.resize((size_t)n * bands);
+    fake::on_readback = readback;
+  }
+  trevr_status build(void* st) {
+    const float* x = in.data();
+    return trevr_build_tree(&p, n, x, x, x, x, x, x, x, ws.data(), ws.size(), st, &t);
+  }
+  trevr_status forward(void* st, size_t bytes) {
+    return trevr_compute_J(t, nullptr, nullptr, out.data(), scratch.data(), bytes, st);
+  }
+  size_t needed() {
+    size_t b = 0;
+    EXPECT(trevr_scratch_needed(t, &b) == TREVR_OK);
+    return b;
+  }
+};
+
+// A tree built on one stream and used on another, or given up: nothing may
+// run beside the build's last kernels.
+void stream_order() {
+  using Call = std::function<trevr_status(Case&)>;
+  const Call calls[] = {
+      [](Case& c) { return c.forward(B, c.scratch.size()); },
+      [](Case& c) { return trevr_compute_J_noalloc(c.t, nullptr, nullptr, c.out.data(), B); },
+      [](Case& c) {
+        double* o = c.out.data();
+        return trevr_compute_J_backward(c.t, nullptr, nullptr, o, o, o, o, c.scratch.data(),
+                                        c.scratch.size(), B);
+      },
+      [](Case& c) {   // refused before anything is launched, then another stream
+        EXPECT(c.forward(B, 16) == TREVR_E_CAPACITY);
+        return c.forward((void*)0x3000, c.scratch.size());
+      },
+  };
+  for (const Call& call : calls) {
+    fake::reset();
+    Case c;
+    EXPECT(c.build(A) == TREVR_OK);
+    EXPECT(call(c) == TREVR_OK);
+    EXPECT(fake::loose_operations() == 0);
+    EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
+    EXPECT(fake::host_waited_for(A));
+  }
+  // given up on another stream than its own, which never ran
+  fake::reset();
+  Case c;
+  EXPECT(c.build(A) == TREVR_OK);
+  EXPECT(c.forward(B, 16) == TREVR_E_CAPACITY);
+  EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
+  EXPECT(fake::host_waited_for(A));
+}
+
+const std::map<std::string, void (*)()> cases = {
+    {"stream_order", stream_order},
+};
+}  // namespace
+
+int main(int argc, char** argv) {
+  const auto it = argc == 2 ? cases.find(argv[1]) : cases.end();
+  if (it == cases.end()) {
+    for (const auto& c : cases) std::printf("%s\n", c.first.c_str());
+    return 2;
+  }
+  it->second();
+  std::printf("%s: %d failures\n", argv[1], failures);
+  return failures ? 1 : 0;
+}

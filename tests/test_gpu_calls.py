@@ -1,0 +1,51 @@
+"""Calls in an unusual order or with unusual options, against the oracle or
+against the same call in its usual form.  Tolerance where nothing else is said:
+J within 1e-4 of the oracle (FP32 optical depths, floor 1e-12 of the band's
+largest J), work counters equal."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2310_15235_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = ("buckets", "segments", "source_entries", "absorber_entries", "near_pairs",
+          "near_src_hits")
+
+
+def _close_J(J, c, sc, act):
+    Jo, co = oracle.OracleTree(sc).compute_J(act)
+    a = act.astype(bool)
+    floor = 1e-12 * np.abs(Jo[:, a]).max(axis=1, keepdims=True)
+    err = np.abs(J[:, a] - Jo[:, a]) / np.maximum(np.abs(Jo[:, a]), floor)
+    assert err.max() <= 1e-4
+    for k in COUNTS:
+        assert c[k] == co[k], (k, c[k], co[k])
+
+
+def _device(a, dtype):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a, dtype), device="cuda")
+
+
+# the tree's larger cells are still being formed when the build returns: a
+# call on another stream waits for them
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_built_on_one_stream_used_on_another(noalloc):
+    import torch
+    from paper_2310_15235_amd import api
+    sc = scenes.uniform_scene(n=12000, seed=5, n_src=200, bands=(1.0, 10.0, 100.0), nside=2)
+    act = scenes.active_subset(sc, 0.2, 1)
+    flag = _device(act, np.uint8)
+    torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(s1):
+        T = api.Tree.from_scene(sc)
+    with torch.cuda.stream(s2):
+        J = (T.compute_J_noalloc if noalloc else T.compute_J)(flag)
+        T.check()
+        c = T.counters()
+    s2.synchronize()
+    _close_J(J.cpu().numpy(), c, sc, act)
+    T.close()
