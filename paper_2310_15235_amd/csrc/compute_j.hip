@@ -1712,9 +1712,12 @@ unsigned persistent_grid(const void* fn, int threads, uint64_t items, uint32_t d
 void take_kept(const trevr_tree* T, Scratch& S, Carve& cv, uint32_t nb) {
   const size_t buckets = std::min<size_t>(nb, kBatch);
   const size_t groups = (size_t)(T->nray + 63) / 64;
-  static constexpr int caps[9] = {0, KeptCap<1>::value, KeptCap<2>::value, KeptCap<3>::value,
-                                  KeptCap<4>::value, KeptCap<5>::value, KeptCap<6>::value,
-                                  KeptCap<7>::value, KeptCap<8>::value};
+  static constexpr int caps[] = {
+      0, KeptCap<1>::value, KeptCap<2>::value, KeptCap<3>::value, KeptCap<4>::value,
+      KeptCap<5>::value, KeptCap<6>::value, KeptCap<7>::value, KeptCap<8>::value,
+      KeptCap<9>::value, KeptCap<10>::value, KeptCap<11>::value, KeptCap<12>::value,
+      KeptCap<13>::value, KeptCap<14>::value, KeptCap<15>::value, KeptCap<16>::value};
+  static_assert(sizeof(caps) / sizeof(caps[0]) == kMaxBands + 1, "a window per band count");
   const size_t tau_n = buckets * groups * caps[T->B] * T->B;
   const size_t tex_n = (T->p.flags & TREVR_BACKGROUND) ? buckets * T->nray * T->B : 0;
   if (!(T->p.flags & TREVR_KEEP_DEPTHS) || (tau_n + tex_n) * sizeof(float) > ((size_t)1 << 30)) {

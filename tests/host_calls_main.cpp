@@ -118,7 +118,34 @@ void stream_order() {
   EXPECT(fake::host_waited_for(A));
 }
 
+// Scratch of the kept depths, per band count: each group of 64 rays of each
+// bucket keeps what fits one window of the far-field kernels.
+void kept_depths() {
+  for (int bands = 1; bands <= 16; ++bands)
+    for (int nside : {1, 4})
+      for (uint32_t bg : {0u, (uint32_t)TREVR_BACKGROUND}) {
+        const size_t window = bands == 1 ? 512 : bands <= 3 ? 448 : bands == 4 ? 192 : bands == 6 ? 224 : 256;
+        const size_t rays = 12 * nside * nside, groups = (rays + 63) / 64;
+        size_t need[2];
+        for (uint32_t keep : {0u, (uint32_t)TREVR_KEEP_DEPTHS}) {
+          fake::reset();
+          active_buckets = 3;
+          Case c(TREVR_NEAR_FIELD | bg | keep, bands, nside);
+          EXPECT(c.build(A) == TREVR_OK);
+          EXPECT(trevr_compute_J(c.t, nullptr, c.in.data(), c.out.data(), c.scratch.data(),
+                                 c.scratch.size(), A) == TREVR_OK);
+          need[keep != 0] = c.needed();
+          EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
+        }
+        size_t kept = active_buckets * groups * window * bands * sizeof(float);
+        if (bg) kept = (kept + 255) / 256 * 256 + active_buckets * rays * bands * sizeof(float);
+        EXPECT(need[1] - need[0] == kept);
+      }
+  active_buckets = 0;
+}
+
 const std::map<std::string, void (*)()> cases = {
+    {"kept_depths", kept_depths},
     {"stream_order", stream_order},
 };
 }  // namespace

@@ -49,3 +49,24 @@ def test_built_on_one_stream_used_on_another(noalloc):
     s2.synchronize()
     _close_J(J.cpu().numpy(), c, sc, act)
     T.close()
+
+
+# the kept depths of more than eight bands:
+# the adjoint that reads them against the one that sums them again, to FP32
+# rounding of atomic sums (1e-5 of a value, 1e-6 of the array's largest)
+@pytest.mark.parametrize("bands", [8, 9, 16])
+def test_kept_depths_of_many_bands(bands):
+    from paper_2310_15235_amd import api
+    sc = scenes.lognormal_scene(n=3000, seed=8, grid=16, nside=2,
+                                bands=tuple(float(2 ** (k / 2)) for k in range(bands)))
+    gJ = _device(np.random.default_rng(2).normal(size=(bands, sc.n)), np.float64)
+    grads = []
+    for flags in (0, api.KEEP_DEPTHS):
+        T = api.Tree.from_scene(sc, extra_flags=flags)
+        T.tune(api.TUNE_ADJOINT, 1)   # one scratch for both calls: the depths stay in it
+        T.compute_J()
+        grads.append([g.cpu().numpy() for g in T.compute_J_backward(gJ)])
+        T.check()
+        T.close()
+    for x, y in zip(*grads):
+        assert np.all(np.abs(x - y) <= 1e-5 * np.abs(x) + 1e-6 * np.abs(x).max())
