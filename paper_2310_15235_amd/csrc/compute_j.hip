@@ -163,11 +163,54 @@ __global__ void __launch_bounds__(256) k_active_buckets(const DevTree* __restric
 // wavefront per bucket.
 // Each round queries only the shell the sphere grew by.  The shells are
 // disjoint and together make up the final sphere, so their elements are the
-// p-p set: the rounds leave it as runs (NearOut) in the bucket's stage_cap
-// staging words, {run count or kNoRuns, unused, runs...}, for k_near_fill.
-// Also records the radius before the last growth (-1 if it never grew) and
-// the element whose size set the final radius by that growth (the smallest
-// sorted slot among equal sizes), for the adjoint.
+// p-p set; they go where `o` says (slots: each round's behind those of the
+// rounds before).  Also finds the radius before the last growth (-1 if it
+// never grew) and the element whose size set the final radius by that growth
+// (the smallest sorted slot among equal sizes), for the adjoint.
+struct Sphere {
+  double r, rprev;
+  uint32_t cnt, nlum, arg;
+  bool overflow;   // a query ran out of the traversal stack
+};
+template <int SC>
+__device__ inline Sphere grow_sphere(const DevTree& T, uint32_t leaf, const double c[3],
+                                     uint32_t* stack, uint2* leafq, NearOut& o) {
+  const int lane = threadIdx.x;
+  Sphere s{T.rpp_min, -1.0, 0u, 0u, 0xFFFFFFFFu, false};
+  const uint2 lk = T.nlink[leaf];
+  double rm = 0.0;
+  for (uint32_t k = lk.x + lane; k < lk.x + lk.y; k += 64)
+    rm = fmax(rm, sqrt(dist2_pt3((double)T.x[k], (double)T.y[k], (double)T.z[k], c)) + T.h[k]);
+  s.r = fmax(s.r, wave_max(rm));
+  // the widest element so far (smallest slot among equal sizes) is kept
+  // across rounds
+  double r2in = -1.0, hw = 0.0;
+  uint32_t hwa = 0xFFFFFFFFu;
+  for (;;) {
+    double hm = 0.0;
+    uint32_t ha = 0xFFFFFFFFu, nl = 0;
+    const uint32_t found = wave_near(T, c, s.r * s.r, stack, stack_cap<SC>(T), leafq, &hm, &nl, o,
+                                     &s.overflow, &ha, r2in);
+    s.cnt += found;
+    s.nlum += nl;
+    o.lum0 += nl;
+    o.dark0 += found - nl;
+    if (hm > hw || (hm == hw && ha < hwa)) {
+      hw = hm;
+      hwa = ha;
+    }
+    const double rn = fmax(s.r, hw / T.wbeam);
+    if (!(rn > s.r) || s.overflow) return s;
+    r2in = s.r * s.r;
+    s.rprev = s.r;
+    s.r = rn;
+    s.arg = hwa;   // the widest element inside the sphere set the new radius
+  }
+}
+
+// The spheres of the active buckets; their sets are left as runs (NearOut) in
+// the bucket's stage_cap staging words, {run count or kNoRuns, unused,
+// runs...}, for k_near_fill.
 // Bound by its chain of dependent reads: five wavefronts per SIMD (102
 // registers of the 106 it would take) beat four, 2^18 clumpy elements 0.86 ->
 // 0.82 ms; six (85, with spills) took 0.97.
@@ -185,48 +228,18 @@ __global__ void __launch_bounds__(64, 5) k_setup(const DevTree* __restrict__ TT,
   const uint32_t leaf = blist[b];
   double c[3];
   leaf_centre(T, leaf, c);
-  double r = 0.0, rprev = -1.0;
-  uint32_t cnt = 0, nlum = 0, arg = 0xFFFFFFFFu;
-  bool overflow = false;
+  Sphere s{0.0, -1.0, 0u, 0u, 0xFFFFFFFFu, false};
   NearOut o{stage_cap ? stage + (size_t)b * stage_cap + 2 : nullptr, true, 0u, 0u, 0u,
             stage_cap ? (stage_cap - 2u) / 2u : 0u};
-  if (T.flags & TREVR_NEAR_FIELD) {
-    r = T.rpp_min;
-    const uint2 lk = T.nlink[leaf];
-    double rm = 0.0;
-    for (uint32_t s = lk.x + lane; s < lk.x + lk.y; s += 64)
-      rm = fmax(rm, sqrt(dist2_pt3((double)T.x[s], (double)T.y[s], (double)T.z[s], c)) + T.h[s]);
-    r = fmax(r, wave_max(rm));
-    // each round counts only the shell the sphere grew by; the widest
-    // element so far (smallest slot among equal sizes) is kept across rounds
-    double r2in = -1.0, hw = 0.0;
-    uint32_t hwa = 0xFFFFFFFFu;
-    for (;;) {
-      double hm = 0.0;
-      uint32_t ha = 0xFFFFFFFFu, nl = 0;
-      cnt += wave_near(T, c, r * r, stack, stack_cap<SC>(T), leafq, &hm, &nl, o, &overflow, &ha,
-                       r2in);
-      nlum += nl;
-      if (hm > hw || (hm == hw && ha < hwa)) {
-        hw = hm;
-        hwa = ha;
-      }
-      const double rn = fmax(r, hw / T.wbeam);
-      if (!(rn > r) || overflow) break;
-      r2in = r * r;
-      rprev = r;
-      r = rn;
-      arg = hwa;   // the widest element inside the sphere set the new radius
-    }
-  }
+  if (T.flags & TREVR_NEAR_FIELD) s = grow_sphere<SC>(T, leaf, c, stack, leafq, o);
   if (lane == 0) {
-    brad[b] = r;
-    bprev[b] = rprev;
-    barg[b] = arg;
-    ncnt[b] = cnt;
-    nlumc[b] = nlum;
+    brad[b] = s.r;
+    bprev[b] = s.rprev;
+    barg[b] = s.arg;
+    ncnt[b] = s.cnt;
+    nlumc[b] = s.nlum;
     if (stage_cap) stage[(size_t)b * stage_cap] = o.out ? o.nrun : kNoRuns;
-    if (overflow) atomicOr(ovf, OVF_SETUP);
+    if (s.overflow) atomicOr(ovf, OVF_SETUP);
   }
   __syncthreads();
   }
@@ -239,9 +252,12 @@ __global__ void __launch_bounds__(64, 5) k_setup(const DevTree* __restrict__ TT,
 // boxes: its runs are sorted in LDS by (first slot, staging index) (bitonic,
 // the staging index breaks ties between two shells' members of one window),
 // then placed by a prefix over their member counts.  The others query the
-// sphere again (the same sphere as the last query of k_setup, so the same
-// stack suffices) and, for trees of up to 64 x (LDS words) elements, are put
-// in slot order through a bitmap.
+// sphere again and, for trees of up to 64 x (LDS words) elements, are put in
+// slot order through a bitmap.  One query of the whole sphere may need more of
+// the stack than the shells of k_setup did (it also opens the cells surely
+// inside the inner spheres: 182 entries against 138 in a bucket of 3000 clumpy
+// elements at N_side 4); it is then done again shell by shell, for which the
+// stack sufficed.
 template <int SC>
 __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT,
                                                   const uint32_t* rng, const uint32_t* blist,
@@ -307,10 +323,15 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
   double c[3];
   leaf_centre(T, blist[b], c);
   const double r = brad[b];
+  uint32_t* stack = reinterpret_cast<uint32_t*>(lds);
   bool overflow = false;
   NearOut o{out, false, 0u, nl, 0u, 0u};
-  wave_near(T, c, r * r, reinterpret_cast<uint32_t*>(lds), stack_cap<SC>(T), leafq, nullptr,
-            nullptr, o, &overflow);
+  wave_near(T, c, r * r, stack, stack_cap<SC>(T), leafq, nullptr, nullptr, o, &overflow);
+  if (overflow) {
+    __syncthreads();
+    o = NearOut{out, false, 0u, nl, 0u, 0u};
+    overflow = grow_sphere<SC>(T, blist[b], c, stack, leafq, o).overflow;
+  }
   // the queried list into slot order as well, when a bitmap of the tree's
   // slots fits the LDS: each part (luminous, others) marked, then read back
   // in order, a contiguous range of bitmap words per lane

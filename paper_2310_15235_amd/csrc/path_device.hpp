@@ -263,7 +263,8 @@ struct NearOut {
 // the exact test.  With r2in >= 0, only the shell r2in <= d2 < r2 (cells
 // surely inside the inner sphere are skipped), so a sphere that grows can be
 // counted shell by shell with the same memberships.  The traversal stack
-// lives in `stack` (cap words).  Opened leaves are queued in leafq (kLeafQ
+// lives in `stack` (cap words); a query that it does not hold sets *overflow
+// and is not finished.  Opened leaves are queued in leafq (kLeafQ
 // entries) and scanned 64 at a time: among the 64 nodes of a traversal step a
 // few are leaves, and scanning those at once left most lanes idle through the
 // forty loads of a batch (setup of 2^18 elements 1.30 -> 0.86 ms, of 4096 at
@@ -382,7 +383,7 @@ __device__ inline uint32_t wave_near(const DevTree& T, const double c[3], double
     __syncthreads();
     if (ltail - lhead >= 64u) scan_leaves(64u);
   }
-  if (ltail != lhead) scan_leaves(ltail - lhead);
+  if (!*overflow && ltail != lhead) scan_leaves(ltail - lhead);
   if (lane == 0) atomic_max_u64(&T.counters[CNT_MAX_STACK], (unsigned long long)maxsp);
   const double hw = wave_max(hm);
   if (hmax) *hmax = hw;

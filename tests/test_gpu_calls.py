@@ -70,3 +70,22 @@ def test_kept_depths_of_many_bands(bands):
         T.close()
     for x, y in zip(*grads):
         assert np.all(np.abs(x - y) <= 1e-5 * np.abs(x) + 1e-6 * np.abs(x).max())
+
+
+# p-p sets that the list fill finds again, with stacks between what the shells
+# of these four elements' buckets take (110 to 114 entries) and what one query
+# of the whole sphere takes (182): at 114 to 181 the fill goes shell by shell,
+# below the setup takes the large stack, above one query does
+@pytest.mark.parametrize("limit", [64, 113, 114, 128, 181, 182, 1024])
+def test_list_fill_within_the_stack_of_the_shells(limit):
+    from paper_2310_15235_amd import api
+    sc = scenes.lognormal_scene(n=3000, seed=35, grid=16, bands=(1.0, 10.0), nside=4)
+    act = np.zeros(sc.n, np.uint8)
+    act[[504, 740, 18, 213]] = 1
+    T = api.Tree.from_scene(sc)
+    T.tune(api.TUNE_STAGE, 0)
+    T.tune(api.TUNE_STACK, limit)
+    J = T.compute_J(_device(act, np.uint8))
+    T.check()
+    _close_J(J.cpu().numpy(), T.counters(), sc, act)
+    T.close()
