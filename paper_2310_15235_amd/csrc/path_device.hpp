@@ -1305,9 +1305,11 @@ __device__ inline CellSight see_cell(const DevTree& T, uint32_t node, const doub
   const float marg = 1e-5f * D2 + 1e-30f;
   S.every = !(D2 - R2 > marg);
   S.thr = D2 - R2 - marg;
+  // (1/D2 would be flushed to zero where it is subnormal, |mc| from 9.2e18 on:
+  // parsecs in cm; an R2 flushed to zero belongs to a sine below 1e-4)
   S.cand = S.every ? G.all
                    : (cand_row(T, S.mc[0], S.mc[1], S.mc[2],
-                               cull_sqrt(R2 * __builtin_amdgcn_rcpf(D2)))[g] & G.all) | G.aimed;
+                               cull_sqrt(R2) * __builtin_amdgcn_rsqf(D2))[g] & G.all) | G.aimed;
   return S;
 }
 __device__ inline bool sees(const CellSight& S, const RayGroup& G, int kq) {

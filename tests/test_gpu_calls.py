@@ -89,3 +89,28 @@ def test_list_fill_within_the_stack_of_the_shells(limit):
     T.check()
     _close_J(J.cpu().numpy(), T.counters(), sc, act)
     T.close()
+
+
+def _in_units(sc, s):
+    """The scene in units s times smaller, with FP32 masses, opacities and
+    luminosities in range (kappa rho x length unchanged)."""
+    f = lambda a, k: np.ascontiguousarray(np.asarray(a, np.float64) * k, np.float32)
+    big = 1e33
+    box = None if sc.box is None else tuple(float(np.float32(v * s)) for v in sc.box)
+    return sc.with_(x=f(sc.x, s), y=f(sc.y, s), z=f(sc.z, s), m=f(sc.m, big),
+                    rho=f(sc.rho, big / s ** 3), kappa=f(sc.kappa, s * s / big),
+                    lum=f(sc.lum, big), box=box)
+
+
+# parsecs in cm: squares of lengths reach 2^126, above which their reciprocals
+# are subnormal; every ray of a cell is found there too
+@pytest.mark.parametrize("nside", [1, 2, 4])
+@pytest.mark.parametrize("s", [5e18, 1.05e19])
+def test_rays_of_cells_in_cm(s, nside):
+    from paper_2310_15235_amd import api
+    sc = _in_units(scenes.lognormal_scene(n=4000, seed=3, grid=16, bands=(1.0, 10.0), nside=nside), s)
+    act = scenes.active_subset(sc, 0.2, 2)
+    c = api.compute_J(sc, active=act)[1]
+    o = oracle.OracleTree(sc).compute_J(act)[1]
+    for k in ("buckets", "segments", "source_entries", "absorber_entries"):
+        assert c[k] == o[k], (k, c[k], o[k])
