@@ -636,7 +636,8 @@ __device__ inline void log_skip(const JobLog& J, LogPos& p, uint32_t cnt) {
 // read at the run's first pair): s = jr the source relative to the bucket
 // centre, jinv = 1/|s|^2, lim = |s| + the receivers' reach R (a 1e-5
 // margin), and the round cone's k2 = 1 - R^2/|s|^2 and m2 = R^2 / (|s|^2
-// (|s|^2 - R^2)), m2 < 0 when |s| <= R.
+// (|s|^2 - R^2)), m2 < 0 when |s| <= R.  (m2 without |s|^4, which leaves FP32's
+// range from |s| = 4e9 on.)
 struct RunTab {
   const float (*jr)[3];
   const float *jinv, *lim, *k2, *m2;
@@ -652,7 +653,7 @@ __device__ inline void run_tab_entry(const float s[3], float reach, float (*jr)[
   jinv[t] = L2 > 0.0f ? 1.0f / L2 : 0.0f;
   lim[t] = (cull_sqrt(L2) + reach) * (1.0f + 1e-5f);
   k2[t] = L2 > R2 ? (L2 - R2) / L2 : 0.0f;
-  m2[t] = L2 > R2 ? R2 / (L2 * (L2 - R2)) : -1.0f;
+  m2[t] = L2 > R2 ? R2 / (L2 - R2) * jinv[t] : -1.0f;
 }
 
 // Whether p comes within A - R u of the point u s of the segment from the

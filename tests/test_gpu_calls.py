@@ -95,7 +95,7 @@ def _in_units(sc, s):
     """The scene in units s times smaller, with FP32 masses, opacities and
     luminosities in range (kappa rho x length unchanged)."""
     f = lambda a, k: np.ascontiguousarray(np.asarray(a, np.float64) * k, np.float32)
-    big = 1e33
+    big = 1e33 if s > 1.0 else 1.0
     box = None if sc.box is None else tuple(float(np.float32(v * s)) for v in sc.box)
     return sc.with_(x=f(sc.x, s), y=f(sc.y, s), z=f(sc.z, s), m=f(sc.m, big),
                     rho=f(sc.rho, big / s ** 3), kappa=f(sc.kappa, s * s / big),
@@ -114,3 +114,15 @@ def test_rays_of_cells_in_cm(s, nside):
     o = oracle.OracleTree(sc).compute_J(act)[1]
     for k in ("buckets", "segments", "source_entries", "absorber_entries"):
         assert c[k] == o[k], (k, c[k], o[k])
+
+
+# ... and the p-p sources' round cone, whose terms held a length to the fourth
+# power: J in units from 1e-10 to 1e19 of the box
+@pytest.mark.parametrize("nside", [1, 4])
+@pytest.mark.parametrize("s", [1e-10, 3e9, 1e11, 1e15, 1.05e19])
+def test_J_in_any_unit_of_length(s, nside):
+    from paper_2310_15235_amd import api
+    sc = _in_units(scenes.lognormal_scene(n=4000, seed=3, grid=16, bands=(1.0, 10.0), nside=nside), s)
+    act = scenes.active_subset(sc, 0.2, 2)
+    J, c = api.compute_J(sc, active=act)
+    _close_J(J, c, sc, act)
