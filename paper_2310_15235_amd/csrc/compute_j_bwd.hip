@@ -227,7 +227,10 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
         const float x = (float)sqrt(rij2) * ri.inv_rh;
         const float f = fshape(x);
         const float Kv = f * ri.kfac;
-        const float dKdh = -(2.0f * f + x * fshape_d(x)) * ri.kfac * rinvh[i];
+        // dK/dh = -(2 f + x f') kfac / h: 1/h^3 leaves FP32's range below h =
+        // 1e-13 and above 4e12
+        const double dKdh =
+            (double)(-(2.0f * f + x * fshape_d(x)) * ri.kfac) * (double)rinvh[i];
         double ghi = 0.0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -237,7 +240,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
           red[t][b] += term;
           const double w = (double)gw[i][b];
           gl[b] = w * (double)Kv * E;
-          ghi += w * Lj * E * (double)dKdh;
+          ghi += w * Lj * E * dKdh;
           gt[b] = (float)(-w * term);
           valid = valid || gt[b] != 0.0f;
         }
@@ -894,8 +897,10 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
             const float f = fshape(x);
             const float fd = fshape_d(x);
             const float Kv = f * ri.kfac;
-            const float dKdr = fd * ri.inv_rh * ri.kfac;
-            const float dKdh = -(2.0f * f + x * fd) * ri.kfac * rinvh[ii];
+            // K's derivatives by r and h over kfac (not times it: 1/h^3 leaves
+            // FP32's range below h = 1e-13 and above 4e12)
+            const float fr = fd * ri.inv_rh;
+            const float fh = -(2.0f * f + x * fd) * rinvh[ii];
             const float invs = __builtin_amdgcn_rcpf(W.s[q]);
             const float ratio = rr * invs;
             const int ray = W.ray[q];
@@ -918,16 +923,17 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
                 ps += w * tc * invs;
                 prr -= w * tau * invs;
               }
-              prr += gwb * Le * dKdr;
-              ph += gwb * Le * dKdh;
+              const float wk = gwb * Le * ri.kfac;
+              prr += wk * fr;
+              ph += wk * fh;
             }
             ghf += (double)ph;
             float pp[3] = {0.0f, 0.0f, 0.0f};
             if (rr > 0.0f) {
-              const float ir = prr / rr;
-              pp[0] = ir * dx;
-              pp[1] = ir * dy;
-              pp[2] = ir * dz;
+              const float ir = 1.0f / rr;   // (not prr / rr: L/r^4 leaves the range too)
+              pp[0] = prr * (ir * dx);
+              pp[1] = prr * (ir * dy);
+              pp[2] = prr * (ir * dz);
             }
             for (int o = 1; o < P2; o <<= 1) {
 #pragma unroll

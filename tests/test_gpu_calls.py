@@ -126,3 +126,25 @@ def test_J_in_any_unit_of_length(s, nside):
     act = scenes.active_subset(sc, 0.2, 2)
     J, c = api.compute_J(sc, active=act)
     _close_J(J, c, sc, act)
+
+
+# gradients in units that differ by powers of two, so that every decision and
+# every rounding in range is the same: what differs is the order of atomic sums
+# (1e-5 of a value, 1e-6 of the array's largest)
+@pytest.mark.parametrize("nside", [1, 4])
+@pytest.mark.parametrize("s,m,lum", [(-44, -100, -90), (30, 60, 40), (50, 100, 90), (63, 110, 100)])
+def test_gradients_in_any_unit_of_length(s, m, lum, nside):
+    from paper_2310_15235_amd import api
+    sc = scenes.lognormal_scene(n=3000, seed=3, grid=16, bands=(1.0, 10.0), nside=nside)
+    gJ = np.random.default_rng(1).normal(size=(2, sc.n))
+    S, M, L = 2.0 ** s, 2.0 ** m, 2.0 ** lum
+    f = lambda a, k: np.ascontiguousarray(np.asarray(a, np.float64) * k, np.float32)
+    moved = sc.with_(x=f(sc.x, S), y=f(sc.y, S), z=f(sc.z, S), m=f(sc.m, M),
+                     rho=f(sc.rho, M / S ** 3), kappa=f(sc.kappa, S ** 2 / M), lum=f(sc.lum, L),
+                     box=None if sc.box is None else tuple(v * S for v in sc.box))
+    want = api.compute_J_backward(sc, gJ)
+    got = api.compute_J_backward(moved, gJ)
+    J = L / S ** 2   # unit of J, then of the derivatives by L, kappa and rho
+    for a, b, unit in zip(want, got, (J / L, J / (S ** 2 / M), J / (M / S ** 3))):
+        b = b / unit
+        assert np.all(np.abs(b - a) <= 1e-5 * np.abs(a) + 1e-6 * np.abs(a).max())
