@@ -278,7 +278,9 @@ trevr_status trevr_compute_J_backward(trevr_tree* t, const uint8_t* active, cons
  *                     buffer need not grow, and the forward's state be lost,
  *                     between the two (default 0).  Setting it raises
  *                     trevr_scratch_needed to an estimate for both calls
- *                     (left as it is where that would pass 16 GiB).
+ *                     (left as it is where that would pass 16 GiB).  Without
+ *                     effect on trevr_compute_J_noalloc and on trees with the
+ *                     complex source model, which have no adjoint.
  * Returns TREVR_E_INVALID for an unknown key or a value out of range.
  */
 enum {

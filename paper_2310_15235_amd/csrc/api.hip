@@ -263,7 +263,7 @@ trevr_status trevr_compute_J(trevr_tree* t, const uint8_t* active, const float* 
     return set_error(TREVR_E_INVALID, "TREVR_BACKGROUND needs bg");
   const trevr_status rc = use_stream(t, stream);
   if (rc != TREVR_OK) return rc;
-  return used(t, compute_J_impl(t, active, bg, J, scratch, scratch_bytes));
+  return used(t, compute_J_impl(t, active, bg, J, scratch, scratch_bytes, false));
 }
 
 // Scratch of trevr_compute_J_noalloc: a fixed device array, one copy per GPU.
@@ -308,7 +308,8 @@ trevr_status trevr_compute_J_noalloc(trevr_tree* t, const uint8_t* active, const
   if ((rc = use_stream(t, stream)) != TREVR_OK) return rc;
   rc = used(t, compute_J_impl(t, active, bg, J, ptr,
                               TREVR_NOALLOC_SCRATCH_BYTES +
-                                  std::min(kNoallocParts, parts_bytes(t->num_leaves))));
+                                  std::min(kNoallocParts, parts_bytes(t->num_leaves)),
+                              true));
   if (rc == TREVR_E_CAPACITY) {
     char msg[160];
     std::snprintf(msg, sizeof msg,
@@ -362,7 +363,8 @@ trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value) {
     case TREVR_TUNE_ADJOINT:
       if (value != 0 && value != 1)
         return set_error(TREVR_E_INVALID, "room for the adjoint is 0 or 1");
-      t->adjoint_room = value != 0;
+      // (no adjoint of the complex source model)
+      t->adjoint_room = value != 0 && !(t->p.flags & TREVR_COMPLEX_SRC);
       if (t->adjoint_room) t->scratch_needed = std::max(t->scratch_needed, adjoint_scratch_guess(t));
       return TREVR_OK;
     default:

@@ -2014,7 +2014,7 @@ trevr_status launch_far(const Launch& L, int B, const Scratch& S, const Items& I
 #undef TREVR_BAND_SWITCH
 
 trevr_status compute_J_impl(trevr_tree* T, const uint8_t* active, const float* bg, double* J,
-                            void* scratch, size_t scratch_bytes) {
+                            void* scratch, size_t scratch_bytes, bool fixed) {
   hipStream_t st = T->stream;
   Scratch S = carve_scratch(scratch, T->num_leaves, default_cut_entries(T->num_leaves));
   S.stage_cap = std::min(S.stage_cap, T->stage_limit & ~63u);
@@ -2036,8 +2036,8 @@ trevr_status compute_J_impl(trevr_tree* T, const uint8_t* active, const float* b
   S.tpp = dyn.take<float>(tot[TOT_TPP]);
   S.ptau = dyn.take<float>(tot[TOT_PTAU]);
   take_kept(T, S, dyn, nb);
-  const size_t need =
-      T->adjoint_room ? carve_adjoint(T, S, dyn, tot).end : S.fixed + dyn.off + 256;
+  const size_t need = T->adjoint_room && !fixed ? carve_adjoint(T, S, dyn, tot).end
+                                                : S.fixed + dyn.off + 256;
   T->scratch_needed = need;
   if (scratch_bytes < need) return set_error(TREVR_E_CAPACITY, "scratch too small for the p-p lists");
   if ((rc = near_fill(tree_launch(T), S)) != TREVR_OK) return rc;

@@ -205,8 +205,9 @@ trevr_status hip_check(hipError_t e, const char* what);
 trevr_status build_tree_impl(trevr_tree* t, const float* x, const float* y, const float* z,
                              const float* m, const float* rho, const float* kappa,
                              const float* lum);
+// (fixed: the scratch can neither grow nor serve an adjoint)
 trevr_status compute_J_impl(trevr_tree* t, const uint8_t* active, const float* bg, double* J,
-                            void* scratch, size_t scratch_bytes);
+                            void* scratch, size_t scratch_bytes, bool fixed);
 trevr_status compute_J_backward_impl(trevr_tree* t, const uint8_t* active, const float* bg,
                                      const double* gJ, double* gL, double* gkappa, double* grho,
                                      void* scratch, size_t scratch_bytes);

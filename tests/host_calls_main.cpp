@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -50,31 +51,31 @@ void readback(void* dst, const void*, size_t bytes) {
 
 struct Case {
   trevr_params p{};
-  int64_t n = 4000;
-  std::vector<float> in;
-  std::vector<char> ws, scratch;
-  std::vector<double> out;
+  int64_t n;
+  size_t tree_bytes = 0, scratch_bytes = 0;
+  // never read: no kernel runs
+  std::unique_ptr<char[]> ws, scratch;
+  float in[1];
+  double out[1];
   trevr_tree* t = nullptr;
-  explicit Case(uint32_t flags = TREVR_NEAR_FIELD, int bands = 1, int nside = 1) {
+  explicit Case(uint32_t flags = TREVR_NEAR_FIELD, int bands = 1, int nside = 1, int64_t size = 4000)
+      : n(size) {
     p.nside = nside;
     p.leaf_size = 8;
     p.n_bands = bands;
     p.flags = flags;
     p.theta = 0.75;
-    size_t tb = 0, sb = 0;
-    EXPECT(trevr_workspace_bytes(&p, n, &tb, &sb) == TREVR_OK);
-    in.assign((size_t)n * (bands + 1), 1.0f);
-    ws.resize(tb);
-    scratch.resize(sb);
-    out.resize((size_t)n * bands);
+    EXPECT(trevr_workspace_bytes(&p, n, &tree_bytes, &scratch_bytes) == TREVR_OK);
+    ws.reset(new char[tree_bytes]);
+    scratch.reset(new char[scratch_bytes]);
     fake::on_readback = readback;
   }
   trevr_status build(void* st) {
-    const float* x = in.data();
-    return trevr_build_tree(&p, n, x, x, x, x, x, x, x, ws.data(), ws.size(), st, &t);
+    const float* x = in;
+    return trevr_build_tree(&p, n, x, x, x, x, x, x, x, ws.get(), tree_bytes, st, &t);
   }
   trevr_status forward(void* st, size_t bytes) {
-    return trevr_compute_J(t, nullptr, nullptr, out.data(), scratch.data(), bytes, st);
+    return trevr_compute_J(t, nullptr, in, out, scratch.get(), bytes, st);
   }
   size_t needed() {
     size_t b = 0;
@@ -88,16 +89,16 @@ struct Case {
 void stream_order() {
   using Call = std::function<trevr_status(Case&)>;
   const Call calls[] = {
-      [](Case& c) { return c.forward(B, c.scratch.size()); },
-      [](Case& c) { return trevr_compute_J_noalloc(c.t, nullptr, nullptr, c.out.data(), B); },
+      [](Case& c) { return c.forward(B, c.scratch_bytes); },
+      [](Case& c) { return trevr_compute_J_noalloc(c.t, nullptr, nullptr, c.out, B); },
       [](Case& c) {
-        double* o = c.out.data();
-        return trevr_compute_J_backward(c.t, nullptr, nullptr, o, o, o, o, c.scratch.data(),
-                                        c.scratch.size(), B);
+        double* o = c.out;
+        return trevr_compute_J_backward(c.t, nullptr, nullptr, o, o, o, o, c.scratch.get(),
+                                        c.scratch_bytes, B);
       },
       [](Case& c) {   // refused before anything is launched, then another stream
         EXPECT(c.forward(B, 16) == TREVR_E_CAPACITY);
-        return c.forward((void*)0x3000, c.scratch.size());
+        return c.forward((void*)0x3000, c.scratch_bytes);
       },
   };
   for (const Call& call : calls) {
@@ -132,8 +133,8 @@ void kept_depths() {
           active_buckets = 3;
           Case c(TREVR_NEAR_FIELD | bg | keep, bands, nside);
           EXPECT(c.build(A) == TREVR_OK);
-          EXPECT(trevr_compute_J(c.t, nullptr, c.in.data(), c.out.data(), c.scratch.data(),
-                                 c.scratch.size(), A) == TREVR_OK);
+          EXPECT(trevr_compute_J(c.t, nullptr, c.in, c.out, c.scratch.get(),
+                                 c.scratch_bytes, A) == TREVR_OK);
           need[keep != 0] = c.needed();
           EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
         }
@@ -144,7 +145,35 @@ void kept_depths() {
   active_buckets = 0;
 }
 
+// Room for an adjoint is asked for where one can follow in the same scratch: not
+// in the fixed array (which cannot grow), nor with the complex source model.
+void adjoint_room() {
+  fake::reset();
+  Case c(TREVR_NEAR_FIELD, 1, 1, 4000000);   // accumulators of 96 MB, past the array
+  EXPECT(c.build(A) == TREVR_OK);
+  EXPECT(trevr_compute_J_noalloc(c.t, nullptr, nullptr, c.out, A) == TREVR_OK);
+  EXPECT(c.forward(A, c.scratch_bytes) == TREVR_OK);
+  const size_t plain = c.needed();
+  EXPECT(trevr_tree_tune(c.t, TREVR_TUNE_ADJOINT, 1) == TREVR_OK);
+  EXPECT(trevr_compute_J_noalloc(c.t, nullptr, nullptr, c.out, A) == TREVR_OK);
+  EXPECT(c.forward(A, plain) == TREVR_E_CAPACITY);
+  EXPECT(c.needed() >= plain + 3 * sizeof(double) * (size_t)c.n);
+  EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
+  fake::reset();
+  Case d(TREVR_NEAR_FIELD | TREVR_COMPLEX_SRC, 1, 1);
+  EXPECT(d.build(A) == TREVR_OK);
+  EXPECT(trevr_tree_tune(d.t, TREVR_TUNE_ADJOINT, 1) == TREVR_OK);
+  EXPECT(d.needed() == 0);
+  EXPECT(d.forward(A, d.scratch_bytes) == TREVR_OK);
+  const size_t with = d.needed();
+  EXPECT(trevr_tree_tune(d.t, TREVR_TUNE_ADJOINT, 0) == TREVR_OK);
+  EXPECT(d.forward(A, d.scratch_bytes) == TREVR_OK);
+  EXPECT(d.needed() == with);
+  EXPECT(trevr_tree_destroy(d.t) == TREVR_OK);
+}
+
 const std::map<std::string, void (*)()> cases = {
+    {"adjoint_room", adjoint_room},
     {"kept_depths", kept_depths},
     {"stream_order", stream_order},
 };
