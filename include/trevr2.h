@@ -281,13 +281,17 @@ trevr_status trevr_compute_J_backward(trevr_tree* t, const uint8_t* active, cons
  *                     (left as it is where that would pass 16 GiB).  Without
  *                     effect on trevr_compute_J_noalloc and on trees with the
  *                     complex source model, which have no adjoint.
+ *   TREVR_TUNE_RECEIVERS  elements that are active at most, in [0, n] (default
+ *                     n): what the estimate goes by that TREVR_TUNE_ADJOINT makes
+ *                     when set after it.
  * Returns TREVR_E_INVALID for an unknown key or a value out of range.
  */
 enum {
   TREVR_TUNE_STACK = 0,
   TREVR_TUNE_CUT = 1,
   TREVR_TUNE_STAGE = 2,
-  TREVR_TUNE_ADJOINT = 3
+  TREVR_TUNE_ADJOINT = 3,
+  TREVR_TUNE_RECEIVERS = 4
 };
 trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value);
 

@@ -34,7 +34,7 @@ EXPORTED = ("trevr_workspace_bytes", "trevr_build_tree", "trevr_compute_J",
             "trevr_compute_J_noalloc", "trevr_forest_profile_enable",
             "trevr_forest_profile_read", "trevr_forest_job_log")
 NOALLOC_SCRATCH_BYTES = 64 << 20   # the fixed device array of trevr_compute_J_noalloc
-TUNE_STACK, TUNE_CUT, TUNE_STAGE, TUNE_ADJOINT = 0, 1, 2, 3
+TUNE_STACK, TUNE_CUT, TUNE_STAGE, TUNE_ADJOINT, TUNE_RECEIVERS = 0, 1, 2, 3, 4
 CONFIGS = 8          # launch configurations of the forest autotuner
 PROF_NAMES = ("setup", "walk", "reduce", "near", "adj_reduce", "adj_near", "adj_tree", "pp_src",
               "adj_pp_src")
@@ -269,11 +269,17 @@ class Tree:
     def scratch(self):
         return self._scratch
 
-    def reserve_adjoint(self):
+    def reserve_adjoint(self, active=None):
         """Room for compute_J and its adjoint in one scratch from the start: the
         calls then find their state again instead of growing the buffer (and
-        redoing the bucket setup, then the forward) on the way."""
+        redoing the bucket setup, then the forward) on the way.  The buffer is an
+        estimate, some 20% more than what is used in the usual media, 16 GiB at
+        most; with the calls' active flags it goes by how many are set."""
         torch = _torch()
+        # counting waits for the flags: only where they may save much (the two
+        # columns per receiver, ray and band are most of the estimate)
+        if active is not None and 8 * self.n * 12 * self.nside ** 2 * self.B > 1 << 28:
+            self.tune(TUNE_RECEIVERS, int(torch.count_nonzero(active)))
         self.tune(TUNE_ADJOINT, 1)
         need = ctypes.c_size_t()
         _check(lib().trevr_scratch_needed(self.handle, ctypes.byref(need)), "trevr_scratch_needed")
@@ -623,7 +629,7 @@ class TrevrJ:
                     T = Tree(x.detach(), y.detach(), z.detach(), m.detach(), rho.detach(),
                              kappa.detach(), lum.detach(), **opts)
                     if any(ctx.needs_input_grad):
-                        T.reserve_adjoint()
+                        T.reserve_adjoint(active)
                     J = T.compute_J(active, bg)
                     ctx.tree, ctx.active, ctx.bg = T, active, bg
                     ctx.dtypes = (rho.dtype, kappa.dtype, lum.dtype)

@@ -193,6 +193,7 @@ trevr_status trevr_build_tree(const trevr_params* p, int64_t n, const float* x, 
   T->cut_default = kCutCap;
   T->stage_limit = (uint32_t)kStageCap;
   T->adjoint_room = false;
+  T->receivers = n;
   const size_t need = layout_tree(*p, n, T->nclass, nullptr, nullptr);
   if (tree_ws_bytes < need) {
     delete T;
@@ -366,6 +367,11 @@ trevr_status trevr_tree_tune(trevr_tree* t, int key, int64_t value) {
       // (no adjoint of the complex source model)
       t->adjoint_room = value != 0 && !(t->p.flags & TREVR_COMPLEX_SRC);
       if (t->adjoint_room) t->scratch_needed = std::max(t->scratch_needed, adjoint_scratch_guess(t));
+      return TREVR_OK;
+    case TREVR_TUNE_RECEIVERS:
+      if (value < 0 || value > t->n)
+        return set_error(TREVR_E_INVALID, "receivers must be in [0, n]");
+      t->receivers = value;
       return TREVR_OK;
     default:
       return set_error(TREVR_E_INVALID, "unknown tuning key");

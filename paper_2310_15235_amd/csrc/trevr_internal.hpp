@@ -193,6 +193,7 @@ struct trevr_tree {
   uint32_t cut_default;                     // cut-list entries per bucket to try first
   uint32_t stage_limit;                     // most staging words per bucket for p-p sets
   bool adjoint_room;                        // compute_J asks for the adjoint's scratch too
+  int64_t receivers;                        // active elements, at most (for the estimate)
   trevr::Prof prof;                         // kernel timing (trevr_profile_enable)
 };
 

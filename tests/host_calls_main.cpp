@@ -172,7 +172,30 @@ void adjoint_room() {
   EXPECT(trevr_tree_destroy(d.t) == TREVR_OK);
 }
 
+// The estimate for a forward and its adjoint takes the receivers that it is told
+// of: two columns per ray and band of each.
+void adjoint_estimate() {
+  const size_t rays = 48, bands = 2;
+  size_t need[3];
+  const int64_t told[3] = {-1, 4000, 400};   // -1: nothing said, every element
+  for (int k = 0; k < 3; ++k) {
+    fake::reset();
+    Case c(TREVR_NEAR_FIELD, bands, 2);
+    EXPECT(c.build(A) == TREVR_OK);
+    if (told[k] >= 0) EXPECT(trevr_tree_tune(c.t, TREVR_TUNE_RECEIVERS, told[k]) == TREVR_OK);
+    EXPECT(trevr_tree_tune(c.t, TREVR_TUNE_ADJOINT, 1) == TREVR_OK);
+    need[k] = c.needed();
+    EXPECT(trevr_tree_tune(c.t, TREVR_TUNE_RECEIVERS, -1) == TREVR_E_INVALID);
+    EXPECT(trevr_tree_tune(c.t, TREVR_TUNE_RECEIVERS, c.n + 1) == TREVR_E_INVALID);
+    EXPECT(trevr_tree_destroy(c.t) == TREVR_OK);
+  }
+  EXPECT(need[0] == need[1]);
+  const size_t less = (4000 - 400) * rays * bands * 2 * sizeof(float);
+  EXPECT(need[2] + less <= need[1]);
+}
+
 const std::map<std::string, void (*)()> cases = {
+    {"adjoint_estimate", adjoint_estimate},
     {"adjoint_room", adjoint_room},
     {"kept_depths", kept_depths},
     {"stream_order", stream_order},

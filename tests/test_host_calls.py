@@ -23,7 +23,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["stream_order", "kept_depths", "adjoint_room"])
+@pytest.mark.parametrize("case", ["stream_order", "kept_depths", "adjoint_room", "adjoint_estimate"])
 def test_host_calls(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
