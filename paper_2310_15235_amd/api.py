@@ -613,7 +613,9 @@ class TrevrJ:
     ``TrevrJ.apply(x, y, z, m, rho, kappa, lum, active, bg, opts)`` builds the
     tree and returns J [B, n] (float64).  The backward pass calls
     trevr_compute_J_backward on the same tree; positions, masses, the active
-    set and bg get no gradient.  ``opts`` holds the Tree keyword arguments
+    set and bg get no gradient.  Where gradients are recorded, the tree's scratch
+    is taken large enough for both passes at once (Tree.reserve_adjoint), and
+    held until the graph goes.  ``opts`` holds the Tree keyword arguments
     (nside, leaf_size, theta, flags, rpp_min, box)."""
 
     _fn = None
@@ -625,10 +627,10 @@ class TrevrJ:
 
             class _F(torch.autograd.Function):
                 @staticmethod
-                def forward(ctx, x, y, z, m, rho, kappa, lum, active, bg, opts):
+                def forward(ctx, x, y, z, m, rho, kappa, lum, active, bg, opts, recorded):
                     T = Tree(x.detach(), y.detach(), z.detach(), m.detach(), rho.detach(),
                              kappa.detach(), lum.detach(), **opts)
-                    if any(ctx.needs_input_grad):
+                    if recorded:
                         T.reserve_adjoint(active)
                     J = T.compute_J(active, bg)
                     ctx.tree, ctx.active, ctx.bg = T, active, bg
@@ -641,7 +643,11 @@ class TrevrJ:
                                                              ctx.active, ctx.bg)
                     dr, dk, dl = ctx.dtypes
                     return (None, None, None, None, gr.to(dr), gk.to(dk), gL.to(dl), None, None,
-                            None)
+                            None, None)
 
             cls._fn = _F
-        return cls._fn.apply(*args)
+        # (in forward, ctx.needs_input_grad is set without a recording too)
+        torch = _torch()
+        recorded = torch.is_grad_enabled() and any(
+            isinstance(a, torch.Tensor) and a.requires_grad for a in args)
+        return cls._fn.apply(*args, recorded)
