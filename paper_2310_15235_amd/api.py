@@ -166,6 +166,8 @@ def _dev(t, dtype):
 class Tree:
     """A radiation tree built on the GPU; owns its workspace tensor."""
 
+    _room = False   # reserve_adjoint: compute_J asks for the adjoint's scratch too
+
     def __init__(self, x, y, z, m, rho, kappa, lum, *, nside=2, leaf_size=8, theta=0.75,
                  flags=THICK_CORR | NEAR_FIELD, rpp_min=0.0, box=None, scratch=None,
                  target=None):
@@ -232,7 +234,8 @@ class Tree:
 
     def _call_with_scratch(self, fn, where):
         """Run fn(scratch_ptr, scratch_bytes); on TREVR_E_CAPACITY grow the
-        scratch to the size the library reports and run once more."""
+        scratch to the size the library reports and run once more.  Where that
+        does not fit the memory and holds room for an adjoint, run without."""
         torch = _torch()
         for _ in range(2):
             st = fn(ctypes.c_void_p(self._scratch.data_ptr()), self._scratch.numel())
@@ -243,9 +246,25 @@ class Tree:
                    "trevr_scratch_needed")
             if need.value <= self._scratch.numel():
                 break
-            self._scratch = torch.empty(int(need.value * 1.1) + 4096, dtype=torch.uint8,
-                                        device=self.device)
+            size = int(need.value * 1.1) + 4096
+            try:
+                self._scratch = torch.empty(size, dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:
+                if not self._room:
+                    raise
+                self._drop_room()
+                return self._call_with_scratch(fn, where)
         _check(st, where)
+
+    def _drop_room(self):
+        """Back to a scratch that was never reserved: the forward may fit where
+        both passes do not, and the adjoint asks for what it needs itself."""
+        torch = _torch()
+        self._room = False
+        self.tune(TUNE_ADJOINT, 0)
+        self._scratch = None   # the reserved one goes before another is taken
+        self._scratch = torch.empty(workspace_bytes(self.params, self.n)[1], dtype=torch.uint8,
+                                    device=self.device)
 
     def compute_J_backward(self, gJ, active=None, bg=None, out=None):
         """Adjoint of compute_J: (dE/dL [B, n], dE/dkappa [B, n], dE/drho [n])
@@ -281,6 +300,7 @@ class Tree:
         if active is not None and 8 * self.n * 12 * self.nside ** 2 * self.B > 1 << 28:
             self.tune(TUNE_RECEIVERS, int(torch.count_nonzero(active)))
         self.tune(TUNE_ADJOINT, 1)
+        self._room = True
         need = ctypes.c_size_t()
         _check(lib().trevr_scratch_needed(self.handle, ctypes.byref(need)), "trevr_scratch_needed")
         if need.value > self._scratch.numel():
