@@ -650,10 +650,11 @@ __device__ inline void run_tab_entry(const float s[3], float reach, float (*jr)[
   jr[t][0] = s[0];
   jr[t][1] = s[1];
   jr[t][2] = s[2];
-  jinv[t] = L2 > 0.0f ? 1.0f / L2 : 0.0f;
+  const float inv = L2 > 0.0f ? 1.0f / L2 : 0.0f;
+  jinv[t] = inv;
   lim[t] = (cull_sqrt(L2) + reach) * (1.0f + 1e-5f);
   k2[t] = L2 > R2 ? (L2 - R2) / L2 : 0.0f;
-  m2[t] = L2 > R2 ? R2 / (L2 - R2) * jinv[t] : -1.0f;
+  m2[t] = L2 > R2 ? R2 / (L2 - R2) * inv : -1.0f;
 }
 
 // Whether p comes within A - R u of the point u s of the segment from the
