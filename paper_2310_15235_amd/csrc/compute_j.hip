@@ -518,8 +518,13 @@ __global__ void __launch_bounds__(64, 5) k_walk(const DevTree* __restrict__ TT, 
 // the directed ray), 64 at a time first with a conservative FP32 test, then
 // with the exact FP64 one, and adds each hit's kappa Sigma to the (receiver,
 // ray) sums in LDS, written out once per group.
+//
+// Four workgroups per CU at every band count: from 13 bands on the registers
+// would leave three (129 to 136 of them against 128; 16 bands, 2^17 clumpy
+// elements at N_side 1: 0.912 ms with three, 0.882 with four).  Below, the bound
+// changes what is spilled and costs 5 to 14%, so it is not set there.
 template <int NB>
-__global__ void __launch_bounds__(kNT) k_pp_rays(const DevTree* __restrict__ TT, Items I,
+__global__ void __launch_bounds__(kNT, NB >= 13 ? 4 : 1) k_pp_rays(const DevTree* __restrict__ TT, Items I,
                                                 const uint32_t* blist, const uint32_t* bscene,
                                                 const uint32_t* noff, const uint32_t* nidx,
                                                 const uint32_t* toff, const uint8_t* active,
