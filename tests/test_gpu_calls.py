@@ -148,3 +148,30 @@ def test_gradients_in_any_unit_of_length(s, m, lum, nside):
     for a, b, unit in zip(want, got, (J / L, J / (S ** 2 / M), J / (M / S ** 3))):
         b = b / unit
         assert np.all(np.abs(b - a) <= 1e-5 * np.abs(a) + 1e-6 * np.abs(a).max())
+
+
+# more than 2^20 buckets in one launch: the setup's and the walk's workgroups go
+# on to buckets a grid's width apart.  A forest of two scenes with a bucket per
+# element against each scene's own tree, whose launches stay below (FP32 rounding
+# of atomic sums: 1e-5)
+def test_more_buckets_than_the_grid_bound():
+    import torch
+    from paper_2310_15235_amd import api
+    scs = [scenes.uniform_scene(n=n, seed=n, n_src=60, bands=(1.0,), nside=1, leaf_size=1, theta=1.2)
+           for n in (600001, 500000)]
+    F = api.Forest(scs)
+    J = F.split(F.compute_J())
+    F.check()
+    counts = [F.counters(s) for s in range(2)]
+    assert sum(c["buckets"] for c in counts) > 1 << 20
+    for sc, Jf, cf in zip(scs, J, counts):
+        T = api.Tree.from_scene(sc)
+        Jt = T.compute_J()
+        T.check()
+        ct = T.counters()
+        assert bool(((Jf - Jt).abs() <= 1e-5 * Jt.abs()).all())
+        for k in COUNTS:
+            assert cf[k] == ct[k], (k, cf[k], ct[k])
+        T.close()
+    F.close()
+    torch.cuda.synchronize()
