@@ -12,8 +12,8 @@
 //                     cells, opened buckets and resolved element sources, each
 //                     source tagged with its HEALPix pixel;
 //   k_pp_rays         256 threads per bucket take (p-p element, receiver)
-//                     pairs, each testing the element's rays of the
-//                     candidate table: per receiver and ray the p-p optical depth
+//                     pairs, each testing the rays of the element's HEALPix
+//                     ring range: per receiver and ray the p-p optical depth
 //                     (kept for the far field);
 //   k_pp_src          the attenuated p-p sources (J starts with these):
 //                     element-major for sets of 256 or more (or whose pairs
@@ -211,37 +211,37 @@ __device__ inline Sphere grow_sphere(const DevTree& T, uint32_t leaf, const doub
 // The spheres of the active buckets; their sets are left as runs (NearOut) in
 // the bucket's stage_cap staging words, {run count or kNoRuns, unused,
 // runs...}, for k_near_fill.
-// Bound by its chain of dependent reads: five wavefronts per SIMD (102
-// registers of the 106 it would take) beat four, 2^18 clumpy elements 0.86 ->
-// 0.82 ms; six (85, with spills) took 0.97.
+// Bound by its chain of dependent reads: five wavefronts per SIMD (96
+// registers, five spilled) beat four, 2^18 clumpy elements 0.86 -> 0.82 ms; six
+// (more spilled) took 0.97.
 template <int SC>
 __global__ void __launch_bounds__(64, 5) k_setup(const DevTree* __restrict__ TT, Items I,
-                                              const uint32_t* blist, const uint32_t* bscene,
-                                              double* brad, double* bprev, uint32_t* barg,
-                                              uint32_t* ncnt, uint32_t* nlumc, uint32_t* ovf,
-                                              uint32_t* stage, uint32_t stage_cap) {
+                                                 const uint32_t* blist, const uint32_t* bscene,
+                                                 double* brad, double* bprev, uint32_t* barg,
+                                                 uint32_t* ncnt, uint32_t* nlumc, uint32_t* ovf,
+                                                 uint32_t* stage, uint32_t stage_cap) {
   __shared__ uint32_t stack[SC];
   __shared__ uint2 leafq[kLeafQ];
   const int lane = threadIdx.x;
   for (uint32_t b = grid_item(I); b != kNoItem; b = grid_next(I, b)) {
-  const DevTree& T = TT[bscene[b]];
-  const uint32_t leaf = blist[b];
-  double c[3];
-  leaf_centre(T, leaf, c);
-  Sphere s{0.0, -1.0, 0u, 0u, 0xFFFFFFFFu, false};
-  NearOut o{stage_cap ? stage + (size_t)b * stage_cap + 2 : nullptr, true, 0u, 0u, 0u,
-            stage_cap ? (stage_cap - 2u) / 2u : 0u};
-  if (T.flags & TREVR_NEAR_FIELD) s = grow_sphere<SC>(T, leaf, c, stack, leafq, o);
-  if (lane == 0) {
-    brad[b] = s.r;
-    bprev[b] = s.rprev;
-    barg[b] = s.arg;
-    ncnt[b] = s.cnt;
-    nlumc[b] = s.nlum;
-    if (stage_cap) stage[(size_t)b * stage_cap] = o.out ? o.nrun : kNoRuns;
-    if (s.overflow) atomicOr(ovf, OVF_SETUP);
-  }
-  __syncthreads();
+    const DevTree& T = TT[bscene[b]];
+    const uint32_t leaf = blist[b];
+    double c[3];
+    leaf_centre(T, leaf, c);
+    Sphere s{0.0, -1.0, 0u, 0u, 0xFFFFFFFFu, false};
+    NearOut o{stage_cap ? stage + (size_t)b * stage_cap + 2 : nullptr, true, 0u, 0u, 0u,
+              stage_cap ? (stage_cap - 2u) / 2u : 0u};
+    if (T.flags & TREVR_NEAR_FIELD) s = grow_sphere<SC>(T, leaf, c, stack, leafq, o);
+    if (lane == 0) {
+      brad[b] = s.r;
+      bprev[b] = s.rprev;
+      barg[b] = s.arg;
+      ncnt[b] = s.cnt;
+      nlumc[b] = s.nlum;
+      if (stage_cap) stage[(size_t)b * stage_cap] = o.out ? o.nrun : kNoRuns;
+      if (s.overflow) atomicOr(ovf, OVF_SETUP);
+    }
+    __syncthreads();
   }
 }
 
@@ -374,9 +374,9 @@ __global__ void __launch_bounds__(64) k_near_fill(const DevTree* __restrict__ TT
 // 0.46 -> 0.47).
 template <int SC>
 __global__ void __launch_bounds__(64, 5) k_walk(const DevTree* __restrict__ TT, Items I,
-                                             const uint32_t* blist, const uint32_t* bscene,
-                                             const double* brad, uint2* cut, uint32_t cap,
-                                             uint32_t* bstat, uint32_t* ovf) {
+                                                const uint32_t* blist, const uint32_t* bscene,
+                                                const double* brad, uint2* cut, uint32_t cap,
+                                                uint32_t* bstat, uint32_t* ovf) {
   __shared__ uint32_t stack[SC];
   __shared__ uint32_t lfirst[64], lbeg[64];
   const int lane = threadIdx.x;
@@ -521,8 +521,9 @@ __global__ void __launch_bounds__(64, 5) k_walk(const DevTree* __restrict__ TT, 
 //
 // Four workgroups per CU at every band count: from 13 bands on the registers
 // would leave three (129 to 136 of them against 128; 16 bands, 2^17 clumpy
-// elements at N_side 1: 0.912 ms with three, 0.882 with four).  Below, the bound
-// changes what is spilled and costs 5 to 14%, so it is not set there.
+// elements at N_side 1: 0.912 ms with three, 0.882 with four).  Below, where
+// four fit anyway, the bound changes how registers are given out and costs 14% on
+// the batched workload, so it is not set there.
 template <int NB>
 __global__ void __launch_bounds__(kNT, NB >= 13 ? 4 : 1) k_pp_rays(const DevTree* __restrict__ TT, Items I,
                                                 const uint32_t* blist, const uint32_t* bscene,
@@ -1469,7 +1470,10 @@ __global__ void __launch_bounds__(256) k_cost_bins(const DevTree* __restrict__ T
 // Also the parts of the buckets of each bin for the p-p sources (split): a
 // bucket's parts are doubled, up to kMostParts and the passes its bin's buckets
 // have, while one would cost more than the band count's total over kSplitItems
-// items per workgroup slot.  (Scene by scene: whole buckets.)
+// items per workgroup slot.  (Scene by scene: whole buckets.)  The slots are this
+// chip's, and the total is the whole call's: a lone tree of more than 65536
+// buckets, which runs in batches, is split less than each batch by itself would
+// be.
 __global__ void __launch_bounds__(1024) k_scan_bins(uint32_t* bins, uint32_t order, uint32_t* rng,
                                                     const uint32_t* bpass, uint4* split) {
   static_assert(kMaxBands * kCostBins <= 1024, "one bin per thread");
@@ -1611,7 +1615,8 @@ static unsigned grid_of(int64_t work, int threads) {
 
 // Grids of the kernels of one wavefront per bucket (setup, p-p list fill,
 // walk), whose bucket count is on the device: a workgroup per leaf of the
-// trees, up to a bound, beyond which they take buckets a grid's width apart.
+// trees, up to a bound, beyond which they take buckets a grid's width apart (a
+// launch may not hold 2^32 threads, 67M buckets: there has to be one).
 // Setup and walk read the tree, and buckets next to each other read the same
 // parts of it: workgroups that go on to buckets far away spread an XCD's L2
 // over many scenes (20 scenes of 2^12 to 2^17 elements: 6.10 and 1.50 ms with

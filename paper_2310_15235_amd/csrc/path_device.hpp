@@ -91,7 +91,12 @@ __device__ inline uint32_t next_item(const Items& I, uint32_t* s_item, bool& fir
 // N_side 4 8.13 -> 5.60 ms, of 4096 at N_side 2 248 -> 155 us (adjoint 257 ->
 // 148), of 48 small scenes 3.95 -> 2.75 ms.  Within a bin the items run through
 // the buckets' first parts, then their second, ...: parts of one bucket at work
-// together add to the same elements in the adjoint (8% of its time).
+// together add to the same elements in the adjoint (8% of its time).  A launch
+// that needs no parts pays for them: on the batched workload k_pp_src takes 472
+// ms per forward (heaviest first) and 477 (scene by scene) where claims of whole
+// buckets, without the part, its passes and the added J, took 464 and 470; neither
+// keeping the part in LDS (15 registers spilled instead of 20) nor reading the
+// table and the counter together changed that.
 struct WorkPart {
   uint32_t item, bucket, part, parts;   // item: over all band counts (job log)
 };
@@ -1050,8 +1055,6 @@ template <int NB> struct PpRayGroup {
 
 // Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
 // their reciprocals and an FP32 copy (conservative candidate filter).
-// Directions of one group of up to 64 rays: FP64 (exact ray-box tests),
-// their reciprocals and an FP32 copy (conservative candidate filter).
 struct RayGroup {
   double n[64][3], inv[64][3];
   float nf[64][3];
@@ -1121,7 +1124,7 @@ constexpr uint32_t kSrcCellBit = 0x80000000u;
 // What bounds it is the chain of waits: 256 entries listed and staged at a
 // time, two barriers and two waits on memory each, and an index for the order,
 // through which every later look at a ray's sources went, cost k_far 3.02 ms
-// where it takes 2.78 (clumpy, three bands), 3.55 -> 3.17 (2^21, 1% active).
+// where it takes 2.83 (clumpy, three bands), 3.55 -> 3.29 (2^21, 1% active).
 constexpr int kStagePer = 8, kStageRound = kStagePer * kFT;
 template <int CAP, int NB, bool kSfx>
 __device__ inline uint32_t stage_window(const DevTree& T, const uint2* mycut, uint32_t ncut,

@@ -21,7 +21,7 @@
 // 2^18 elements of one band): before, one launch per level and step (200
 // launches, the host reading the levels back every six), now some 30 with one
 // readback.  Kernels of a build, before -> now: 4096 elements of one band 540 ->
-// 165 us, 2^18 of three bands 1360 -> 400 us, 2^21 of two bands and 24 direction
+// 137 us, 2^18 of three bands 1360 -> 355 us, 2^21 of two bands and 24 direction
 // classes 3500 -> 1480 us.
 
 #include <algorithm>
@@ -898,7 +898,7 @@ __device__ inline void cell_role(const TreeBufs& tb, uint32_t p, int role, int B
 // its cells from the deepest level up, a barrier between levels (the
 // children's values were stored by the same workgroup).  One launch for some
 // ten levels; level by level over the whole tree, moments and averages took 528
-// us in 50 launches (2^18 elements, three bands), now 103 here and 86 in k_cells.
+// us in 50 launches (2^18 elements, three bands), now 91 here and 92 in k_cells.
 __global__ void __launch_bounds__(256) k_subtrees(int64_t n, int B, int nclass, int linear,
                                                   TreeBufs tb) {
   constexpr int kMost = 2 * kSubtree;
@@ -981,7 +981,7 @@ __global__ void __launch_bounds__(1024) k_cells(int dhi, int dlo, int B, int ncl
 // combine so that attenuated luminosities add, per band:
 //   L e^{-tau} = L_1 e^{-tau_1} + L_2 e^{-tau_2},
 // and the node keeps alpha = tau / d (zero when d = 0 or L = 0).  Runs after
-// k_alpha of the same level (it reads the node's transmission averages).
+// k_subtrees and k_cells, level by level (it reads the transmission averages).
 __global__ void k_csrc(TreeBufs tb, uint32_t lb, uint32_t le, int B, int nclass, int nray) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (gid >= (int64_t)(le - lb) * nray) return;
