@@ -99,12 +99,21 @@ __device__ inline double thick_dC(double tau) {
   return (exp(-tau) - thick_C(tau)) / tau;
 }
 
-// Per receiver of a chunk: w_ib = dE/dJ_ib C_ib (the adjoint of the raw J)
-// and 1/h_i.  Threads t < nrecv * NB.
+// Per receiver of a chunk: w_ib = dE/dJ_ib C_ib (the adjoint of the raw J), and
+// what the kernel's derivatives by h and r need.  Threads t < nrecv * NB.
+//
+// Those derivatives hold 1/h^3, which leaves FP32's range below h = 1e-13 and
+// above 4e12: they are formed with every length over 2^e, e the binary exponent of
+// h, and scaled when they have met the luminosity, which rounds no value
+// differently.
+struct RecvScaled {
+  float inv_h, inv_rh, kfac;   // 1/h, 1/(R h), 1/(2 h^2) times 2^e, 2^e, 2^2e
+  int e;
+};
 template <int NB>
 __device__ inline void load_receiver_adjoints(const DevTree& T, const double* gJ,
                                               const RecvInfo* recv, int nrecv, float (*gw)[NB],
-                                              float* rinvh) {
+                                              RecvScaled* rs) {
   const int t = threadIdx.x;
   const int64_t n = T.n;
   if (t < nrecv * NB) {
@@ -115,7 +124,11 @@ __device__ inline void load_receiver_adjoints(const DevTree& T, const double* gJ
       C = thick_C((double)T.kappa[(int64_t)b * n + sl] * (double)T.rho[sl] * recv[i].h);
     gw[i][b] = (float)(gJ[(int64_t)b * n + T.perm[sl]] * C);
   }
-  if (t < nrecv) rinvh[t] = (float)(1.0 / recv[t].h);
+  if (t < nrecv) {
+    const int e = ilogb(recv[t].h);
+    rs[t] = RecvScaled{ldexpf((float)(1.0 / recv[t].h), e), ldexpf(recv[t].inv_rh, e),
+                       ldexpf(recv[t].kfac, 2 * e), e};
+  }
   __syncthreads();
 }
 
@@ -154,7 +167,8 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
   __shared__ PairTile<NB> PT;
   __shared__ RecvInfo recv[kRMax];
   __shared__ uint32_t nrecv_s, s_part[4];
-  __shared__ float gw[kRMax][NB], rinvh[kRMax];
+  __shared__ float gw[kRMax][NB];
+  __shared__ RecvScaled rs[kRMax];
   __shared__ double red[kNT][NB];
   __shared__ double redh[kNT];
   __shared__ uint16_t jobq[kNT / 64][2][kJobQ];   // per wavefront: (element lane, source run)
@@ -191,7 +205,7 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
   for (;;) {
     const int nrecv = load_receivers(T, act, c, member, lk.x + lk.y, recv, &nrecv_s);
     if (nrecv == 0) break;
-    load_receiver_adjoints<NB>(T, gJ, recv, nrecv, gw, rinvh);
+    load_receiver_adjoints<NB>(T, gJ, recv, nrecv, gw, rs);
     const float* pt = ptau + (int64_t)poff[bucket] + (int64_t)nact * nl * NB;
     const int stride = (kNT / nrecv) * nrecv;       // thread t keeps receiver t % nrecv
     const int i = t % nrecv;
@@ -227,10 +241,8 @@ __global__ void __launch_bounds__(kNT, 4) k_pp_src_bwd(const DevTree* __restrict
         const float x = (float)sqrt(rij2) * ri.inv_rh;
         const float f = fshape(x);
         const float Kv = f * ri.kfac;
-        // dK/dh = -(2 f + x f') kfac / h: 1/h^3 leaves FP32's range below h =
-        // 1e-13 and above 4e12
         const double dKdh =
-            (double)(-(2.0f * f + x * fshape_d(x)) * ri.kfac) * (double)rinvh[i];
+            ldexp((double)(-(2.0f * f + x * fshape_d(x)) * rs[i].kfac * rs[i].inv_h), -3 * rs[i].e);
         double ghi = 0.0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -729,7 +741,8 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
   __shared__ float tpp[kRMax][64][NB], gtpp[kRMax][64][NB];
   __shared__ float tex[64][NB], gtex[64][NB];
   __shared__ RecvInfo recv[kRMax];
-  __shared__ float gw[kRMax][NB], rinvh[kRMax];
+  __shared__ float gw[kRMax][NB];
+  __shared__ RecvScaled rs[kRMax];
   __shared__ uint32_t nrecv_s, wcnt[kStagePer * (kFT / 64)], s_item;
   __shared__ double redr[kFT / 64];
   // the sweeps' hit queues and, after them, the receivers' sums
@@ -776,7 +789,7 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
   for (;;) {
     const int nrecv = load_receivers(T, act, c, member, lk.x + lk.y, recv, &nrecv_s);
     if (nrecv == 0) break;
-    load_receiver_adjoints<NB>(T, gJ, recv, nrecv, gw, rinvh);
+    load_receiver_adjoints<NB>(T, gJ, recv, nrecv, gw, rs);
     int P2 = 1;
     while (P2 < nrecv) P2 <<= 1;
     const int my_i = t & (P2 - 1);
@@ -897,10 +910,9 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
             const float f = fshape(x);
             const float fd = fshape_d(x);
             const float Kv = f * ri.kfac;
-            // K's derivatives by r and h over kfac (not times it: 1/h^3 leaves
-            // FP32's range below h = 1e-13 and above 4e12)
-            const float fr = fd * ri.inv_rh;
-            const float fh = -(2.0f * f + x * fd) * rinvh[ii];
+            const int he = rs[ii].e;   // lengths over 2^he (RecvScaled)
+            const float dKdr = fd * rs[ii].inv_rh * rs[ii].kfac;
+            const float dKdh = -(2.0f * f + x * fd) * rs[ii].kfac * rs[ii].inv_h;
             const float invs = __builtin_amdgcn_rcpf(W.s[q]);
             const float ratio = rr * invs;
             const int ray = W.ray[q];
@@ -923,17 +935,16 @@ __global__ void __launch_bounds__(kFT, BwdCfg<NB>::waves)
                 ps += w * tc * invs;
                 prr -= w * tau * invs;
               }
-              const float wk = gwb * Le * ri.kfac;
-              prr += wk * fr;
-              ph += wk * fh;
+              prr += ldexpf(gwb * Le * dKdr, -3 * he);
+              ph += gwb * Le * dKdh;
             }
-            ghf += (double)ph;
+            ghf += ldexp((double)ph, -3 * he);
             float pp[3] = {0.0f, 0.0f, 0.0f};
             if (rr > 0.0f) {
-              const float ir = 1.0f / rr;   // (not prr / rr: L/r^4 leaves the range too)
-              pp[0] = prr * (ir * dx);
-              pp[1] = prr * (ir * dy);
-              pp[2] = prr * (ir * dz);
+              const float ir = prr / ldexpf(rr, -he);
+              pp[0] = ir * ldexpf(dx, -he);
+              pp[1] = ir * ldexpf(dy, -he);
+              pp[2] = ir * ldexpf(dz, -he);
             }
             for (int o = 1; o < P2; o <<= 1) {
 #pragma unroll
